@@ -48,10 +48,12 @@ PEAK_GBS = 8000.0
 # the roofline line times for each: the launches from the first certificate
 # kernel to the end of phase 0 (of the merge levels inside the kernel, for the
 # one-workgroup-per-node plan)
-PLAN_NAMES = {0: "many workgroups per chunk", 1: "one workgroup per node", 2: "whole tree in LDS"}
+PLAN_NAMES = {0: "many workgroups per chunk", 1: "one workgroup per node", 2: "whole tree in LDS",
+              3: "whole list in one pass"}
 UNIT_NAMES = {0: "phase 0 per query (k_phase0 stages and the compressions between them)",
               1: "k_solo per query (phase 0 and the merge levels it runs, one workgroup per node)",
-              2: "k_batched per query (phase 0 and every merge, in LDS)"}
+              2: "k_batched per query (phase 0 and every merge, in LDS)",
+              3: "certificate per query (k_rows stages, path compressions, code table and k_filter)"}
 CSRC = os.path.join(ROOT, "paper_2108_07346_amd", "csrc")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 

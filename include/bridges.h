@@ -84,6 +84,11 @@ int br_destroy(br_ctx* ctx);
  *             left outside F).  cert_cap >= min(E, 2(V-1)) always suffices.
  *   d_counts  device int64 [3]: |F|, |F'|, status (BR_OK, or BR_ERANGE if an
  *             id was out of range; the other values are then meaningless).
+ * The tree's root is what is returned, and on one GPU every chunk's edges are
+ * at hand: by default the root's certificate is taken from the edges directly
+ * (every level folded into it, so M has no effect on the result or its cost);
+ * a tuned or forced plan (br_autotune, BR_SOLO, BR_LDS) builds the chunks'
+ * certificates and merges them as Section III does between machines.
  * Asynchronous.  Returns BR_EINVAL / BR_ECAP (cert_cap too small) / BR_ENOMEM /
  * BR_EHIP before enqueueing anything.
  */
@@ -212,8 +217,8 @@ int32_t br_lds_max_v(void);
 /*
  * br_autotune -- measure the launch shapes of the certificate path for this
  * device and input shape and keep the fastest for later calls on inputs of
- * the same shape bucket (V and E in powers of two, the same M): the team
- * path (many workgroups per chunk) with three first-stage tiles, the
+ * the same shape bucket (V and E in powers of two, the same M): the whole
+ * list in one pass, the team path (many workgroups per chunk) with three first-stage tiles, the
  * whole-tree LDS kernel where V fits, and the one-workgroup-per-node path in
  * each worker shape with the depths of the merges it does itself around its
  * default; then the winner again with its team merges requesting each
@@ -256,8 +261,9 @@ typedef struct br_profile {
     double ms_bridge_dev;  /* device bridge step (final step 1 only)              */
     int64_t plan_kind;     /* certificate plan of the last plain-path call: 0 many
                               workgroups per chunk, 1 one workgroup per node
-                              (resident slots), 2 the whole tree in LDS        */
-    int64_t alg_bytes;     /* br_bridges_find at profiling level 2, plans 0 and 1:
+                              (resident slots), 2 the whole tree in LDS, 3 the
+                              whole list in one pass (no merge rounds)         */
+    int64_t alg_bytes;     /* br_bridges_find at profiling level 2, plans 0, 1 and 3:
                               the bytes the method itself moves at this M
                               (Section III): 8 per input edge read by phase 0,
                               8 per certificate edge written to a node's region,

@@ -63,10 +63,32 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     P.E = E;
     P.V = V;
     P.M = M;
+    const int64_t bound = 2 * (int64_t(V) - 1);
+    // The whole list in one pass unless a plan is asked for by name: on one
+    // GPU the chunks' own certificates and their merges only add work (large
+    // workload: M = 4096 / 64 / 4 chunks 120 / 18 / 12 ms per query; dense
+    // workload: M = 16 / 1 chunks 0.59 / 0.37 ms).
+    const int lds_want = knob("BR_LDS", "lds", -1);
+    const bool plan_env = env_int("BR_SOLO", -1) >= 0 || env_int("BR_LDS", -1) >= 0;   // wins over a tuned "fuse"
+    const int fuse = plan_env ? env_int("BR_FUSE", 0) : knob("BR_FUSE", "fuse", -1);
+    const bool named = knob("BR_SOLO", "solo", -1) >= 0 || lds_want >= 0;
+    const int64_t per_chunk = (E + M - 1) / M;   // largest chunk
+    const bool lds_rule = V <= batched_max_v_big() && M < (1 << 20) && per_chunk <= (int64_t(1) << 18);
+    if (allow_solo && E > 0 &&
+        (fuse == 1 || (fuse < 0 && !named && !lds_rule))) {
+        P.fused = true;
+        P.M = 1;
+        P.qs = (int64_t)V * 32 <= (int64_t(128) << 20) ? 8 : 2;
+        P.off = {0};
+        P.cap = {std::min(E, bound)};
+        P.cert_pairs = P.cap[0];
+        plan_fused(P);
+        return P;
+    }
     while ((int64_t(1) << P.rounds) < M) P.rounds++;
     // phase-0 tiles fill the LDS stage; merge rounds size their own tiles
     P.tile = tile_size();
-    const int64_t per = (E + M - 1) / M;   // largest chunk
+    const int64_t per = per_chunk;
     P.tpc = (int32_t)std::max<int64_t>(1, (per + P.tile - 1) / P.tile);
     P.xcd_map = M >= 8 ? 1 : 0;
     const int64_t chunk_slots = P.xcd_map ? 8 * ((M + 7) / 8) : M;
@@ -85,7 +107,6 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     // packed 8 bytes per vertex otherwise (more chunks: capacity wins)
     P.qs = (int64_t)M * V * 32 <= (int64_t(128) << 20) ? 8 : 2;
     auto lo = [&](int64_t i) { return i * (E / M) + (i * (E % M)) / M; };
-    const int64_t bound = 2 * (int64_t(V) - 1);
     P.off.resize(M);
     P.cap.resize(M);
     int64_t acc = 0;
@@ -110,7 +131,7 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     P.prem = knob("BR_PREM", "prem", 0) != 0;
     // the whole tree in LDS: V within a workgroup's LDS, chunks short enough
     // for one CU each (a CU offers about 10^9 edges/s in LDS)
-    const int lds = knob("BR_LDS", "lds", -1);
+    const int lds = lds_want;
     if (allow_solo && E > 0 && V <= batched_max_v_big() && M < (1 << 20) &&
         (lds == 1 || (lds < 0 && per <= (int64_t(1) << 18)))) {
         P.lds = true;
@@ -206,12 +227,12 @@ int ensure_pinned(br_ctx* c, size_t bytes) {
     return BR_OK;
 }
 
-// Workspace layout: [err | cnt | state | packed state | cert | off | cap |
-// solo: pool | park + arrivals | queue | dense node states | slot tags | slots |
+// Workspace layout: [err | cnt | state | packed state | root codes | cert | off |
+// cap | code table | solo: pool | park + arrivals | queue | dense node states | slot tags | slots |
 // bridge step]; everything before `cert` is cleared per call.
 struct Layout {
-    size_t err, cnt, state, packed, cert, off, cap, pool, park, queue, dense, tags, slots, sbuf, lmeta, rootw, bws,
-        total;
+    size_t err, cnt, state, packed, rcode, cert, off, cap, pool, park, queue, dense, tags, slots, sbuf, lmeta, rootw,
+        code, bws, total;
 };
 // the one-graph batch description of the LDS plan: eoff[2], then V, M,
 // rbase, cbase, vbase, n_items (one int64 word each), then the M work items
@@ -237,11 +258,13 @@ static Layout layout(const Plan& P, bool device_final) {
     L.state = o;
     if (P.lds) o = align256(o + sizeof(uint32_t) * (size_t)P.lds_counters);     // arrivals, queue
     else if (!P.solo) o = align256(o + sizeof(uint32_t) * (size_t)P.qs * (size_t)P.V * (size_t)P.M);
-    L.packed = o; if (!P.solo && !P.lds && P.qs != 2 && P.M > 1) o = align256(o + sizeof(uint32_t) * 2 * (size_t)P.V * (size_t)P.M);
+    L.packed = o; if (!P.solo && !P.lds && !P.fused && P.qs != 2 && P.M > 1) o = align256(o + sizeof(uint32_t) * 2 * (size_t)P.V * (size_t)P.M);
+    L.rcode = o; if (P.code_per) o = align256(o + sizeof(uint32_t) * ((size_t)P.V + 1));   // and the codes' counter
     L.cert = o; o = align256(o + sizeof(int2) * (size_t)std::max<int64_t>(P.cert_pairs, 1));
     L.off = o; o = align256(o + sizeof(int64_t) * (size_t)P.M);
     L.cap = o; o = align256(o + sizeof(int64_t) * (size_t)P.M);
-    L.pool = L.park = L.queue = L.dense = L.tags = L.slots = L.sbuf = L.lmeta = L.rootw = o;
+    L.pool = L.park = L.queue = L.dense = L.tags = L.slots = L.sbuf = L.lmeta = L.rootw = L.code = o;
+    if (P.fused) o = align256(o + sizeof(uint32_t) * (size_t)P.code_words);
     if (P.lds) {
         L.lmeta = o; o = align256(o + sizeof(int64_t) * (kLdsMetaWords + (size_t)P.M));
         L.rootw = o; o = align256(o + sizeof(uint32_t) * (size_t)P.V);
@@ -285,7 +308,10 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
                     hipStream_t s, Plan& P, DevBufs& B, bool device_final, const TuneEntry* plan_knobs) {
     const int64_t E = Ea + Eb;
     P = plan_knobs ? make_plan(E, V, M, true, plan_knobs) : plan_for(c->device, E, V, M);
-    if (Eb > 0 && P.lds) P = make_plan(E, V, M, false, nullptr);   // the LDS kernel reads one edge array
+    if (Eb > 0 && P.lds) {                                         // the LDS kernel reads one edge array
+        const TuneEntry one{{"fuse", 1}};
+        P = make_plan(E, V, M, env_int("BR_LDS", -1) < 0, &one);
+    }
     const Layout L = layout(P, device_final);
     int rc = ensure_workspace(c, L.total, s);
     if (rc) return rc;
@@ -299,11 +325,32 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
     B.cnt = reinterpret_cast<uint32_t*>(base + L.cnt);
     B.state = reinterpret_cast<uint32_t*>(base + L.state);
     B.qs = P.qs;
-    B.packed = P.qs != 2 && P.M > 1 ? reinterpret_cast<uint32_t*>(base + L.packed) : nullptr;
+    B.packed = P.qs != 2 && P.M > 1 && !P.fused ? reinterpret_cast<uint32_t*>(base + L.packed) : nullptr;
     B.cert = reinterpret_cast<int2*>(base + L.cert);
     B.off = reinterpret_cast<const int64_t*>(base + L.off);
     B.cap = reinterpret_cast<const int64_t*>(base + L.cap);
     c->bws = reinterpret_cast<int32_t*>(base + L.bws);
+    c->prof.plan_kind = P.fused ? 3 : (P.lds ? 2 : (P.solo ? 1 : 0));
+    c->prof.rounds = P.rounds;
+    if (P.fused) {
+        rc = fused_prepare();
+        if (rc) return rc;
+        c->solo_key_base = nullptr;    // this call's layout overwrites where slots may have been
+        FusedBufs F;
+        F.rcode = reinterpret_cast<uint32_t*>(base + L.rcode);
+        F.ncode = F.rcode + P.V;
+        F.code = reinterpret_cast<uint32_t*>(base + L.code);
+        ev_record(c, 0, s);
+        launch_fused_init(base, L.cert, reinterpret_cast<int64_t*>(base + L.off), reinterpret_cast<int64_t*>(base + L.cap),
+                          P.cap[0], s);
+        ev_record(c, 1, s);
+        c->prof.launches = 1 + launch_fused(P, B, F, s);
+        BR_HIP(hipGetLastError());
+        ev_record(c, 2, s);
+        ev_record(c, 3, s);
+        return BR_OK;
+    }
+    M = P.M;
     // node regions: staged through pinned memory (the previous call's copy has
     // completed: every entry point ends with a stream synchronisation or an
     // event wait on the staging copy)
@@ -337,7 +384,6 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
     // all-singleton forests, zero counters and error word
     BR_HIP(hipMemsetAsync(base, 0, L.cert, s));
     c->prof.launches = 1;
-    c->prof.plan_kind = P.lds ? 2 : (P.solo ? 1 : 0);
     int32_t first_step = 1;
     if (P.lds) {
         c->solo_key_base = nullptr;
@@ -410,7 +456,6 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
         BR_HIP(hipGetLastError());
     }
     ev_record(c, 3, s);
-    c->prof.rounds = P.rounds;
     return BR_OK;
 }
 
@@ -898,21 +943,21 @@ int br_autotune(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t
     int source = 0;   // 0: from the cache, 1: measured now
     if (!tune_get(key, best)) {
         source = 1;
-        // candidate plans: the team path with three first-stage tiles, the
+        // candidate plans: the whole list in one pass, the team path with three first-stage tiles, the
         // whole-tree LDS kernel where V fits, and the one-workgroup-per-node
         // path in each worker shape with the merge depths around its default
         // (and depths 1 and 2)
         std::vector<TuneEntry> cands;
+        if (E > 0) cands.push_back({{"fuse", 1}});
         for (int tile : {4096, 2048, 1024}) cands.push_back({{"lds", 0}, {"solo", 0}, {"tile", tile}});
         if (E > 0 && V <= batched_max_v_big() && M < (1 << 20)) cands.push_back({{"lds", 1}});
         if (E > 0 && V <= solo_max_v()) {
-            const Plan d = make_plan(E, V, M, true, nullptr);
             for (int v = 0; v < solo_variants(); v++) {
                 TuneEntry on{{"lds", 0}, {"solo", 1}, {"variant", v}};
                 const Plan dv = make_plan(E, V, M, true, &on);
                 std::vector<int> tops;
                 for (int top : {dv.solo_top - 1, dv.solo_top, dv.solo_top + 1, 1, 2})
-                    if (top >= 0 && top <= d.rounds && std::find(tops.begin(), tops.end(), top) == tops.end())
+                    if (top >= 0 && top <= dv.rounds && std::find(tops.begin(), tops.end(), top) == tops.end())
                         tops.push_back(top);
                 for (int top : tops) cands.push_back({{"lds", 0}, {"solo", 1}, {"variant", v}, {"top", top}});
             }
@@ -967,7 +1012,7 @@ int br_autotune(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t
             }
             return BR_OK;
         };
-        if (M > 1 && !(best.count("lds") && best["lds"] == 1)) {
+        if (M > 1 && !best.count("fuse") && !(best.count("lds") && best["lds"] == 1)) {
             rc = try_alt("prem", 1);
             if (rc) return rc;
         }

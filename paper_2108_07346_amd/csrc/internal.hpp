@@ -121,6 +121,11 @@ struct Plan {
     bool lds_big = false;          // the 160 KB kernel (V above the small kernel's limit)
     int32_t lds_blocks = 0;
     int64_t lds_counters = 0;      // merge arrival counters
+    // the whole list certified in one pass (fused_kernels.hip); M is 1 then
+    bool fused = false;
+    int32_t s1 = 1, s2 = 1;        // rows r of stage 1: r % s1 == 0; of stages 1 and 2: r % s2 == 0
+    int32_t code_per = 0;          // codes per word of the stage 3 table (0: no table)
+    int32_t code_words = 0;
 };
 
 // Certificate regions: node i owns pairs [off[i], off[i]+cap[i]); its F1 grows
@@ -225,6 +230,18 @@ int32_t batched_max_blocks_per_cu();
 // Largest V the final steps take: they count the 2(V-1) arcs of the
 // certificate's forest tours in 30-bit fields (and the host search in int32).
 constexpr int32_t kFinalStepMaxV = 1 << 29;
+
+// The one-pass certificate (fused_kernels.hip).
+struct FusedBufs {
+    uint32_t* rcode = nullptr;     // [V] code of each root of F' (zero at launch)
+    uint32_t* ncode = nullptr;     // [1] codes given (zero at launch)
+    uint32_t* code = nullptr;      // [code_words]
+};
+void plan_fused(Plan& P);
+int fused_prepare();               // once per process: the kernels' LDS limit
+// zeroes `bytes` (a multiple of 16) at base and writes node 0's region table
+void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int64_t cap0, hipStream_t s);
+int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);   // kernels enqueued
 
 void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 void launch_phase0(const Plan& P, DevBufs& B, hipStream_t s);
