@@ -83,6 +83,8 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
         P.cap = {std::min(E, bound)};
         P.cert_pairs = P.cap[0];
         plan_fused(P);
+        // on a dense list nearly every edge of F lies inside a component of F'
+        P.contract = V <= 4096 || E >= 6 * (int64_t)V;
         return P;
     }
     while ((int64_t(1) << P.rounds) < M) P.rounds++;
@@ -232,7 +234,7 @@ int ensure_pinned(br_ctx* c, size_t bytes) {
 // bridge step]; everything before `cert` is cleared per call.
 struct Layout {
     size_t err, cnt, state, packed, rcode, cert, off, cap, pool, park, queue, dense, tags, slots, sbuf, lmeta, rootw,
-        code, bws, total;
+        code, hid, ctr, bws, total;
 };
 // the one-graph batch description of the LDS plan: eoff[2], then V, M,
 // rbase, cbase, vbase, n_items (one int64 word each), then the M work items
@@ -260,6 +262,7 @@ static Layout layout(const Plan& P, bool device_final) {
     else if (!P.solo) o = align256(o + sizeof(uint32_t) * (size_t)P.qs * (size_t)P.V * (size_t)P.M);
     L.packed = o; if (!P.solo && !P.lds && !P.fused && P.qs != 2 && P.M > 1) o = align256(o + sizeof(uint32_t) * 2 * (size_t)P.V * (size_t)P.M);
     L.rcode = o; if (P.code_per) o = align256(o + sizeof(uint32_t) * ((size_t)P.V + 1));   // and the codes' counter
+    L.hid = o; if (P.contract && device_final) o = align256(o + sizeof(uint32_t) * contract_clear_words(P.V));
     L.cert = o; o = align256(o + sizeof(int2) * (size_t)std::max<int64_t>(P.cert_pairs, 1));
     L.off = o; o = align256(o + sizeof(int64_t) * (size_t)P.M);
     L.cap = o; o = align256(o + sizeof(int64_t) * (size_t)P.M);
@@ -280,6 +283,7 @@ static Layout layout(const Plan& P, bool device_final) {
         L.sbuf = o;
         if (P.solo_nbk > 0) o = align256(o + sizeof(int2) * (size_t)solo_sbuf_stride(P) * (size_t)P.workers);
     }
+    L.ctr = o; if (P.contract && device_final) o = align256(o + sizeof(uint32_t) * contract_words());
     L.bws = o; if (device_final) o = align256(o + sizeof(int32_t) * (size_t)device_bridges_words(P.V));
     L.total = o;
     return L;
@@ -340,6 +344,11 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
         F.rcode = reinterpret_cast<uint32_t*>(base + L.rcode);
         F.ncode = F.rcode + P.V;
         F.code = reinterpret_cast<uint32_t*>(base + L.code);
+        if (P.contract && device_final) {
+            rc = contract_prepare();
+            if (rc) return rc;
+            c->contract = contract_carve(reinterpret_cast<uint32_t*>(base + L.hid), reinterpret_cast<uint32_t*>(base + L.ctr), V);
+        }
         ev_record(c, 0, s);
         launch_fused_init(base, L.cert, reinterpret_cast<int64_t*>(base + L.off), reinterpret_cast<int64_t*>(base + L.cap),
                           P.cap[0], s);
@@ -618,29 +627,43 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
     c->keys.clear();
     if (mode == 1) {
         // final step on the device: only the bridges come back
-        uint64_t* d_keys = nullptr;
-        uint32_t* d_n = nullptr;
-        rc = device_bridges(P, B, c->bws, &d_keys, &d_n, s);
-        if (rc) return rc;
-        BR_HIP(hipGetLastError());
-        ev_record(c, 5, s);
-        // counters, error word and the first keys in one copy (the status block
-        // precedes the keys); more keys than last time take a second copy
         rc = ensure_pinned(c, 256 + 8 * (size_t)V);
         if (rc) return rc;
         uint32_t* hc = static_cast<uint32_t*>(c->pinned);
         uint64_t* hk = reinterpret_cast<uint64_t*>(static_cast<char*>(c->pinned) + 256);
-        const size_t guess = std::min<size_t>(std::max<size_t>(c->keys_hint, 1024), (size_t)V);
-        BR_HIP(hipMemcpyAsync(hc, d_n - 1, 256 + 8 * guess, hipMemcpyDeviceToHost, s));
-        rc = ctx_end(c, s);
-        if (rc) return rc;
-        BR_HIP(hipStreamSynchronize(s));
-        n1 = hc[2]; n2 = hc[3]; err = hc[4];
-        const uint32_t nk = std::min<uint32_t>(hc[1], (uint32_t)std::max(V - 1, 0));
-        if (nk > guess) {
-            BR_HIP(hipMemcpyAsync(hk + guess, d_keys + guess, 8 * (size_t)(nk - guess), hipMemcpyDeviceToHost, s));
+        uint32_t nk = 0;
+        bool solved = false;
+        if (P.contract) {
+            launch_contract(P, B, c->contract, 0, hc, hk, nullptr, s);
+            BR_HIP(hipGetLastError());
+            ev_record(c, 5, s);
+            rc = ctx_end(c, s);
+            if (rc) return rc;
             BR_HIP(hipStreamSynchronize(s));
+            solved = hc[6] != 0;
+            nk = hc[1];
         }
+        if (!solved) {
+            uint64_t* d_keys = nullptr;
+            uint32_t* d_n = nullptr;
+            rc = device_bridges(P, B, c->bws, &d_keys, &d_n, s);
+            if (rc) return rc;
+            BR_HIP(hipGetLastError());
+            ev_record(c, 5, s);
+            // counters, error word and the first keys in one copy (the status block
+            // precedes the keys); more keys than last time take a second copy
+            const size_t guess = std::min<size_t>(std::max<size_t>(c->keys_hint, 1024), (size_t)V);
+            BR_HIP(hipMemcpyAsync(hc, d_n - 1, 256 + 8 * guess, hipMemcpyDeviceToHost, s));
+            rc = ctx_end(c, s);
+            if (rc) return rc;
+            BR_HIP(hipStreamSynchronize(s));
+            nk = std::min<uint32_t>(hc[1], (uint32_t)std::max(V - 1, 0));
+            if (nk > guess) {
+                BR_HIP(hipMemcpyAsync(hk + guess, d_keys + guess, 8 * (size_t)(nk - guess), hipMemcpyDeviceToHost, s));
+                BR_HIP(hipStreamSynchronize(s));
+            }
+        }
+        n1 = hc[2]; n2 = hc[3]; err = hc[4];
         c->keys_hint = nk;
         ev_record(c, 4, s);
         t1 = std::chrono::steady_clock::now();
@@ -734,22 +757,35 @@ static int classes_common(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t 
     std::vector<uint64_t>& tkeys = c->keys;
     tkeys.clear();
     if (mode == 1) {
-        // bridges and classes on the device: one copy of the status block and
-        // labels (and one of the tree's edges)
-        int32_t* d_label = nullptr;
-        uint32_t* d_n = nullptr;
-        uint64_t* d_tkeys = nullptr;
-        rc = h_tree ? device_bridge_tree(P, B, c->bws, &d_label, &d_n, &d_tkeys, s)
-                    : device_classes(P, B, c->bws, &d_label, &d_n, s);
-        if (rc) return rc;
-        BR_HIP(hipGetLastError());
-        rc = ensure_pinned(c, 256 + 4 * (size_t)V);
+        // bridges and classes on the device: the status block, the labels and
+        // the tree's edges come back
+        const size_t o_tree = (256 + 4 * (size_t)V + 7) & ~size_t(7);
+        rc = ensure_pinned(c, o_tree + (P.contract ? 8 * (size_t)std::min<int64_t>(V, kMaxCross) : 0));
         if (rc) return rc;
         uint32_t* hc = static_cast<uint32_t*>(c->pinned);
-        BR_HIP(hipMemcpyAsync(hc, d_n - 1, 256 + 4 * (size_t)V, hipMemcpyDeviceToHost, s));
-        rc = ctx_end(c, s);
-        if (rc) return rc;
-        BR_HIP(hipStreamSynchronize(s));
+        uint64_t* ht = reinterpret_cast<uint64_t*>(static_cast<char*>(c->pinned) + o_tree);
+        uint64_t* d_tkeys = nullptr;
+        bool solved = false;
+        if (P.contract) {
+            launch_contract(P, B, c->contract, h_tree ? 2 : 1, hc, hc + 64, ht, s);
+            BR_HIP(hipGetLastError());
+            rc = ctx_end(c, s);
+            if (rc) return rc;
+            BR_HIP(hipStreamSynchronize(s));
+            solved = hc[6] != 0;
+        }
+        if (!solved) {
+            int32_t* d_label = nullptr;
+            uint32_t* d_n = nullptr;
+            rc = h_tree ? device_bridge_tree(P, B, c->bws, &d_label, &d_n, &d_tkeys, s)
+                        : device_classes(P, B, c->bws, &d_label, &d_n, s);
+            if (rc) return rc;
+            BR_HIP(hipGetLastError());
+            BR_HIP(hipMemcpyAsync(hc, d_n - 1, 256 + 4 * (size_t)V, hipMemcpyDeviceToHost, s));
+            rc = ctx_end(c, s);
+            if (rc) return rc;
+            BR_HIP(hipStreamSynchronize(s));
+        }
         const uint32_t err = hc[4];
         if (err & 1u) return fail(BR_ERANGE, "%s: an edge has a vertex id outside [0, %d)", who, V);
         if (err != 0 || (int64_t)hc[2] + hc[3] > P.cap[0]) return fail(BR_EINTERNAL, "%s: region overflow", who);
@@ -758,10 +794,14 @@ static int classes_common(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t 
         if (h_tree) {
             const uint32_t nt = hc[5];
             if (nt > (uint32_t)std::max(V - 1, 0)) return fail(BR_EINTERNAL, "%s: %u tree edges", who, nt);
-            tkeys.resize(nt);
-            if (nt) {
-                BR_HIP(hipMemcpyAsync(tkeys.data(), d_tkeys, 8 * (size_t)nt, hipMemcpyDeviceToHost, s));
-                BR_HIP(hipStreamSynchronize(s));
+            if (solved) {
+                tkeys.assign(ht, ht + nt);
+            } else {
+                tkeys.resize(nt);
+                if (nt) {
+                    BR_HIP(hipMemcpyAsync(tkeys.data(), d_tkeys, 8 * (size_t)nt, hipMemcpyDeviceToHost, s));
+                    BR_HIP(hipStreamSynchronize(s));
+                }
             }
         }
     } else {

@@ -1,0 +1,178 @@
+// Final step over the contracted certificate (contract.hpp has the reason why
+// contracting the components of F' keeps bridges and classes): the edges of F
+// that cross components of F' are collected by all workgroups, then one
+// workgroup solves what is left, and the answer goes straight to pinned host
+// memory.  What bounds it is latency: three launches in a row for bridges, four
+// for labels, where the tour-based step over all of F takes eleven and more.
+#include <hip/hip_runtime.h>
+
+#include "contract.hpp"
+#include "device_util.hpp"
+#include "internal.hpp"
+
+namespace br {
+
+namespace {
+
+// root of x in F' (no shortcut stores: the state is read by every workgroup)
+__device__ __forceinline__ uint32_t root2(const uint32_t* q, int64_t qs, uint32_t x) {
+    for (uint32_t d = q[qs * (int64_t)x + 1]; d; d = q[qs * (int64_t)x + 1]) x -= d;
+    return x;
+}
+
+// Collects the crossing edges of F: the roots of their ends at C.he, their
+// place in F at C.hk; every root gets a number in H (C.hid: 1 + number).  One
+// reservation per block on each counter; past kMaxCross edges nothing more is
+// collected (the tour-based step takes over).
+__global__ void __launch_bounds__(kSolveT) k_cross(const int2* f1, const uint32_t* cnt, const uint32_t* q, int64_t qs,
+                                                   Contract C) {
+    __shared__ uint32_t ne, nv, be, bv;
+    const int64_t n1 = cnt[0];
+    for (int64_t base = blockIdx.x * (int64_t)kSolveT; base < n1; base += (int64_t)gridDim.x * kSolveT) {
+        if (threadIdx.x == 0) { ne = 0; nv = 0; }
+        __syncthreads();
+        const int64_t k = base + threadIdx.x;
+        uint32_t r[2] = {0, 0}, at = 0, id[2] = {0, 0};
+        bool cross = false, took[2] = {false, false};
+        if (k < n1) {
+            const int2 e = f1[k];
+            r[0] = root2(q, qs, (uint32_t)e.x);
+            r[1] = root2(q, qs, (uint32_t)e.y);
+            cross = r[0] != r[1];
+        }
+        const uint64_t m = __ballot(cross);
+        if (m) {
+            const int leader = __ffsll((unsigned long long)m) - 1;
+            if (__lane_id() == leader) at = atomicAdd(&ne, (uint32_t)__popcll(m));
+            at = __shfl(at, leader) + lane_rank(m);
+            for (int t = 0; t < 2; t++) {
+                // a device-scope look first: many edges share a large component's root
+                took[t] = cross && __hip_atomic_load(&C.hid[r[t]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 &&
+                          atomicCAS(&C.hid[r[t]], 0u, 0xffffffffu) == 0;
+                if (took[t]) id[t] = atomicAdd(&nv, 1u);
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            be = ne ? atomicAdd(&C.hcnt[1], ne) : 0;
+            bv = nv ? atomicAdd(&C.hcnt[0], nv) : 0;
+        }
+        __syncthreads();
+        if (cross && be + at < (uint32_t)kMaxCross) {
+            C.he[be + at] = make_uint2(r[0], r[1]);
+            C.hk[be + at] = (uint32_t)k;
+        }
+        for (int t = 0; t < 2; t++)
+            if (took[t]) {
+                C.hid[r[t]] = bv + id[t] + 1;
+                if (bv + id[t] < (uint32_t)kMaxCross) C.hroot[bv + id[t]] = r[t];
+            }
+        const bool full = be >= (uint32_t)kMaxCross;
+        __syncthreads();
+        if (full) break;
+    }
+}
+
+// One workgroup: bridges (mode 0), classes (1) or classes and bridge tree (2)
+// of H.  out: 64 status words in host memory -- [1] bridges or classes, [2],
+// [3] |F|, |F'|, [4] error word, [5] bridges (the tree's edges), [6] 1 if
+// solved -- then (modes 0 and 2) the keys min << 32 | max at `keys`.
+__global__ void __launch_bounds__(kSolveT) k_solve(const int2* f1, const uint32_t* cnt, const uint32_t* err, int32_t V,
+                                                   Contract C, int32_t mode, uint32_t* out, uint64_t* keys,
+                                                   uint32_t* solved) {
+    extern __shared__ __align__(16) unsigned char raw[];
+    SolveLds& L = *reinterpret_cast<SolveLds*>(raw);
+    const uint32_t n = C.hcnt[0], m = C.hcnt[1];
+    bool ok = n <= (uint32_t)kMaxCross && m <= (uint32_t)kMaxCross;
+    if (ok) ok = solve_contracted(L, C, n, m, mode != 0, [&](uint32_t j) {
+            const uint2 r = C.he[j];
+            return make_uint2(C.hid[r.x] - 1, C.hid[r.y] - 1);
+        });
+    __syncthreads();
+    if (threadIdx.x == 0) L.nout = 0;
+    __syncthreads();
+    if (ok)
+        for (uint32_t j = threadIdx.x; j < m; j += kSolveT) {
+            if (!C.isbr[j]) continue;
+            uint32_t a, b;
+            if (mode == 0) {
+                const int2 e = f1[C.hk[j]];
+                a = (uint32_t)e.x;
+                b = (uint32_t)e.y;
+            } else {
+                const uint2 r = C.he[j];
+                a = C.hcls[C.hid[r.x] - 1];
+                b = C.hcls[C.hid[r.y] - 1];
+            }
+            const uint32_t p = atomicAdd(&L.nout, 1u);
+            if (mode != 1) keys[p] = (uint64_t)min(a, b) << 32 | max(a, b);
+        }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        out[1] = mode == 0 ? L.nout : (uint32_t)V - cnt[1] - (ok ? L.nuni : 0u);
+        out[2] = cnt[0];
+        out[3] = cnt[1];
+        out[4] = *err;
+        out[5] = L.nout;
+        out[6] = ok ? 1u : 0u;
+        *solved = ok ? 1u : 0u;
+    }
+}
+
+// class labels of all vertices, straight to host memory
+__global__ void __launch_bounds__(256) k_labels(const uint32_t* q, int64_t qs, int32_t V, Contract C,
+                                                const uint32_t* solved, int32_t* label) {
+    if (!*solved) return;
+    GRID_LOOP(x, (int64_t)V) {
+        const uint32_t r = root2(q, qs, (uint32_t)x), h = C.hid[r];
+        label[x] = (int32_t)(h ? C.hcls[h - 1] : r);
+    }
+}
+
+}  // namespace
+
+int contract_prepare() {
+    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_solve),
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SolveLds));
+    return e == hipSuccess ? BR_OK : hip_fail(e, "hipFuncSetAttribute(k_solve)");
+}
+
+size_t contract_clear_words(int32_t V) { return (size_t)V + 64; }
+size_t contract_words() { return 11 * (size_t)kMaxCross; }
+
+Contract contract_carve(uint32_t* cleared, uint32_t* scratch, int32_t V) {
+    Contract C;
+    C.hid = cleared;
+    C.hcnt = cleared + V;
+    C.solved = C.hcnt + 2;
+    uint32_t* p = scratch;
+    auto take = [&](size_t k) { uint32_t* r = p; p += k * kMaxCross; return r; };
+    C.he = reinterpret_cast<uint2*>(take(2));
+    C.hk = take(1);
+    C.hroot = take(1);
+    C.hcls = take(1);
+    C.isbr = take(1);
+    C.core = take(1);
+    C.corej = take(1);
+    C.tree = take(1);
+    C.treej = take(1);
+    C.non = take(1);
+    C.root = C.core;          // the core's edges are read before its roots are written
+    return C;
+}
+
+void launch_contract(const Plan& P, const DevBufs& B, const Contract& C, int mode, uint32_t* h_status, void* h_data,
+                     uint64_t* h_tree, hipStream_t s) {
+    const int2* f1 = B.cert + P.off[0];
+    const int64_t nf = std::max<int64_t>(1, std::min<int64_t>(P.E, (int64_t)P.V - 1));
+    hipLaunchKernelGGL(k_cross, dim3((unsigned)std::min<int64_t>((nf + kSolveT - 1) / kSolveT, 1024)), dim3(kSolveT), 0, s,
+                       f1, (const uint32_t*)B.cnt, (const uint32_t*)B.state, B.qs, C);
+    hipLaunchKernelGGL(k_solve, dim3(1), dim3(kSolveT), sizeof(SolveLds), s, f1, (const uint32_t*)B.cnt,
+                       (const uint32_t*)B.err, P.V, C, mode, h_status,
+                       mode == 0 ? reinterpret_cast<uint64_t*>(h_data) : h_tree, C.solved);
+    if (mode != 0)
+        hipLaunchKernelGGL(k_labels, dim3(grid_for(P.V)), dim3(256), 0, s, (const uint32_t*)B.state, B.qs, P.V, C,
+                           (const uint32_t*)C.solved, reinterpret_cast<int32_t*>(h_data));
+}
+
+}  // namespace br

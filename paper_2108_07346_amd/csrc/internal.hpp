@@ -126,6 +126,7 @@ struct Plan {
     int32_t s1 = 1, s2 = 1;        // rows r of stage 1: r % s1 == 0; of stages 1 and 2: r % s2 == 0
     int32_t code_per = 0;          // codes per word of the stage 3 table (0: no table)
     int32_t code_words = 0;
+    bool contract = false;         // final step over the contracted certificate first (contract_kernels.hip)
 };
 
 // Certificate regions: node i owns pairs [off[i], off[i]+cap[i]); its F1 grows
@@ -243,6 +244,30 @@ int fused_prepare();               // once per process: the kernels' LDS limit
 void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int64_t cap0, hipStream_t s);
 int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);   // kernels enqueued
 
+// The contracted certificate (contract.hpp, contract_kernels.hip): edges of F
+// that cross components of F', at most kMaxCross of them and of their ends.
+constexpr int kMaxCross = 16384;
+struct Contract {
+    uint32_t* hid = nullptr;       // [V] 1 + number in H of a root of F' (zero at launch)
+    uint32_t* hcnt = nullptr;      // [2] H's vertices and edges (zero at launch)
+    uint32_t* solved = nullptr;    // [1]
+    uint2* he = nullptr;           // per edge of H: the roots of its ends
+    uint32_t* hk = nullptr;        // ... its place in F
+    uint32_t* isbr = nullptr;      // ... 1 if it is a bridge
+    uint32_t* hroot = nullptr;     // per vertex of H: its root
+    uint32_t* hcls = nullptr;      // ... its class's smallest vertex
+    uint32_t *core = nullptr, *corej = nullptr, *tree = nullptr, *treej = nullptr, *non = nullptr, *root = nullptr;
+};
+int contract_prepare();            // once per process: the kernel's LDS limit
+size_t contract_clear_words(int32_t V);    // words that must be zero at launch
+size_t contract_words();                   // scratch words
+Contract contract_carve(uint32_t* cleared, uint32_t* scratch, int32_t V);
+// mode 0 bridges, 1 classes, 2 classes and bridge tree.  h_status: 64 words of
+// pinned memory (the status block of a bridge step, word 6: 1 if solved);
+// h_data: keys (mode 0) or labels, also pinned; h_tree: the tree's keys.
+void launch_contract(const Plan& P, const DevBufs& B, const Contract& C, int mode, uint32_t* h_status, void* h_data,
+                     uint64_t* h_tree, hipStream_t s);
+
 void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 void launch_phase0(const Plan& P, DevBufs& B, hipStream_t s);
 int phase0_launches(const Plan& P);   // kernels launch_phase0 enqueues for this plan
@@ -339,6 +364,7 @@ struct br_ctx {
     size_t keys_hint = 0;          // bridges found by the previous call (first copy size)
     int final_step = 1;            // 0: host search (Algorithm 1), 1: device bridge step
     int32_t* bws = nullptr;        // device bridge-step scratch inside the workspace
+    br::Contract contract;         // contracted final step's scratch inside the workspace
     br_profile prof{};
     hipEvent_t ev[8] = {};
     // recorded at the end of the work every entry point enqueues; the next call
