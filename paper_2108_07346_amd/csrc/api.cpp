@@ -73,9 +73,21 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     const int fuse = plan_env ? env_int("BR_FUSE", 0) : knob("BR_FUSE", "fuse", -1);
     const bool named = knob("BR_SOLO", "solo", -1) >= 0 || lds_want >= 0;
     const int64_t per_chunk = (E + M - 1) / M;   // largest chunk
-    const bool lds_rule = V <= batched_max_v_big() && M < (1 << 20) && per_chunk <= (int64_t(1) << 18);
+    // the union-find in LDS wherever V fits a workgroup's: a search step costs a
+    // tenth of one through the caches
+    if (allow_solo && E > 0 && fuse != 1 && V <= batched_max_v_big() && lds_want != 0) {
+        P.lds = true;
+        P.M = 1;
+        P.qs = 2;
+        P.off = {0};
+        P.cap = {std::min(E, bound)};
+        P.cert_pairs = P.cap[0];
+        P.contract = true;
+        plan_lds(P);
+        return P;
+    }
     if (allow_solo && E > 0 &&
-        (fuse == 1 || (fuse < 0 && !named && !lds_rule))) {
+        (fuse == 1 || (fuse < 0 && !named))) {
         P.fused = true;
         P.M = 1;
         P.qs = (int64_t)V * 32 <= (int64_t(128) << 20) ? 8 : 2;
@@ -131,17 +143,6 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     const int cus = g_cus > 0 ? g_cus : 256;
     P.tile0_max = knob("BR_TILE0", "tile", 0);
     P.prem = knob("BR_PREM", "prem", 0) != 0;
-    // the whole tree in LDS: V within a workgroup's LDS, chunks short enough
-    // for one CU each (a CU offers about 10^9 edges/s in LDS)
-    const int lds = lds_want;
-    if (allow_solo && E > 0 && V <= batched_max_v_big() && M < (1 << 20) &&
-        (lds == 1 || (lds < 0 && per <= (int64_t(1) << 18)))) {
-        P.lds = true;
-        P.lds_big = V > batched_max_v_dev();
-        P.lds_blocks = (int32_t)std::min<int64_t>(M, (int64_t)cus * (P.lds_big ? 1 : batched_blocks_per_cu()));
-        P.lds_counters = (int64_t)P.rounds * (((int64_t)M + 1) / 2) + 2;
-        return P;
-    }
     const int want = knob("BR_SOLO", "solo", -1);
     if (allow_solo && E > 0 && V <= solo_max_v() &&
         (want == 1 || (want < 0 && M >= cus && per <= (int64_t)V && V >= (1 << 17)))) {
@@ -233,12 +234,9 @@ int ensure_pinned(br_ctx* c, size_t bytes) {
 // cap | code table | solo: pool | park + arrivals | queue | dense node states | slot tags | slots |
 // bridge step]; everything before `cert` is cleared per call.
 struct Layout {
-    size_t err, cnt, state, packed, rcode, cert, off, cap, pool, park, queue, dense, tags, slots, sbuf, lmeta, rootw,
-        code, hid, ctr, bws, total;
+    size_t err, cnt, state, packed, rcode, cert, off, cap, pool, park, queue, dense, tags, slots, sbuf, code, hid,
+        ctr, bws, total;
 };
-// the one-graph batch description of the LDS plan: eoff[2], then V, M,
-// rbase, cbase, vbase, n_items (one int64 word each), then the M work items
-constexpr size_t kLdsMetaWords = 8;
 // the largest chunk, in edges
 static int64_t solo_chunk_max(const Plan& P) { return P.M > 0 ? (P.E + P.M - 1) / P.M : 0; }
 // edges of a worker's reordering buffer: a chunk, and with bucketed merges
@@ -258,20 +256,15 @@ static Layout layout(const Plan& P, bool device_final) {
     L.err = o; o += 256;
     L.cnt = o; o = align256(o + sizeof(uint32_t) * 2 * (size_t)P.M);
     L.state = o;
-    if (P.lds) o = align256(o + sizeof(uint32_t) * (size_t)P.lds_counters);     // arrivals, queue
-    else if (!P.solo) o = align256(o + sizeof(uint32_t) * (size_t)P.qs * (size_t)P.V * (size_t)P.M);
-    L.packed = o; if (!P.solo && !P.lds && !P.fused && P.qs != 2 && P.M > 1) o = align256(o + sizeof(uint32_t) * 2 * (size_t)P.V * (size_t)P.M);
-    L.rcode = o; if (P.code_per) o = align256(o + sizeof(uint32_t) * ((size_t)P.V + 1));   // and the codes' counter
+    if (!P.solo) o = align256(o + sizeof(uint32_t) * (size_t)P.qs * (size_t)P.V * (size_t)P.M);
+    L.packed = o; if (!P.solo && !P.fused && P.qs != 2 && P.M > 1) o = align256(o + sizeof(uint32_t) * 2 * (size_t)P.V * (size_t)P.M);
+    L.rcode = o; if (P.fused && P.code_per) o = align256(o + sizeof(uint32_t) * ((size_t)P.V + 1));   // and the codes' counter
     L.hid = o; if (P.contract && device_final) o = align256(o + sizeof(uint32_t) * contract_clear_words(P.V));
     L.cert = o; o = align256(o + sizeof(int2) * (size_t)std::max<int64_t>(P.cert_pairs, 1));
     L.off = o; o = align256(o + sizeof(int64_t) * (size_t)P.M);
     L.cap = o; o = align256(o + sizeof(int64_t) * (size_t)P.M);
-    L.pool = L.park = L.queue = L.dense = L.tags = L.slots = L.sbuf = L.lmeta = L.rootw = L.code = o;
-    if (P.fused) o = align256(o + sizeof(uint32_t) * (size_t)P.code_words);
-    if (P.lds) {
-        L.lmeta = o; o = align256(o + sizeof(int64_t) * (kLdsMetaWords + (size_t)P.M));
-        L.rootw = o; o = align256(o + sizeof(uint32_t) * (size_t)P.V);
-    }
+    L.pool = L.park = L.queue = L.dense = L.tags = L.slots = L.sbuf = L.code = o;
+    if (P.code_words) o = align256(o + sizeof(uint32_t) * (size_t)P.code_words);
     if (P.solo) {
         const int64_t top_nodes = ((int64_t)P.M + (int64_t(1) << P.solo_top) - 1) >> P.solo_top;
         L.pool = o; o = align256(o + 4 * (size_t)((P.nslots + 31) / 32));
@@ -309,13 +302,10 @@ int run_certificate_with(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V
 }
 
 int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_b, int64_t Eb, int32_t V, int32_t M,
-                    hipStream_t s, Plan& P, DevBufs& B, bool device_final, const TuneEntry* plan_knobs) {
+                    hipStream_t s, Plan& P, DevBufs& B, bool device_final, const TuneEntry* plan_knobs,
+                    FinalReq* final_req) {
     const int64_t E = Ea + Eb;
     P = plan_knobs ? make_plan(E, V, M, true, plan_knobs) : plan_for(c->device, E, V, M);
-    if (Eb > 0 && P.lds) {                                         // the LDS kernel reads one edge array
-        const TuneEntry one{{"fuse", 1}};
-        P = make_plan(E, V, M, env_int("BR_LDS", -1) < 0, &one);
-    }
     const Layout L = layout(P, device_final);
     int rc = ensure_workspace(c, L.total, s);
     if (rc) return rc;
@@ -336,24 +326,33 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
     c->bws = reinterpret_cast<int32_t*>(base + L.bws);
     c->prof.plan_kind = P.fused ? 3 : (P.lds ? 2 : (P.solo ? 1 : 0));
     c->prof.rounds = P.rounds;
-    if (P.fused) {
+    if (P.fused || P.lds) {
         rc = fused_prepare();
+        if (rc == BR_OK && P.lds) rc = lds_cert_prepare();
+        if (rc == BR_OK && P.contract && device_final) rc = contract_prepare();
         if (rc) return rc;
         c->solo_key_base = nullptr;    // this call's layout overwrites where slots may have been
         FusedBufs F;
         F.rcode = reinterpret_cast<uint32_t*>(base + L.rcode);
         F.ncode = F.rcode + P.V;
         F.code = reinterpret_cast<uint32_t*>(base + L.code);
-        if (P.contract && device_final) {
-            rc = contract_prepare();
-            if (rc) return rc;
+        c->contract = Contract();
+        if (P.contract && device_final)
             c->contract = contract_carve(reinterpret_cast<uint32_t*>(base + L.hid), reinterpret_cast<uint32_t*>(base + L.ctr), V);
-        }
         ev_record(c, 0, s);
-        launch_fused_init(base, L.cert, reinterpret_cast<int64_t*>(base + L.off), reinterpret_cast<int64_t*>(base + L.cap),
-                          P.cap[0], s);
-        ev_record(c, 1, s);
-        c->prof.launches = 1 + launch_fused(P, B, F, s);
+        if (P.lds) {
+            ev_record(c, 1, s);
+            const bool fin = final_req && device_final;
+            c->prof.launches = fin ? launch_lds_cert(P, B, F, c->contract, final_req->mode, final_req->h_status,
+                                                     final_req->h_data, final_req->h_tree, s)
+                                   : launch_lds_cert(P, B, F, c->contract, -1, nullptr, nullptr, nullptr, s);
+            if (fin) final_req->done = P.lds_whole;
+        } else {
+            launch_fused_init(base, L.cert, reinterpret_cast<int64_t*>(base + L.off), reinterpret_cast<int64_t*>(base + L.cap),
+                              P.cap[0], s);
+            ev_record(c, 1, s);
+            c->prof.launches = 1 + launch_fused(P, B, F, s);
+        }
         BR_HIP(hipGetLastError());
         ev_record(c, 2, s);
         ev_record(c, 3, s);
@@ -363,7 +362,7 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
     // node regions: staged through pinned memory (the previous call's copy has
     // completed: every entry point ends with a stream synchronisation or an
     // event wait on the staging copy)
-    const size_t meta_words = 2 * (size_t)M + (P.lds ? kLdsMetaWords + (size_t)M : 0);
+    const size_t meta_words = 2 * (size_t)M;
     if (c->h_meta_n < meta_words) {
         if (c->h_meta) BR_HIP(hipHostFree(c->h_meta));
         c->h_meta = nullptr;
@@ -376,53 +375,12 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
     ev_record(c, 0, s);
     BR_HIP(hipMemcpyAsync(base + L.off, c->h_meta, sizeof(int64_t) * M, hipMemcpyHostToDevice, s));
     BR_HIP(hipMemcpyAsync(base + L.cap, c->h_meta + M, sizeof(int64_t) * M, hipMemcpyHostToDevice, s));
-    if (P.lds) {
-        int64_t* lm = c->h_meta + 2 * M;
-        lm[0] = 0;                 // eoff: graph 0 is edges [0, E)
-        lm[1] = E;
-        lm[2] = V | ((int64_t)M << 32);   // V[0] and Mg[0] as two int32 words
-        lm[3] = 1;                 // rbase: node k > 0 of graph 0 at index k
-        lm[4] = 0;                 // cbase
-        lm[5] = 0;                 // vbase
-        lm[6] = 0;
-        lm[7] = 0;
-        for (int64_t k = 0; k < M; k++) lm[kLdsMetaWords + k] = k;   // items: graph 0, chunk k
-        BR_HIP(hipMemcpyAsync(base + L.lmeta, lm, sizeof(int64_t) * (kLdsMetaWords + (size_t)M), hipMemcpyHostToDevice, s));
-    }
     BR_HIP(hipEventRecord(c->ev[7], s));
     // all-singleton forests, zero counters and error word
     BR_HIP(hipMemsetAsync(base, 0, L.cert, s));
     c->prof.launches = 1;
     int32_t first_step = 1;
-    if (P.lds) {
-        c->solo_key_base = nullptr;
-        const int64_t* lm = reinterpret_cast<const int64_t*>(base + L.lmeta);
-        BatchDev BD{};
-        BD.edges = B.edges;
-        BD.eoff = lm;
-        BD.V = reinterpret_cast<const int32_t*>(lm + 2);
-        BD.Mg = reinterpret_cast<const int32_t*>(lm + 2) + 1;
-        BD.rbase = lm + 3;
-        BD.cbase = lm + 4;
-        BD.vbase = lm + 5;
-        BD.noff = B.off;
-        BD.ncap = B.cap;
-        BD.items = lm + kLdsMetaWords;
-        BD.n_items = M;
-        BD.cert = B.cert;
-        BD.ncnt = B.cnt;
-        BD.arrive = reinterpret_cast<uint32_t*>(base + L.state);
-        BD.queue = BD.arrive + P.lds_counters - 1;
-        BD.err = B.err;
-        BD.rootw = reinterpret_cast<uint32_t*>(base + L.rootw);
-        ev_record(c, 1, s);
-        launch_batched(BD, P.lds_blocks, s, P.lds_big);
-        // the bridge step reads F's roots from the flags the kernel wrote (0 at a root)
-        B.state = BD.rootw;
-        B.qs = 1;
-        B.packed = nullptr;
-        first_step = M;            // every merge ran inside the kernel
-    } else if (P.solo) {
+    if (P.solo) {
         rc = solo_prepare(V);
         if (rc) return rc;
         SoloBufs Sb;
@@ -619,7 +577,10 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
     const int mode = c->final_step;   // read once: the workspace layout depends on it
     Plan P;
     DevBufs B;
-    rc = run_certificate(c, d_edges, E, nullptr, 0, V, M, s, P, B, mode == 1);
+    rc = ensure_pinned(c, std::max<size_t>(64 << 10, 256 + 8 * (size_t)V));
+    if (rc) return rc;
+    FinalReq fin{0, static_cast<uint32_t*>(c->pinned), static_cast<char*>(c->pinned) + 256, nullptr, false};
+    rc = run_certificate(c, d_edges, E, nullptr, 0, V, M, s, P, B, mode == 1, nullptr, &fin);
     if (rc) return rc;
     const int64_t cap0 = P.cap[0];
     uint32_t n1 = 0, n2 = 0, err = 0;
@@ -627,14 +588,12 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
     c->keys.clear();
     if (mode == 1) {
         // final step on the device: only the bridges come back
-        rc = ensure_pinned(c, 256 + 8 * (size_t)V);
-        if (rc) return rc;
-        uint32_t* hc = static_cast<uint32_t*>(c->pinned);
-        uint64_t* hk = reinterpret_cast<uint64_t*>(static_cast<char*>(c->pinned) + 256);
+        uint32_t* hc = fin.h_status;
+        uint64_t* hk = static_cast<uint64_t*>(fin.h_data);
         uint32_t nk = 0;
         bool solved = false;
         if (P.contract) {
-            launch_contract(P, B, c->contract, 0, hc, hk, nullptr, s);
+            if (!fin.done) launch_contract(P, B, c->contract, 0, hc, hk, nullptr, s);
             BR_HIP(hipGetLastError());
             ev_record(c, 5, s);
             rc = ctx_end(c, s);
@@ -752,22 +711,25 @@ static int classes_common(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t 
     const int mode = c->final_step;   // read once: the workspace layout depends on it
     Plan P;
     DevBufs B;
-    rc = run_certificate(c, d_edges, E, nullptr, 0, V, M, s, P, B, mode == 1);
+    // status block, labels, then the tree's edges
+    const size_t o_tree = (256 + 4 * (size_t)V + 7) & ~size_t(7);
+    rc = ensure_pinned(c, std::max<size_t>(64 << 10, o_tree + 8 * (size_t)std::min<int64_t>(V, kMaxCross)));
+    if (rc) return rc;
+    FinalReq fin{h_tree ? 2 : 1, static_cast<uint32_t*>(c->pinned), static_cast<char*>(c->pinned) + 256,
+                 reinterpret_cast<uint64_t*>(static_cast<char*>(c->pinned) + o_tree), false};
+    rc = run_certificate(c, d_edges, E, nullptr, 0, V, M, s, P, B, mode == 1, nullptr, &fin);
     if (rc) return rc;
     std::vector<uint64_t>& tkeys = c->keys;
     tkeys.clear();
     if (mode == 1) {
         // bridges and classes on the device: the status block, the labels and
         // the tree's edges come back
-        const size_t o_tree = (256 + 4 * (size_t)V + 7) & ~size_t(7);
-        rc = ensure_pinned(c, o_tree + (P.contract ? 8 * (size_t)std::min<int64_t>(V, kMaxCross) : 0));
-        if (rc) return rc;
-        uint32_t* hc = static_cast<uint32_t*>(c->pinned);
-        uint64_t* ht = reinterpret_cast<uint64_t*>(static_cast<char*>(c->pinned) + o_tree);
+        uint32_t* hc = fin.h_status;
+        uint64_t* ht = fin.h_tree;
         uint64_t* d_tkeys = nullptr;
         bool solved = false;
         if (P.contract) {
-            launch_contract(P, B, c->contract, h_tree ? 2 : 1, hc, hc + 64, ht, s);
+            if (!fin.done) launch_contract(P, B, c->contract, fin.mode, hc, fin.h_data, ht, s);
             BR_HIP(hipGetLastError());
             rc = ctx_end(c, s);
             if (rc) return rc;
@@ -990,7 +952,7 @@ int br_autotune(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t
         std::vector<TuneEntry> cands;
         if (E > 0) cands.push_back({{"fuse", 1}});
         for (int tile : {4096, 2048, 1024}) cands.push_back({{"lds", 0}, {"solo", 0}, {"tile", tile}});
-        if (E > 0 && V <= batched_max_v_big() && M < (1 << 20)) cands.push_back({{"lds", 1}});
+        if (E > 0 && V <= batched_max_v_big()) cands.push_back({{"lds", 1}});
         if (E > 0 && V <= solo_max_v()) {
             for (int v = 0; v < solo_variants(); v++) {
                 TuneEntry on{{"lds", 0}, {"solo", 1}, {"variant", v}};

@@ -303,7 +303,6 @@ void launch_phase0(const Plan& P, DevBufs& B, hipStream_t s) {
 int phase0_launches(const Plan& P) {
     // mirrors launch_phase0's choices
     if (P.solo) return 2;
-    if (P.lds) return 1;
     if (P.E == 0) return 0;
     const int64_t per = (P.E + P.M - 1) / P.M;
     const bool has_packed = P.qs != 2 && P.M > 1;

@@ -186,4 +186,40 @@ __device__ bool solve_contracted(SolveLds& L, const Contract& C, uint32_t n, uin
     return true;
 }
 
+// The answer for the host: bridges (mode 0), classes (1) or classes and bridge
+// tree (2).  out: 64 status words -- [1] bridges or classes, [2], [3] |F|, |F'|,
+// [4] error word, [5] bridges (the tree's edges), [6] 1 if solved -- and (modes
+// 0 and 2) the keys min << 32 | max.
+__device__ __forceinline__ void report_contracted(SolveLds& L, const int2* f1, uint32_t c1, uint32_t c2, uint32_t err,
+                                                  uint32_t V, const Contract& C, uint32_t m, bool ok, int32_t mode,
+                                                  uint32_t* out, uint64_t* keys) {
+    if (threadIdx.x == 0) L.nout = 0;
+    __syncthreads();
+    if (ok)
+        for (uint32_t j = threadIdx.x; j < m; j += kSolveT) {
+            if (!C.isbr[j]) continue;
+            uint32_t a, b;
+            if (mode == 0) {
+                const int2 e = f1[C.hk[j]];
+                a = (uint32_t)e.x;
+                b = (uint32_t)e.y;
+            } else {
+                const uint2 r = C.he[j];
+                a = C.hcls[C.hid[r.x] - 1];
+                b = C.hcls[C.hid[r.y] - 1];
+            }
+            const uint32_t p = atomicAdd(&L.nout, 1u);
+            if (mode != 1) keys[p] = (uint64_t)min(a, b) << 32 | max(a, b);
+        }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        out[1] = mode == 0 ? L.nout : V - c2 - (ok ? L.nuni : 0u);
+        out[2] = c1;
+        out[3] = c2;
+        out[4] = err;
+        out[5] = L.nout;
+        out[6] = ok ? 1u : 0u;
+    }
+}
+
 }  // namespace br

@@ -73,13 +73,9 @@ __global__ void __launch_bounds__(kSolveT) k_cross(const int2* f1, const uint32_
     }
 }
 
-// One workgroup: bridges (mode 0), classes (1) or classes and bridge tree (2)
-// of H.  out: 64 status words in host memory -- [1] bridges or classes, [2],
-// [3] |F|, |F'|, [4] error word, [5] bridges (the tree's edges), [6] 1 if
-// solved -- then (modes 0 and 2) the keys min << 32 | max at `keys`.
+// one workgroup solves H and reports to host memory
 __global__ void __launch_bounds__(kSolveT) k_solve(const int2* f1, const uint32_t* cnt, const uint32_t* err, int32_t V,
-                                                   Contract C, int32_t mode, uint32_t* out, uint64_t* keys,
-                                                   uint32_t* solved) {
+                                                   Contract C, int32_t mode, uint32_t* out, uint64_t* keys) {
     extern __shared__ __align__(16) unsigned char raw[];
     SolveLds& L = *reinterpret_cast<SolveLds*>(raw);
     const uint32_t n = C.hcnt[0], m = C.hcnt[1];
@@ -89,34 +85,8 @@ __global__ void __launch_bounds__(kSolveT) k_solve(const int2* f1, const uint32_
             return make_uint2(C.hid[r.x] - 1, C.hid[r.y] - 1);
         });
     __syncthreads();
-    if (threadIdx.x == 0) L.nout = 0;
-    __syncthreads();
-    if (ok)
-        for (uint32_t j = threadIdx.x; j < m; j += kSolveT) {
-            if (!C.isbr[j]) continue;
-            uint32_t a, b;
-            if (mode == 0) {
-                const int2 e = f1[C.hk[j]];
-                a = (uint32_t)e.x;
-                b = (uint32_t)e.y;
-            } else {
-                const uint2 r = C.he[j];
-                a = C.hcls[C.hid[r.x] - 1];
-                b = C.hcls[C.hid[r.y] - 1];
-            }
-            const uint32_t p = atomicAdd(&L.nout, 1u);
-            if (mode != 1) keys[p] = (uint64_t)min(a, b) << 32 | max(a, b);
-        }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        out[1] = mode == 0 ? L.nout : (uint32_t)V - cnt[1] - (ok ? L.nuni : 0u);
-        out[2] = cnt[0];
-        out[3] = cnt[1];
-        out[4] = *err;
-        out[5] = L.nout;
-        out[6] = ok ? 1u : 0u;
-        *solved = ok ? 1u : 0u;
-    }
+    report_contracted(L, f1, cnt[0], cnt[1], *err, (uint32_t)V, C, m, ok, mode, out, keys);
+    if (threadIdx.x == 0) *C.solved = ok ? 1u : 0u;
 }
 
 // class labels of all vertices, straight to host memory
@@ -169,7 +139,7 @@ void launch_contract(const Plan& P, const DevBufs& B, const Contract& C, int mod
                        f1, (const uint32_t*)B.cnt, (const uint32_t*)B.state, B.qs, C);
     hipLaunchKernelGGL(k_solve, dim3(1), dim3(kSolveT), sizeof(SolveLds), s, f1, (const uint32_t*)B.cnt,
                        (const uint32_t*)B.err, P.V, C, mode, h_status,
-                       mode == 0 ? reinterpret_cast<uint64_t*>(h_data) : h_tree, C.solved);
+                       mode == 0 ? reinterpret_cast<uint64_t*>(h_data) : h_tree);
     if (mode != 0)
         hipLaunchKernelGGL(k_labels, dim3(grid_for(P.V)), dim3(256), 0, s, (const uint32_t*)B.state, B.qs, P.V, C,
                            (const uint32_t*)C.solved, reinterpret_cast<int32_t*>(h_data));

@@ -296,6 +296,18 @@ void launch_filter(const DevBufs& B, const Plan& P, uint32_t nsel, uint32_t div,
                            code, P.code_words);
 }
 
+// f(integral constant) for the codes per word
+template <class Fn>
+void with_per(int32_t per, Fn f) {
+    switch (per) {
+        case 2: f(std::integral_constant<int, 2>()); break;
+        case 4: f(std::integral_constant<int, 4>()); break;
+        case 8: f(std::integral_constant<int, 8>()); break;
+        case 16: f(std::integral_constant<int, 16>()); break;
+        default: f(std::integral_constant<int, 32>()); break;
+    }
+}
+
 template <int kPer>
 hipError_t raise_lds() {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_filter<kPer, false>),
@@ -344,6 +356,19 @@ void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int
                        dim3(256), 0, s, reinterpret_cast<uint4*>(base), n16, off, cap, cap0);
 }
 
+// Stage 3 with the table at F.code: every row that is not a multiple of P.s2.
+void launch_filter_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s) {
+    const int64_t nrows = (P.E + kRow - 1) / kRow;
+    const uint32_t nsel = (uint32_t)(nrows - (nrows + P.s2 - 1) / P.s2), div = (uint32_t)(P.s2 - 1);
+    const int cus = g_cus > 0 ? g_cus : 256;
+    // a wavefront takes at least four loads' worth of the list; two
+    // workgroups share a CU where their tables allow it
+    const int64_t units = (int64_t)nsel * (kRow / 128);
+    const int per_cu = 4 * (int64_t)P.code_words + kListBytes <= kFilterLds / 2 ? 2 : 1;
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * per_cu, (units + 4 * kFilterWaves - 1) / (4 * kFilterWaves)));
+    with_per(P.code_per, [&](auto per) { launch_filter<decltype(per)::value>(B, P, nsel, div, F.code, grid, s); });
+}
+
 int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s) {
     if (P.E == 0) return 0;
     int launches = 0;
@@ -383,24 +408,12 @@ int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_
             launches++;
         }
         const dim3 wgrid((unsigned)((P.code_words + 255) / 256));
-        // a wavefront takes at least four loads' worth of the list; two
-        // workgroups share a CU where their tables allow it
-        const int64_t units = (int64_t)nsel * (kRow / 128);
-        const int per_cu = 4 * (int64_t)P.code_words + kListBytes <= kFilterLds / 2 ? 2 : 1;
-        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * per_cu, (units + 4 * kFilterWaves - 1) / (4 * kFilterWaves)));
-        auto go = [&](auto per) {
-            constexpr int kPer = decltype(per)::value;
-            hipLaunchKernelGGL(k_codes<kPer>, wgrid, dim3(256), 0, s, (const uint32_t*)B.state, B.qs, P.V,
+        auto codes = [&](auto per) {
+            hipLaunchKernelGGL(k_codes<decltype(per)::value>, wgrid, dim3(256), 0, s, (const uint32_t*)B.state, B.qs, P.V,
                                (const uint32_t*)F.rcode, F.code, (int64_t)P.code_words);
-            launch_filter<kPer>(B, P, nsel, div, F.code, grid, s);
         };
-        switch (P.code_per) {
-            case 2: go(std::integral_constant<int, 2>()); break;
-            case 4: go(std::integral_constant<int, 4>()); break;
-            case 8: go(std::integral_constant<int, 8>()); break;
-            case 16: go(std::integral_constant<int, 16>()); break;
-            default: go(std::integral_constant<int, 32>()); break;
-        }
+        with_per(P.code_per, codes);
+        launch_filter_rest(P, B, F, s);
         launches += 2;
     }
     return launches;

@@ -115,12 +115,10 @@ struct Plan {
     int32_t workers = 0;           // persistent workgroups
     int32_t nslots = 0;            // union-find slots (workers' own + free pool)
     int32_t tile0_max = 0;         // team path: largest first-stage tile (0 = the kernel's)
-    // the whole phase tree in LDS (batched_kernels.hip: one graph, a
-    // workgroup per chunk and last-arriver merges) when V fits a workgroup's LDS
+    // the union-find in one workgroup's LDS (lds_cert_kernels.hip) when V fits;
+    // M is 1 then
     bool lds = false;
-    bool lds_big = false;          // the 160 KB kernel (V above the small kernel's limit)
-    int32_t lds_blocks = 0;
-    int64_t lds_counters = 0;      // merge arrival counters
+    bool lds_whole = false;        // the whole list offered there (else rows of it, the rest through k_filter)
     // the whole list certified in one pass (fused_kernels.hip); M is 1 then
     bool fused = false;
     int32_t s1 = 1, s2 = 1;        // rows r of stage 1: r % s1 == 0; of stages 1 and 2: r % s2 == 0
@@ -239,10 +237,17 @@ struct FusedBufs {
     uint32_t* code = nullptr;      // [code_words]
 };
 void plan_fused(Plan& P);
+void plan_lds(Plan& P);
 int fused_prepare();               // once per process: the kernels' LDS limit
 // zeroes `bytes` (a multiple of 16) at base and writes node 0's region table
 void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int64_t cap0, hipStream_t s);
 int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);   // kernels enqueued
+void launch_filter_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);
+struct Contract;
+int lds_cert_prepare();            // once per process: the kernel's LDS limit
+// mode >= 0: the final step too where the list is offered whole (arguments as launch_contract)
+int launch_lds_cert(const Plan& P, const DevBufs& B, const FusedBufs& F, const Contract& C, int mode, uint32_t* h_status,
+                    void* h_data, uint64_t* h_tree, hipStream_t s);
 
 // The contracted certificate (contract.hpp, contract_kernels.hip): edges of F
 // that cross components of F', at most kMaxCross of them and of their ends.
@@ -396,8 +401,18 @@ int ensure_pinned(br_ctx* c, size_t bytes);
 // The input is the concatenation of d_a [Ea] and d_b [Eb] (d_b may be null with Eb = 0).
 // device_final: reserve the device bridge step's scratch in the workspace.
 // plan_knobs: plan with these tuner knobs instead of the tuner's entry.
+// final_req: where the final step's answer goes; a plan that runs it in the
+// same launch sets its `done`.
+struct FinalReq {
+    int mode;
+    uint32_t* h_status;
+    void* h_data;
+    uint64_t* h_tree;
+    bool done;
+};
 int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_b, int64_t Eb, int32_t V, int32_t M,
-                    hipStream_t s, Plan& P, DevBufs& B, bool device_final, const TuneEntry* plan_knobs = nullptr);
+                    hipStream_t s, Plan& P, DevBufs& B, bool device_final, const TuneEntry* plan_knobs = nullptr,
+                    FinalReq* final_req = nullptr);
 int run_certificate_with(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t M, hipStream_t s, Plan& P,
                          DevBufs& B, bool device_final, const TuneEntry* plan_knobs);
 // Order stream s after everything earlier calls on this context enqueued
