@@ -100,7 +100,12 @@ __global__ void __launch_bounds__(256) k_flatten(uint32_t* q, int64_t qs, int32_
                 const uint32_t d = q[qs * x + f];
                 if (d == 0) { root = f == 1; continue; }
                 uint32_t r = (uint32_t)x - d;
-                for (uint32_t e = q[qs * (int64_t)r + f]; e != 0; e = q[qs * (int64_t)r + f]) r -= e;
+                int n = 0;
+                for (uint32_t e = q[qs * (int64_t)r + f]; e != 0; e = q[qs * (int64_t)r + f]) {
+                    r -= e;
+                    // a long chain: leave the way so far to whoever comes by here
+                    if (++n % kFreeSteps == 0) q[qs * x + f] = (uint32_t)x - r;
+                }
                 if (r != (uint32_t)x - d) q[qs * x + f] = (uint32_t)x - r;
             }
         }

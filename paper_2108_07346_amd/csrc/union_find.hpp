@@ -23,59 +23,65 @@ __device__ __forceinline__ uint64_t ld2(const uint32_t* p) {
     return __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
-// representative of x in forest F (path halving on the way)
-template <int F>
-__device__ __forceinline__ uint32_t uf_find(uint32_t* q, int64_t qs, uint32_t x) {
-    uint32_t d = ld(q + qs * (int64_t)x + F);
-    while (d != 0) {
-        const uint32_t p = x - d;
-        const uint32_t dp = ld(q + qs * (int64_t)p + F);
-        if (dp == 0) return p;
-        st(q + qs * (int64_t)x + F, d + dp);   // x now points at its grandparent
-        x = p - dp;
-        d = ld(q + qs * (int64_t)x + F);
-    }
-    return x;
-}
+constexpr int kFreeSteps = 16;   // steps of a search before it begins to shorten the chain
 
-// true iff this call merged the components of u and v in forest F
+// Unite u and v, whose parents were seen as pu and pv (however stale, each
+// names an ancestor or the vertex itself); true iff this call merged their
+// components.  The end whose parent is larger moves up, so the search stops
+// where the two chains meet (Rem's order; no need to reach the roots), and a
+// root that is reached hooks under the other end's parent.  Long searches halve
+// the chain as they go; short ones leave no dirty lines behind, which hooks
+// (swaps at the memory side) would have to write back first.
 //
 // A root that many lanes want to hook is one address, and compare-and-swaps on
 // one address queue at the memory side whether they win or fail.  By the time
-// v's root is found, u has often been hooked by another lane; a device-scope
+// the search is over, u has often been hooked by another lane; a device-scope
 // load (past this XCD's caches, which may show a root long hooked) sees that
-// without joining the queue.  Measured on 1.5 M random edges over 10^6
-// vertices, F and F': 1,400-1,800 us without the load, 215 us with it; 133,072
-// over 66,536: 300-800 and 77 us.
+// without joining the queue.
+//
+// Measured, F and F': 1.5 M random edges over 10^6 vertices 1,400-1,800 us with
+// two full searches and no load before the swap, 215 with the load, 200 in
+// Rem's order; 133,072 over 66,536 vertices 300-800, 77, 62 us; 534,288 over
+// 267,144 vertices (load) 153, 133 us.
 template <int F>
-__device__ __forceinline__ bool uf_unite(uint32_t* q, int64_t qs, uint32_t u, uint32_t v) {
-    for (;;) {
-        u = uf_find<F>(q, qs, u);
-        v = uf_find<F>(q, qs, v);
-        if (u == v) return false;
-        if (u < v) { const uint32_t t = u; u = v; v = t; }
-        uint32_t* w = q + qs * (int64_t)u + F;
-        uint32_t d = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (d == 0 && __hip_atomic_compare_exchange_strong(w, &d, u - v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT))
-            return true;
-        u = u - d;   // u was hooked meanwhile: continue from its parent
+__device__ __forceinline__ bool uf_unite(uint32_t* q, int64_t qs, uint32_t u, uint32_t pu, uint32_t v, uint32_t pv) {
+    for (int n = 0;; n++) {
+        if (pu == pv) return false;
+        if (pu < pv) {
+            uint32_t t = u;
+            u = v;
+            v = t;
+            t = pu;
+            pu = pv;
+            pv = t;
+        }
+        if (u == pu) {
+            uint32_t* w = q + qs * (int64_t)u + F;
+            uint32_t d = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (d == 0 && __hip_atomic_compare_exchange_strong(w, &d, u - pv, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT))
+                return true;
+            pu = u - d;   // u was hooked meanwhile
+            continue;
+        }
+        const uint32_t g = pu - ld(q + qs * (int64_t)pu + F);
+        if (n >= kFreeSteps && g != pu) st(q + qs * (int64_t)u + F, u - g);
+        u = pu;
+        pu = g;
     }
 }
 
-// Offer edge (u,v) to F, then (if rejected) to F'.  su, sv are the
-// endpoints' parent words (F low, F' high), loaded earlier with one 8-byte
-// load each: however stale, each names an ancestor (or the vertex itself), a
-// valid place to start the finds from.
+// Offer edge (u,v) to F, then (if rejected) to F'.  su, sv are the endpoints'
+// parent words (F low, F' high), loaded earlier with one 8-byte load each.
+// F' only joins what F joins, so a shared parent in F' rejects the edge in both.
 __device__ __forceinline__ void offer_from(uint32_t* q, int64_t qs, uint32_t u, uint32_t v, uint64_t su, uint64_t sv,
                                            bool& a1, bool& a2) {
     const uint32_t p1u = u - (uint32_t)su, p1v = v - (uint32_t)sv;
-    a1 = (p1u != p1v) && uf_unite<0>(q, qs, p1u, p1v);
-    a2 = false;
-    if (!a1) {
-        const uint32_t p2u = u - (uint32_t)(su >> 32), p2v = v - (uint32_t)(sv >> 32);
-        a2 = (p2u != p2v) && uf_unite<1>(q, qs, p2u, p2v);
-    }
+    const uint32_t p2u = u - (uint32_t)(su >> 32), p2v = v - (uint32_t)(sv >> 32);
+    a1 = a2 = false;
+    if (p2u == p2v) return;
+    a1 = uf_unite<0>(q, qs, u, p1u, v, p1v);
+    if (!a1) a2 = uf_unite<1>(q, qs, u, p2u, v, p2v);
 }
 
 // Accepted edges of one workgroup tile are staged in LDS (F from the front,
