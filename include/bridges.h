@@ -208,10 +208,9 @@ int br_bridges_find_batched(br_ctx* ctx, const int32_t* d_edges, const int64_t* 
                             int32_t G, int32_t chunk_edges, int32_t* h_bridges, int64_t cap, int64_t* h_bridge_off,
                             void* stream);
 int32_t br_batched_max_v(void);
-/* Largest V for which a plain-path call can run the whole phase tree of
- * Section III inside one workgroup's LDS per chunk (the union-find of
- * Algorithm 2 as two 16-bit parent offsets per vertex in 160 KB); such calls
- * do when their chunks are short enough for one CU each. */
+/* Largest V of a graph whose union-find state (Algorithm 2, two 16-bit parent
+ * offsets per vertex) fits one workgroup's 160 KB of LDS: the batched path
+ * certifies such graphs there, the plain path plans for them (plan_kind 2). */
 int32_t br_lds_max_v(void);
 
 /*
@@ -219,7 +218,7 @@ int32_t br_lds_max_v(void);
  * device and input shape and keep the fastest for later calls on inputs of
  * the same shape bucket (V and E in powers of two, the same M): the whole
  * list in one pass, the team path (many workgroups per chunk) with three first-stage tiles, the
- * whole-tree LDS kernel where V fits, and the one-workgroup-per-node path in
+ * plan for graphs that fit a workgroup's LDS, and the one-workgroup-per-node path in
  * each worker shape with the depths of the merges it does itself around its
  * default; then the winner again with its team merges requesting each
  * thread's edges at once, and (one-workgroup-per-node) with the siblings'
@@ -261,8 +260,11 @@ typedef struct br_profile {
     double ms_bridge_dev;  /* device bridge step (final step 1 only)              */
     int64_t plan_kind;     /* certificate plan of the last plain-path call: 0 many
                               workgroups per chunk, 1 one workgroup per node
-                              (resident slots), 2 the whole tree in LDS, 3 the
-                              whole list in one pass (no merge rounds)         */
+                              (resident slots), 2 graphs that fit a workgroup's
+                              LDS (V <= br_lds_max_v(); the union-find, or the
+                              component table most edges stop at, in LDS; no
+                              merge rounds), 3 larger graphs, the whole list in
+                              one pass (no merge rounds)                       */
     int64_t alg_bytes;     /* br_bridges_find at profiling level 2, plans 0, 1 and 3:
                               the bytes the method itself moves at this M
                               (Section III): 8 per input edge read by phase 0,

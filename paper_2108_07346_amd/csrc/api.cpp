@@ -70,30 +70,24 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     // workload: M = 16 / 1 chunks 0.59 / 0.37 ms).
     const int lds_want = knob("BR_LDS", "lds", -1);
     const bool plan_env = env_int("BR_SOLO", -1) >= 0 || env_int("BR_LDS", -1) >= 0;   // wins over a tuned "fuse"
-    const int fuse = plan_env ? env_int("BR_FUSE", 0) : knob("BR_FUSE", "fuse", -1);
+    const int fuse = plan_env ? env_int("BR_FUSE", -1) : knob("BR_FUSE", "fuse", -1);
     const bool named = knob("BR_SOLO", "solo", -1) >= 0 || lds_want >= 0;
-    const int64_t per_chunk = (E + M - 1) / M;   // largest chunk
-    // the union-find in LDS wherever V fits a workgroup's: a search step costs a
-    // tenth of one through the caches
-    if (allow_solo && E > 0 && fuse != 1 && V <= batched_max_v_big() && lds_want != 0) {
-        P.lds = true;
+    // graphs that fit a workgroup's LDS never take the tree unless told to
+    const bool small_v = V <= batched_max_v_big() && lds_want != 0;
+    if (allow_solo && E > 0 && (fuse == 1 || (fuse < 0 && (!named || small_v)))) {
         P.M = 1;
-        P.qs = 2;
         P.off = {0};
         P.cap = {std::min(E, bound)};
         P.cert_pairs = P.cap[0];
-        P.contract = true;
-        plan_lds(P);
-        return P;
-    }
-    if (allow_solo && E > 0 &&
-        (fuse == 1 || (fuse < 0 && !named))) {
+        P.kind = small_v && fuse != 1 ? 2 : 3;
+        if (P.kind == 2 && plan_lds(P)) {
+            P.lds = true;
+            P.qs = 2;
+            P.contract = true;
+            return P;
+        }
         P.fused = true;
-        P.M = 1;
         P.qs = (int64_t)V * 32 <= (int64_t(128) << 20) ? 8 : 2;
-        P.off = {0};
-        P.cap = {std::min(E, bound)};
-        P.cert_pairs = P.cap[0];
         plan_fused(P);
         // on a dense list nearly every edge of F lies inside a component of F'
         P.contract = V <= 4096 || E >= 6 * (int64_t)V;
@@ -102,7 +96,7 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     while ((int64_t(1) << P.rounds) < M) P.rounds++;
     // phase-0 tiles fill the LDS stage; merge rounds size their own tiles
     P.tile = tile_size();
-    const int64_t per = per_chunk;
+    const int64_t per = (E + M - 1) / M;   // largest chunk
     P.tpc = (int32_t)std::max<int64_t>(1, (per + P.tile - 1) / P.tile);
     P.xcd_map = M >= 8 ? 1 : 0;
     const int64_t chunk_slots = P.xcd_map ? 8 * ((M + 7) / 8) : M;
@@ -147,6 +141,7 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     if (allow_solo && E > 0 && V <= solo_max_v() &&
         (want == 1 || (want < 0 && M >= cus && per <= (int64_t)V && V >= (1 << 17)))) {
         P.solo = true;
+        P.kind = 1;
         P.solo_variant = std::max(0, std::min(knob("BR_SOLO_VARIANT", "variant", 2), solo_variants() - 1));
         // 1,024 threads of workers per CU where registers and LDS hold them
         // (large workload, M = 4096: 64 → 256 workers of 1,024 threads
@@ -324,7 +319,7 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
     B.off = reinterpret_cast<const int64_t*>(base + L.off);
     B.cap = reinterpret_cast<const int64_t*>(base + L.cap);
     c->bws = reinterpret_cast<int32_t*>(base + L.bws);
-    c->prof.plan_kind = P.fused ? 3 : (P.lds ? 2 : (P.solo ? 1 : 0));
+    c->prof.plan_kind = P.kind;
     c->prof.rounds = P.rounds;
     if (P.fused || P.lds) {
         rc = fused_prepare();
@@ -946,7 +941,7 @@ int br_autotune(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t
     if (!tune_get(key, best)) {
         source = 1;
         // candidate plans: the whole list in one pass, the team path with three first-stage tiles, the
-        // whole-tree LDS kernel where V fits, and the one-workgroup-per-node
+        // plan for graphs that fit a workgroup's LDS, and the one-workgroup-per-node
         // path in each worker shape with the merge depths around its default
         // (and depths 1 and 2)
         std::vector<TuneEntry> cands;

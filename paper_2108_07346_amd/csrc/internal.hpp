@@ -118,6 +118,7 @@ struct Plan {
     // the union-find in one workgroup's LDS (lds_cert_kernels.hip) when V fits;
     // M is 1 then
     bool lds = false;
+    int32_t kind = 0;              // br_profile.plan_kind
     bool lds_whole = false;        // the whole list offered there (else rows of it, the rest through k_filter)
     // the whole list certified in one pass (fused_kernels.hip); M is 1 then
     bool fused = false;
@@ -237,7 +238,7 @@ struct FusedBufs {
     uint32_t* code = nullptr;      // [code_words]
 };
 void plan_fused(Plan& P);
-void plan_lds(Plan& P);
+bool plan_lds(Plan& P);            // false: V is past what that plan is for
 int fused_prepare();               // once per process: the kernels' LDS limit
 // zeroes `bytes` (a multiple of 16) at base and writes node 0's region table
 void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int64_t cap0, hipStream_t s);

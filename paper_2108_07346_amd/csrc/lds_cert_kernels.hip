@@ -1,4 +1,4 @@
-// The certificate of a graph of up to 40,944 vertices with the union-find in
+// The certificate of a graph of up to 8,192 vertices with the union-find in
 // one workgroup's LDS (16-bit offsets of both forests in one word per vertex),
 // and for short lists the final step in the same launch.
 //
@@ -6,7 +6,7 @@
 // through the caches, so one workgroup with its state in LDS is faster than
 // hundreds that share one in memory as long as it has few edges to offer.
 // Short lists (P.lds_whole) are offered whole.  Of longer ones it takes rows
-// spread over the list, about 4V edges, after which F' is nearly complete; its
+// spread over the list, 2V or 3V edges, after which F' is nearly complete; its
 // state, compressed, then goes to memory together with the table of F'
 // components (16-bit codes: the root's id + 1), and k_filter sends the rest of
 // the list past the table on every CU (fused_kernels.hip).
@@ -142,18 +142,32 @@ __global__ void __launch_bounds__(kT) k_lds_cert(DevBufs B, int64_t E, int32_t V
 
 }  // namespace
 
+// Vertices up to which this plan is the faster one: one CU offers an edge in
+// 2 to 3 ns, and a graph needs about 2V of them before the table is worth
+// anything (512,000 edges, query with this plan / with stages 1 and 2 on all
+// CUs: V = 2,000 62 / 93 us, 4,000 77 / 94, 8,000 123 / 121, 16,000 172 / 122).
+constexpr int32_t kLdsV = 8192;
+
 // Whether the list is offered whole, and the stride of the rows taken else.
-void plan_lds(Plan& P) {
+// Whole against rows: V = 1,000 45 / 49 us at 16,000 edges, 64 / 51 at 64,000;
+// V = 4,000 82 / 102 at 16,000, 97 / 96 at 32,000; V = 8,000 118 / 129 at
+// 32,000, 148 / 123 at 64,000.  Rows of 3V edges leave fewer for the searches
+// in memory (V = 1,000, 512,000 edges: 2V 61, 3V 54 us); past 4,096 vertices
+// 2V is faster (V = 8,000: 123 and 131 us).
+bool plan_lds(Plan& P) {
     const int64_t E = P.E, V = P.V;
-    P.lds_whole = E <= std::max<int64_t>(6 * V, 32768);
-    P.s1 = P.s2 = P.lds_whole ? 1 : (int32_t)std::max<int64_t>(2, std::min<int64_t>(E / (4 * V), 1 << 20));
+    if (V > kLdsV) return false;
+    P.lds_whole = E <= std::max<int64_t>(16384, std::min<int64_t>(8 * V, 32768));
+    const int64_t sample = (V <= 4096 ? 3 : 2) * V;
+    P.s1 = P.s2 = P.lds_whole ? 1 : (int32_t)std::max<int64_t>(2, std::min<int64_t>(E / sample, 1 << 20));
     P.code_per = P.lds_whole ? 0 : 2;
     P.code_words = P.lds_whole ? 0 : (int32_t)(((V + 1) / 2 + 3) & ~int64_t(3));
+    return true;
 }
 
 int lds_cert_prepare() {
     static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_cert),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 64);
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
     return e == hipSuccess ? BR_OK : hip_fail(e, "hipFuncSetAttribute(k_lds_cert)");
 }
 

@@ -21,20 +21,23 @@ __device__ __forceinline__ uint32_t with_half(uint32_t w, uint32_t h) {
     return F ? ((w & 0xffffu) | (h << 16)) : ((w & 0xffff0000u) | h);
 }
 
+// Representative of x, halving the path: reads and stores of one half, so the
+// other half, which may be changing under a concurrent hook, is left alone.
+// One workgroup's searches are bound by instructions, not by LDS latency (its
+// 16 wavefronts share one CU's issue), so the plain loop wins: climbing both
+// chains at once or in Rem's order, which needs fewer steps, measured 182 and
+// 193 us against 118 for 49,000 edges over 12,345 vertices.
 template <int F>
 __device__ __forceinline__ uint32_t lfind(uint32_t* q, uint32_t x) {
-    uint32_t w = q[x];
-    uint32_t d = half<F>(w);
+    lds_half* h = reinterpret_cast<lds_half*>(q) + F;
+    uint32_t d = h[2 * x];
     while (d != 0) {
         const uint32_t p = x - d;
-        const uint32_t dp = half<F>(q[p]);
+        const uint32_t dp = h[2 * p];
         if (dp == 0) return p;
-        // path halving: a 16-bit store leaves the other half of the word, which
-        // may be changing under a concurrent hook, alone
-        reinterpret_cast<lds_half*>(q)[2 * x + F] = (uint16_t)(d + dp);
+        h[2 * x] = (uint16_t)(d + dp);
         x = p - dp;
-        w = q[x];
-        d = half<F>(w);
+        d = h[2 * x];
     }
     return x;
 }
@@ -59,17 +62,16 @@ __device__ __forceinline__ bool lunite(uint32_t* q, uint32_t u, uint32_t v) {
 }
 
 // Offer (u,v) to F, then to F'.  Both parents come from one 32-bit word per
-// endpoint: when the endpoints already share a parent in a forest (the usual
-// case once the state is compressed) that forest rejects without a search.
+// endpoint; F' only joins what F joins, so a shared parent in F' rejects the
+// edge in both (the usual case once the state is compressed).
 __device__ __forceinline__ void loffer(uint32_t* q, uint32_t u, uint32_t v, bool& a1, bool& a2) {
     const uint32_t wu = q[u], wv = q[v];
+    const uint32_t p2u = u - (wu >> 16), p2v = v - (wv >> 16);
+    a1 = a2 = false;
+    if (p2u == p2v) return;
     const uint32_t p1u = u - (wu & 0xffffu), p1v = v - (wv & 0xffffu);
-    a1 = (p1u != p1v) && lunite<0>(q, p1u, p1v);
-    a2 = false;
-    if (!a1) {
-        const uint32_t p2u = u - (wu >> 16), p2v = v - (wv >> 16);
-        a2 = (p2u != p2v) && lunite<1>(q, p2u, p2v);
-    }
+    a1 = p1u != p1v && lunite<0>(q, p1u, p1v);
+    if (!a1) a2 = lunite<1>(q, p2u, p2v);
 }
 
 // Full path compression of the LDS state (no concurrent hooks: called between

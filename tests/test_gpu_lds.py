@@ -61,10 +61,11 @@ def mixed(V, E, rng):
     return e[rng.permutation(E)]
 
 
-@pytest.mark.parametrize("V", [1, 2, 100, 5461, 5462, 40_943, 40_944])
+# one workgroup up to 8,192 vertices (rows of 3V edges up to 4,096, else 2V)
+@pytest.mark.parametrize("V", [1, 2, 100, 2049, 4096, 4097, 8192, 8193, 40_943, 40_944])
 def test_list_lengths(ctx, V):
     rng = np.random.default_rng(V)
-    whole = max(6 * V, 32_768)                            # offered whole up to here
+    whole = max(16_384, min(8 * V, 32_768))               # offered whole up to here
     for E in (1, 511, 1025, whole - 1, whole, whole + 1, 2 * whole + 513, 9 * whole + 7):
         check(ctx, mixed(V, E, rng), V, "mixed")
 
