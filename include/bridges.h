@@ -297,23 +297,25 @@ int br_get_profile(br_ctx* ctx, br_profile* out);
  * br_articulation_points -- the "failure points" of the abstract: vertices
  * whose removal (with their edges) increases the number of connected
  * components (Section I's bridge definition carried over to vertices).
- * Path: a scan-first certificate of the whole edge list on the GPU -- F a
+ * With the default final step (see br_set_final_step): a spanning forest F of
+ * the list (Algorithm 2's union-find), rooted by its Euler tours, then its
+ * edges grouped into blocks by all the edges of the list (an edge between
+ * unrelated vertices joins their parent edges; a child's parent edge joins its
+ * parent's when the child's subtree reaches outside the parent's), a vertex cut
+ * iff its child edges are not all in its own parent edge's block (a root: in
+ * two or more blocks).  A long list goes through the rules in part, and the
+ * rest only where it joins different groups.
+ * Final step 0: a scan-first certificate of the list on the GPU -- F a
  * breadth-first forest of G (each tree from the smallest vertex of its
  * component; a newly reached vertex takes its smallest-id neighbour one level
  * up as parent), F' a breadth-first forest of G without the vertex pairs of F
- * (all parallel copies of them left out) -- then the cut-vertex test on
- * F u F' (at most 2(V-1) edges).  With the default final step (see
- * br_set_final_step) the test runs on the GPU: F rooted by its Euler tours,
- * tree edges grouped into blocks (an edge of F' between unrelated vertices
- * joins their parent edges; a child's parent edge joins its parent's when the
- * child's subtree reaches outside the parent's), a vertex cut iff its child
- * edges are not all in its own parent edge's block (a root: in two or more
- * blocks).  Final step 0 runs the low-link search on the host instead: a
- * non-root p cuts iff a child c has low[c] >= disc[p], a root iff it has two
- * or more children.  The
- * union-find forests of Algorithm 2 (Section IV-B) would not do: they keep
- * edge connectivity but not vertex connectivity; search-ordered forests keep
- * both (the certificate definition of Section III, for 2-vertex connectivity).
+ * (all parallel copies of them left out) -- and the low-link search on F u F'
+ * (at most 2(V-1) edges) on the host: a non-root p cuts iff a child c has
+ * low[c] >= disc[p], a root iff it has two or more children.  The
+ * union-find forests of Algorithm 2 (Section IV-B) would not do as a
+ * certificate here: they keep edge connectivity but not vertex connectivity;
+ * search-ordered forests keep both (the certificate definition of Section III,
+ * for 2-vertex connectivity).
  *   d_edges  device int32 [E][2], E <= 2^31 - 1; self-loops and parallel edges accepted.
  *   h_out    host int32 [cap]: vertex ids ascending; cap >= V always suffices.
  *   *n_out   number of articulation points; BR_ECAP (no ids written) if it exceeds cap.

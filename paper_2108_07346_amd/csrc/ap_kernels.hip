@@ -631,7 +631,7 @@ static void components(const ApWs& W, const int2* edges, int64_t E, int32_t V, c
 // The scan-first certificate (F, F') of d_edges, left on the device: F at
 // *d_f1, F' at *d_f2, |F| and |F'| at (*d_cnt)[0..1], the error word at
 // *d_err, and per vertex 0 at the roots of F, 1 elsewhere, at *d_roots.
-int scan_first_device(const int2* edges, int64_t E, int32_t V, char* ws, hipStream_t s, uint32_t* h_small, int* levels1,
+static int scan_first_device(const int2* edges, int64_t E, int32_t V, char* ws, hipStream_t s, uint32_t* h_small, int* levels1,
                       int* levels2, int2** d_f1, int2** d_f2, uint32_t** d_cnt, uint32_t** d_err, uint32_t** d_roots) {
     const ApWs W = ap_carve(ws, E, V);
     hipLaunchKernelGGL(k_zero_u32, dim3(grid_for(W.zero_words)), dim3(kT), 0, s, reinterpret_cast<uint32_t*>(ws),

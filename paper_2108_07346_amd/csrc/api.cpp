@@ -253,7 +253,7 @@ static Layout layout(const Plan& P, bool device_final) {
     L.state = o;
     if (!P.solo) o = align256(o + sizeof(uint32_t) * (size_t)P.qs * (size_t)P.V * (size_t)P.M);
     L.packed = o; if (!P.solo && !P.fused && P.qs != 2 && P.M > 1) o = align256(o + sizeof(uint32_t) * 2 * (size_t)P.V * (size_t)P.M);
-    L.rcode = o; if (P.fused && P.code_per) o = align256(o + sizeof(uint32_t) * ((size_t)P.V + 1));   // and the codes' counter
+    L.rcode = o; if (P.code_per) o = align256(o + sizeof(uint32_t) * ((size_t)P.V + 1));   // and the codes' counter
     L.hid = o; if (P.contract && device_final) o = align256(o + sizeof(uint32_t) * contract_clear_words(P.V));
     L.cert = o; o = align256(o + sizeof(int2) * (size_t)std::max<int64_t>(P.cert_pairs, 1));
     L.off = o; o = align256(o + sizeof(int64_t) * (size_t)P.M);
@@ -331,6 +331,7 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
         F.rcode = reinterpret_cast<uint32_t*>(base + L.rcode);
         F.ncode = F.rcode + P.V;
         F.code = reinterpret_cast<uint32_t*>(base + L.code);
+        c->fused = F;
         c->contract = Contract();
         if (P.contract && device_final)
             c->contract = contract_carve(reinterpret_cast<uint32_t*>(base + L.hid), reinterpret_cast<uint32_t*>(base + L.ctr), V);
@@ -853,33 +854,27 @@ int br_articulation_points(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t
     rc = ctx_begin(c, s);
     if (rc) return rc;
     const int mode = c->final_step;   // read once: the workspace layout depends on it
-    const size_t ws_cert = 4 * (size_t)scan_first_words(E, V);
-    const size_t ws_test = mode == 1 ? 4 * (size_t)device_bridges_words(V) : 0;
-    c->solo_key_base = nullptr;        // the scan-first search reuses the workspace
-    rc = ensure_workspace(c, ws_cert + ws_test + 256, s);
+    rc = ensure_pinned(c, std::max<size_t>(64 << 10, 256 + 2 * sizeof(int2) * (size_t)std::max(V, 1)));
     if (rc) return rc;
-    rc = ensure_pinned(c, 256 + 2 * sizeof(int2) * (size_t)std::max(V, 1));
-    if (rc) return rc;
-    char* h = static_cast<char*>(c->pinned);
-    uint32_t* hs = reinterpret_cast<uint32_t*>(h);
     uint32_t n1 = 0, n2 = 0;
     int l1 = 0, l2 = 0;
     std::vector<int32_t> aps;
     std::chrono::steady_clock::time_point t1;
-    char* wsb = static_cast<char*>(c->ws.base);
     if (mode == 1) {
-        // test on the device: only the articulation points come back
-        int2 *f1 = nullptr, *f2 = nullptr;
-        uint32_t *cnt = nullptr, *err = nullptr, *roots = nullptr;
-        rc = scan_first_device(reinterpret_cast<const int2*>(d_edges), E, V, wsb, s, hs, &l1, &l2, &f1, &f2, &cnt, &err,
-                               &roots);
+        // test on the device, on a spanning forest of the whole list: only the
+        // articulation points come back
+        const TuneEntry one{{"fuse", 1}};
+        Plan P;
+        DevBufs B;
+        rc = run_certificate(c, d_edges, E, nullptr, 0, V, 1, s, P, B, true, &one);
         if (rc) return rc;
-        int32_t* tws = reinterpret_cast<int32_t*>(wsb + ((ws_cert + 255) & ~size_t(255)));
+        char* h = static_cast<char*>(c->pinned);
+        uint32_t* hs = reinterpret_cast<uint32_t*>(h);
         uint64_t* d_keys = nullptr;
         uint32_t* d_n = nullptr;
-        rc = device_articulation_cert(f1, f2, 1, cnt, roots, 1, V, tws, &d_keys, &d_n, s);
+        rc = device_articulation(P, B, c->fused, c->bws, &d_keys, &d_n, s);
         if (rc) return rc;
-        launch_bridge_status(cnt, err, d_n, s);
+        launch_bridge_status(B.cnt, B.err, d_n, s);
         BR_HIP(hipGetLastError());
         uint64_t* hk = reinterpret_cast<uint64_t*>(h + 256);
         const size_t guess = std::min<size_t>(std::max<size_t>(c->keys_hint, 1024), (size_t)std::max(V, 1));
@@ -901,7 +896,14 @@ int br_articulation_points(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t
         for (uint32_t i = 0; i < nk; i++) aps[i] = (int32_t)hk[i];
         std::sort(aps.begin(), aps.end());
     } else {
-        // Algorithm 1's search (vertex test) on the host over the copied certificate
+        // Algorithm 1's search (vertex test) on the host over the copied
+        // scan-first certificate
+        c->solo_key_base = nullptr;        // the scan-first search reuses the workspace
+        rc = ensure_workspace(c, 4 * (size_t)scan_first_words(E, V) + 256, s);
+        if (rc) return rc;
+        char* h = static_cast<char*>(c->pinned);
+        uint32_t* hs = reinterpret_cast<uint32_t*>(h);
+        char* wsb = static_cast<char*>(c->ws.base);
         int2* hf1 = reinterpret_cast<int2*>(h + 256);
         int2* hf2 = hf1 + std::max(V, 1);
         rc = scan_first_certificate(reinterpret_cast<const int2*>(d_edges), E, V, wsb, s, hs, hf1, hf2, &n1, &n2, &l1,
@@ -916,7 +918,7 @@ int br_articulation_points(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t
     *n_out = (int64_t)aps.size();
     c->prof.cert_f1 = n1;
     c->prof.cert_f2 = n2;
-    c->prof.rounds = l1 + l2;          // breadth-first levels of the two forests
+    c->prof.rounds = l1 + l2;          // breadth-first levels of the two forests (final step 0)
     c->prof.ms_cert = std::chrono::duration<double, std::milli>(t1 - t0).count();
     c->prof.ms_dfs = std::chrono::duration<double, std::milli>(t2 - t1).count();
     c->prof.ms_total = c->prof.ms_cert + c->prof.ms_dfs;

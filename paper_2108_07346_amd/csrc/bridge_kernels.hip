@@ -19,14 +19,15 @@
 //
 // Launches: one clear, the arc lists, the ranking (one launch whose threads
 // jump asynchronously), tour sizes, downward arcs, one scan, preorder numbers,
-// the F' ranges, the range tables (two launches while the block table fits a
-// workgroup's LDS), the test -- eleven in all.
+// the F' ranges, the range tables (three launches up to 2^24 vertices), the test
+// -- twelve in all.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
 
 #include "device_util.hpp"
 #include "internal.hpp"
+#include "union_find.hpp"
 
 namespace br {
 
@@ -327,6 +328,17 @@ __global__ void k_preorder(const int2* f1, const uint32_t* q, int32_t qs, const 
     }
 }
 
+// An edge between numbers px and py: each vertex's range holds its own number,
+// so only the smaller one's upper end and the larger one's lower end can move
+// (the other two atomics of the four, 2.2 M in all for 548,000 edges, took half
+// of the 90 us).  A stale word read past is only further from the end it moves
+// to: the atomic then settles it.
+__device__ __forceinline__ void range_touch(int32_t* tmin, int32_t* tmax, int32_t px, int32_t py) {
+    const int32_t a = min(px, py), b = max(px, py);
+    if (tmax[a] < b) atomicMax(&tmax[a], b);
+    if (tmin[b] > a) atomicMin(&tmin[b], a);
+}
+
 // F' edges pull each endpoint's range toward the other endpoint's number
 // (both endpoints of an F' edge lie in one tree of F, so both are numbered)
 __global__ void k_nontree(const int2* f2, int32_t dir, const uint32_t* cnt, const int32_t* pre, int32_t* tmin,
@@ -336,10 +348,7 @@ __global__ void k_nontree(const int2* f2, int32_t dir, const uint32_t* cnt, cons
         const int2 e = f2[dir * k];
         const int32_t px = pre[e.x], py = pre[e.y];
         if (px < 0 || py < 0) continue;   // only an inconsistent certificate gets here
-        atomicMin(&tmin[px], py);
-        atomicMax(&tmax[px], py);
-        atomicMin(&tmin[py], px);
-        atomicMax(&tmax[py], px);
+        range_touch(tmin, tmax, px, py);
     }
 }
 
@@ -347,16 +356,49 @@ __global__ void k_nontree(const int2* f2, int32_t dir, const uint32_t* cnt, cons
 //
 // Blocks of 64 numbers (one wavefront each).  Inside a block, level j (1..5)
 // holds the min/max of the 2^j numbers starting at each position (clipped at
-// the block's end), so any range inside one block takes two lookups; a sparse
-// table over the blocks' own min/max answers a run of whole blocks; one
-// workgroup builds that table in LDS when it is small.
+// the block's end), so any range inside one block takes two lookups.  The
+// blocks' own min/max form the next layer, in blocks of 64 again; over its
+// block values a sparse table answers a run of whole blocks (one workgroup
+// builds it in LDS while it is small: up to 2^24 numbers).  One sparse table
+// over the blocks of the first layer took a launch per level past 262,144
+// numbers (13 launches, 60 us at 10^6).
 constexpr int kRB = 64;
 constexpr int kInLev = 5;              // in-block levels 1..5 (level 6 = the block value)
 constexpr int kLdsBlocks = 4096;       // block tables up to this size are built in LDS
 
 __device__ __forceinline__ int floor_log2(uint32_t x) { return 31 - __clz(x); }
 
-__device__ void build_block_table(int32_t* tmn, int32_t* tmx, int64_t nb, int32_t levels, int32_t* smn, int32_t* smx) {
+// one layer: n values (t, u), their in-block levels, their blocks' values
+struct RmqLayer {
+    int32_t *t, *u, *lmin, *lmax, *bmn, *bmx;
+    int64_t n;
+};
+struct Rmq {
+    RmqLayer a, b;                     // b: over a's block values; b's block values are the table's level 0
+    int64_t nb;                        // entries per level of the table
+};
+
+// per block: in-block levels and the block's min/max
+__global__ void __launch_bounds__(kT) k_rmq_blocks(RmqLayer L) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    int32_t a = i < L.n ? L.t[i] : INT32_MAX, b = i < L.n ? L.u[i] : INT32_MIN;
+    for (int j = 1; j <= kInLev + 1; j++) {
+        const int o = 1 << (j - 1);
+        const int32_t da = __shfl_down(a, o), db = __shfl_down(b, o);
+        if (lane + o < 64) { a = min(a, da); b = max(b, db); }
+        if (j <= kInLev) {
+            if (i < L.n) { L.lmin[(int64_t)(j - 1) * L.n + i] = a; L.lmax[(int64_t)(j - 1) * L.n + i] = b; }
+        } else if (lane == 0 && i < L.n) {
+            L.bmn[i >> 6] = a;
+            L.bmx[i >> 6] = b;
+        }
+    }
+}
+
+// the table in one workgroup, in LDS (nb <= kLdsBlocks)
+__global__ void __launch_bounds__(kT) k_rmq_table(int32_t* tmn, int32_t* tmx, int64_t nb, int32_t levels) {
+    __shared__ int32_t smn[kLdsBlocks], smx[kLdsBlocks];
     for (int64_t i = threadIdx.x; i < nb; i += blockDim.x) { smn[i] = tmn[i]; smx[i] = tmx[i]; }
     __syncthreads();
     constexpr int kPer = kLdsBlocks / kT;
@@ -385,39 +427,6 @@ __device__ void build_block_table(int32_t* tmn, int32_t* tmx, int64_t nb, int32_
     }
 }
 
-__device__ __forceinline__ void rmq_block_levels(const int32_t* tmin, const int32_t* tmax, int64_t n, int32_t* lmin,
-                                                 int32_t* lmax, int32_t* tmn, int32_t* tmx, int64_t nb) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    int32_t a = i < n ? tmin[i] : INT32_MAX, b = i < n ? tmax[i] : INT32_MIN;
-    for (int j = 1; j <= kInLev + 1; j++) {
-        const int o = 1 << (j - 1);
-        const int32_t da = __shfl_down(a, o), db = __shfl_down(b, o);
-        if (lane + o < 64) { a = min(a, da); b = max(b, db); }
-        if (j <= kInLev) {
-            if (i < n) { lmin[(int64_t)(j - 1) * n + i] = a; lmax[(int64_t)(j - 1) * n + i] = b; }
-        } else if (lane == 0 && (i >> 6) < nb) {
-            tmn[i >> 6] = a;
-            tmx[i >> 6] = b;
-        }
-    }
-}
-
-// per block: in-block levels and the block's min/max (level 0 of the block table)
-__global__ void __launch_bounds__(kT) k_rmq_blocks(const int32_t* tmin, const int32_t* tmax, int64_t n, int32_t* lmin,
-                                                   int32_t* lmax, int32_t* tmn, int32_t* tmx, int64_t nb) {
-    rmq_block_levels(tmin, tmax, n, lmin, lmax, tmn, tmx, nb);
-}
-
-// the block table in one workgroup, in LDS (nb <= kLdsBlocks).  A separate
-// launch: folded into k_rmq_blocks as "the last workgroup builds it", every
-// workgroup's device-scope release (an L2 write-back) cost more than the
-// launch (dense: 30 us against 5 + 10 us)
-__global__ void __launch_bounds__(kT) k_rmq_table(int32_t* tmn, int32_t* tmx, int64_t nb, int32_t levels) {
-    __shared__ int32_t smn[kLdsBlocks], smx[kLdsBlocks];
-    build_block_table(tmn, tmx, nb, levels, smn, smx);
-}
-
 // sparse table level j (j >= 1) over nb block values, levels stored nb apart
 __global__ void k_rmq_level(int32_t* tmn, int32_t* tmx, int64_t nb, int32_t j) {
     const int64_t half = int64_t(1) << (j - 1);
@@ -429,46 +438,52 @@ __global__ void k_rmq_level(int32_t* tmn, int32_t* tmx, int64_t nb, int32_t j) {
     }
 }
 
-struct Rmq {
-    const int32_t *t, *u, *lmin, *lmax, *tmn, *tmx;
-    int64_t n, nb;
-};
-
-// min/max over [a, b] inside one block
-__device__ __forceinline__ void in_block(const Rmq& R, int32_t a, int32_t b, int32_t& mn, int32_t& mx) {
+// min/max over [a, b] inside one block of a layer
+__device__ __forceinline__ void in_block(const RmqLayer& L, int32_t a, int32_t b, int32_t& mn, int32_t& mx) {
     const int j = floor_log2((uint32_t)(b - a + 1));
     if (j == 0) {
-        mn = R.t[a];
-        mx = R.u[a];
+        mn = L.t[a];
+        mx = L.u[a];
     } else if (j <= kInLev) {
-        const int64_t o = (int64_t)(j - 1) * R.n;
+        const int64_t o = (int64_t)(j - 1) * L.n;
         const int32_t c = b - (1 << j) + 1;
-        mn = min(R.lmin[o + a], R.lmin[o + c]);
-        mx = max(R.lmax[o + a], R.lmax[o + c]);
+        mn = min(L.lmin[o + a], L.lmin[o + c]);
+        mx = max(L.lmax[o + a], L.lmax[o + c]);
     } else {   // the whole block
-        mn = R.tmn[a >> 6];
-        mx = R.tmx[a >> 6];
+        mn = L.bmn[a >> 6];
+        mx = L.bmx[a >> 6];
+    }
+}
+
+// min/max over [l, r] of a layer; rest(a, b, mn, mx) answers a run of whole blocks
+template <class Rest>
+__device__ __forceinline__ void layer_minmax(const RmqLayer& L, int32_t l, int32_t r, int32_t& mn, int32_t& mx, Rest rest) {
+    const int32_t bl = l >> 6, br = r >> 6;
+    if (bl == br) {
+        in_block(L, l, r, mn, mx);
+        return;
+    }
+    int32_t m2, x2;
+    in_block(L, l, bl * 64 + 63, mn, mx);
+    in_block(L, br * 64, r, m2, x2);
+    mn = min(mn, m2);
+    mx = max(mx, x2);
+    if (br - bl > 1) {
+        rest(bl + 1, br - 1, m2, x2);
+        mn = min(mn, m2);
+        mx = max(mx, x2);
     }
 }
 
 __device__ __forceinline__ void range_minmax(const Rmq& R, int32_t l, int32_t r, int32_t& mn, int32_t& mx) {
-    const int32_t bl = l >> 6, br = r >> 6;
-    if (bl == br) {
-        in_block(R, l, r, mn, mx);
-        return;
-    }
-    int32_t m2, x2;
-    in_block(R, l, bl * 64 + 63, mn, mx);
-    in_block(R, br * 64, r, m2, x2);
-    mn = min(mn, m2);
-    mx = max(mx, x2);
-    if (br - bl > 1) {
-        const int32_t a = bl + 1, b = br - 1;
-        const int j = floor_log2((uint32_t)(b - a + 1));
-        const int64_t lev = (int64_t)j * R.nb;
-        mn = min(mn, min(R.tmn[lev + a], R.tmn[lev + b - (1 << j) + 1]));
-        mx = max(mx, max(R.tmx[lev + a], R.tmx[lev + b - (1 << j) + 1]));
-    }
+    layer_minmax(R.a, l, r, mn, mx, [&](int32_t a, int32_t b, int32_t& m, int32_t& x) {
+        layer_minmax(R.b, a, b, m, x, [&](int32_t c, int32_t d, int32_t& m3, int32_t& x3) {
+            const int j = floor_log2((uint32_t)(d - c + 1));
+            const int64_t lev = (int64_t)j * R.nb;
+            m3 = min(R.b.bmn[lev + c], R.b.bmn[lev + d - (1 << j) + 1]);
+            x3 = max(R.b.bmx[lev + c], R.b.bmx[lev + d - (1 << j) + 1]);
+        });
+    });
 }
 
 // Result keys leave a block through LDS with one reservation on *nout per
@@ -556,38 +571,55 @@ __global__ void k_bridges(const int2* f1, const uint32_t* q, int32_t qs, const i
 
 // ---- articulation points of the certificate ------------------------------------
 //
-// The test of Tarjan and Vishkin on the rooted spanning tree F (any spanning
-// tree will do, breadth-first included).  Tree edges are named by their child
-// c and grouped by a union-find: an edge of F' between two unrelated vertices
+// The test of Tarjan and Vishkin on the rooted spanning forest F of the graph
+// (any spanning forest will do).  Tree edges are named by their child
+// c and grouped by a union-find: an edge between two unrelated vertices
 // (neither in the other's subtree) joins their parent edges, and the parent
 // edge of c joins that of its parent p (p not a root) when c's subtree reaches
 // a vertex outside p's subtree.  The groups are the blocks; a vertex is an
 // articulation point iff the edges to its children do not all lie in the block
 // of its own parent edge -- for a root, iff they lie in at least two blocks.
-__device__ __forceinline__ uint32_t tv_find(uint32_t* g, uint32_t x) {
-    uint32_t d = g[x];
-    while (d != 0) {
-        const uint32_t p = x - d, dp = g[p];
-        if (dp == 0) return p;
-        g[x] = d + dp;
-        x = p - dp;
-        d = g[x];
-    }
-    return x;
+//
+// The edges come as they are, tree edges and copies among them: a tree edge
+// reaches only its own ends, which neither rule counts.  An edge whose ends are
+// named by edges of one group already adds nothing: both ends lie in one block
+// of the edges seen so far, and an edge inside a block leaves all blocks as
+// they are.  So a long list takes two rounds: the edges of F' (at most V - 1,
+// and with F 2-edge-connected wherever the graph is) through both rules, then
+// only the edges of the list that join different groups -- k_filter finds them
+// at the rate the list streams.  (Rows of 8V edges in place of F' in the first
+// round: 96 us in k_tv_range alone on the dense workload.)
+__device__ __forceinline__ void tv_unite(uint32_t* g, uint32_t a, uint32_t b) {
+    uf_unite<0>(g, 1, a, a - ld(g + a), b, b - ld(g + b));
 }
 
-__device__ __forceinline__ void tv_unite(uint32_t* g, uint32_t a, uint32_t b) {
-    for (;;) {
-        a = tv_find(g, a);
-        b = tv_find(g, b);
-        if (a == b) return;
-        if (a < b) { const uint32_t t = a; a = b; b = t; }
-        uint32_t expect = 0;
-        if (__hip_atomic_compare_exchange_strong(g + a, &expect, a - b, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT))
-            return;
-        a -= expect;
+// The edges of one round: list[dir * k] for k < *n, or all of edges[0..E) where
+// there is no list (or more than `room` came).
+struct EdgeSet {
+    const int2* edges;
+    int64_t E;
+    const int2* list;
+    int32_t dir;
+    const uint32_t* n;
+    uint32_t room;
+};
+
+template <class Fn>
+__device__ __forceinline__ void for_edges(const EdgeSet& S, int32_t V, Fn f) {
+    const bool listed = S.list && *S.n <= S.room;
+    const int64_t n = listed ? (int64_t)*S.n : S.E;
+    GRID_LOOP(k, n) {
+        const int2 e = listed ? S.list[S.dir * k] : S.edges[k];
+        if ((uint32_t)e.x < (uint32_t)V && (uint32_t)e.y < (uint32_t)V && e.x != e.y) f(e);
     }
+}
+
+// smallest and largest preorder number next to each vertex
+__global__ void __launch_bounds__(kT) k_tv_range(EdgeSet S, int32_t V, const int32_t* pre, int32_t* tmin, int32_t* tmax) {
+    for_edges(S, V, [&](int2 e) {
+        const int32_t px = pre[e.x], py = pre[e.y];
+        if (px >= 0 && py >= 0) range_touch(tmin, tmax, px, py);
+    });
 }
 
 __global__ void k_tv_init(int32_t V, uint32_t* g, int32_t* rmin, int32_t* rmax, int32_t* apf) {
@@ -616,17 +648,16 @@ __global__ void k_tv_tree(const int2* f1, const uint32_t* q, int32_t qs, const i
     }
 }
 
-// edge of F' between unrelated vertices: joins their parent edges
-__global__ void k_tv_cross(const int2* f2, int32_t dir, const uint32_t* cnt, const int32_t* pre, const int32_t* sub,
-                           uint32_t* g) {
-    const int64_t n2 = cnt[1];
-    GRID_LOOP(k, n2) {
-        const int2 e = f2[dir * k];
-        const int32_t px = pre[e.x], py = pre[e.y];
-        if (px < 0 || py < 0 || e.x == e.y) continue;
-        const bool related = (px <= py && py < px + sub[e.x]) || (py <= px && px < py + sub[e.y]);
-        if (!related) tv_unite(g, (uint32_t)e.x, (uint32_t)e.y);
-    }
+// edges between unrelated vertices join their parent edges
+__global__ void __launch_bounds__(kT) k_tv_cross(EdgeSet S, int32_t V, const int32_t* pre, const int32_t* sub, uint32_t* g) {
+    for_edges(S, V, [&](int2 e) {
+        const uint32_t x = (uint32_t)e.x, y = (uint32_t)e.y, gx = x - ld(g + x), gy = y - ld(g + y);
+        if (gx == gy) return;
+        const int32_t px = pre[x], py = pre[y];
+        if (px < 0 || py < 0) return;
+        const bool related = (px <= py && py < px + sub[x]) || (py <= px && px < py + sub[y]);
+        if (!related) uf_unite<0>(g, 1, x, gx, y, gy);
+    });
 }
 
 __global__ void k_tv_compress(uint32_t* g, int32_t V) {
@@ -761,10 +792,11 @@ __global__ void k_status(const uint32_t* cnt, const uint32_t* err, uint32_t* mis
 // directly, so that the counters and the keys leave in one copy.
 struct BridgeWs {
     int32_t *first, *cur, *flag, *tickets, *misc, *nxt, *posof, *tour_len, *tree_n, *tour_base, *vbase, *in_arc, *sub,
-        *pre, *tmin, *tmax, *lmin, *lmax, *tmn, *tmx;
+        *pre, *tmin, *tmax;
     uint64_t *st_tours, *st_flag, *keys, *link;
-    int64_t zero_words, nb;
-    int32_t levels;
+    int64_t zero_words;
+    Rmq R;
+    int32_t levels;                // of the range table
     int64_t words;
 };
 
@@ -796,13 +828,20 @@ static BridgeWs carve(int32_t* base, int32_t V) {
     w.pre = take(V);
     w.tmin = take(V);
     w.tmax = take(V);
-    w.lmin = take((int64_t)kInLev * V);
-    w.lmax = take((int64_t)kInLev * V);
-    w.nb = cdiv(V, kRB);
+    const int64_t nb = cdiv(V, kRB), ns = cdiv(nb, kRB);
     w.levels = 1;
-    while ((int64_t(1) << w.levels) <= w.nb) w.levels++;
-    w.tmn = take(w.levels * w.nb);
-    w.tmx = take(w.levels * w.nb);
+    while ((int64_t(1) << w.levels) <= ns) w.levels++;
+    auto layer = [&](int32_t* t, int32_t* u, int64_t n, int64_t block_words) {
+        RmqLayer L{t, u, nullptr, nullptr, nullptr, nullptr, n};
+        L.lmin = take(kInLev * n);
+        L.lmax = take(kInLev * n);
+        L.bmn = take(block_words);
+        L.bmx = take(block_words);
+        return L;
+    };
+    w.R.a = layer(w.tmin, w.tmax, V, nb);
+    w.R.b = layer(w.R.a.bmn, w.R.a.bmx, nb, w.levels * ns);
+    w.R.nb = ns;
     w.words = o;
     return w;
 }
@@ -847,8 +886,8 @@ static void launch_rank(const int2* f1, const uint32_t* cnt, const int32_t* firs
         hipLaunchKernelGGL(k_rank_mem, dim3((unsigned)resident), dim3(kT), 0, s, f1, cnt, first, nxt, q, qs, link);
 }
 
-static BridgeWs number_tree(const int2* f1, const int2* f2, int32_t dir, const uint32_t* cnt, const uint32_t* q,
-                            int32_t qs, int32_t V, int32_t* ws, hipStream_t s, Rmq* R) {
+static BridgeWs number_vertices(const int2* f1, const uint32_t* cnt, const uint32_t* q, int32_t qs, int32_t V, int32_t* ws,
+                                hipStream_t s) {
     const int64_t A = 2 * (int64_t)std::max(V - 1, 1);
     const BridgeWs W = carve(ws, V);
     hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(W.zero_words)), dim3(kT), 0, s, W.first, W.zero_words);
@@ -863,17 +902,28 @@ static BridgeWs number_tree(const int2* f1, const int2* f2, int32_t dir, const u
     hipLaunchKernelGGL(k_preorder, dim3(grid_for(V)), dim3(kT), 0, s, f1, q, qs, W.first, W.in_arc,
                        (const uint64_t*)W.link, W.tour_len, W.tour_base, W.flag, W.vbase, W.tree_n, V, W.pre, W.sub,
                        W.tmin, W.tmax);
-    hipLaunchKernelGGL(k_nontree, dim3(grid_for(V)), dim3(kT), 0, s, f2, dir, cnt, W.pre, W.tmin, W.tmax);
-    const int64_t rblocks = cdiv(W.nb * kRB, kT);
-    hipLaunchKernelGGL(k_rmq_blocks, dim3((unsigned)rblocks), dim3(kT), 0, s, W.tmin, W.tmax, (int64_t)V, W.lmin,
-                       W.lmax, W.tmn, W.tmx, W.nb);
-    if (W.nb <= kLdsBlocks) {
-        hipLaunchKernelGGL(k_rmq_table, dim3(1), dim3(kT), 0, s, W.tmn, W.tmx, W.nb, W.levels);
+    return W;
+}
+
+// the range tables over tmin / tmax as they are now
+static Rmq build_ranges(const BridgeWs& W, int32_t V, hipStream_t s) {
+    const Rmq& R = W.R;
+    hipLaunchKernelGGL(k_rmq_blocks, dim3((unsigned)cdiv(R.a.n, kT)), dim3(kT), 0, s, R.a);
+    hipLaunchKernelGGL(k_rmq_blocks, dim3((unsigned)cdiv(R.b.n, kT)), dim3(kT), 0, s, R.b);
+    if (R.nb > 1 && R.nb <= kLdsBlocks) {
+        hipLaunchKernelGGL(k_rmq_table, dim3(1), dim3(kT), 0, s, R.b.bmn, R.b.bmx, R.nb, W.levels);
     } else {
         for (int32_t j = 1; j < W.levels; j++)
-            hipLaunchKernelGGL(k_rmq_level, dim3(grid_for(W.nb)), dim3(kT), 0, s, W.tmn, W.tmx, W.nb, j);
+            hipLaunchKernelGGL(k_rmq_level, dim3(grid_for(R.nb)), dim3(kT), 0, s, R.b.bmn, R.b.bmx, R.nb, j);
     }
-    *R = Rmq{W.tmin, W.tmax, W.lmin, W.lmax, W.tmn, W.tmx, (int64_t)V, W.nb};
+    return R;
+}
+
+static BridgeWs number_tree(const int2* f1, const int2* f2, int32_t dir, const uint32_t* cnt, const uint32_t* q,
+                            int32_t qs, int32_t V, int32_t* ws, hipStream_t s, Rmq* R) {
+    const BridgeWs W = number_vertices(f1, cnt, q, qs, V, ws, s);
+    hipLaunchKernelGGL(k_nontree, dim3(grid_for(V)), dim3(kT), 0, s, f2, dir, cnt, W.pre, W.tmin, W.tmax);
+    *R = build_ranges(W, V, s);
     return W;
 }
 
@@ -890,20 +940,41 @@ int device_bridges_cert(const int2* f1, const int2* f2, int32_t dir, const uint3
     return BR_OK;
 }
 
-// Articulation points of a certificate held on the device (same arguments as
-// device_bridges_cert); F must be the spanning forest of the certificate.
-// Writes the vertex ids (as 64-bit keys, unordered) at *d_keys and their number
-// at *d_n, in the same status-block layout.  Scratch reused from the numbering:
-// cur (blocks), tour_len / tree_n (roots' min / max child block), posof (flags).
-int device_articulation_cert(const int2* f1, const int2* f2, int32_t dir, const uint32_t* cnt, const uint32_t* q,
-                             int32_t qs, int32_t V, int32_t* ws, uint64_t** d_keys, uint32_t** d_n, hipStream_t s) {
+// Articulation points of the edge list the plan's certificate was taken from;
+// F is its spanning forest.  Writes the vertex ids (as 64-bit keys, unordered)
+// at *d_keys and their number at *d_n, in the bridge step's status-block
+// layout.  Scratch reused from the numbering: cur (blocks), tour_len / tree_n
+// (roots' min / max child block), posof (flags), link (the second round's
+// edges).
+int device_articulation(const Plan& P, const DevBufs& B, const FusedBufs& F, int32_t* ws, uint64_t** d_keys,
+                        uint32_t** d_n, hipStream_t s) {
+    const int32_t V = P.V, qs = (int32_t)B.qs;
     const int64_t A = 2 * (int64_t)std::max(V - 1, 1);
-    Rmq R;
-    const BridgeWs W = number_tree(f1, f2, dir, cnt, q, qs, V, ws, s, &R);
+    const int2* f1 = B.cert + P.off[0];
+    const uint32_t* q = B.state;
+    const BridgeWs W = number_vertices(f1, B.cnt, q, qs, V, ws, s);
     uint32_t* g = reinterpret_cast<uint32_t*>(W.cur);
     hipLaunchKernelGGL(k_tv_init, dim3(grid_for(V)), dim3(kT), 0, s, V, g, W.tour_len, W.tree_n, W.posof);
-    hipLaunchKernelGGL(k_tv_tree, dim3(grid_for(V)), dim3(kT), 0, s, f1, q, qs, W.first, W.in_arc, W.pre, W.sub, R, V, A, g);
-    hipLaunchKernelGGL(k_tv_cross, dim3(grid_for(V)), dim3(kT), 0, s, f2, dir, cnt, W.pre, W.sub, g);
+    auto round = [&](const EdgeSet& S, int64_t edges) {
+        const dim3 grid(grid_for(std::max<int64_t>(edges, 1)));
+        hipLaunchKernelGGL(k_tv_range, grid, dim3(kT), 0, s, S, V, W.pre, W.tmin, W.tmax);
+        const Rmq R = build_ranges(W, V, s);
+        hipLaunchKernelGGL(k_tv_tree, dim3(grid_for(V)), dim3(kT), 0, s, f1, q, qs, W.first, W.in_arc, W.pre, W.sub, R, V, A, g);
+        hipLaunchKernelGGL(k_tv_cross, grid, dim3(kT), 0, s, S, V, W.pre, W.sub, g);
+    };
+    const bool two = P.code_per > 0;
+    if (!two) {
+        round(EdgeSet{B.edges, P.E, nullptr, 1, nullptr, 0}, P.E);
+    } else {
+        round(EdgeSet{B.edges, P.E, f1 + P.cap[0] - 1, -1, B.cnt + 1, (uint32_t)P.cap[0]}, V);
+        int2* list = reinterpret_cast<int2*>(W.link);
+        uint32_t* n = reinterpret_cast<uint32_t*>(W.tickets) + 3;
+        FusedBufs G = F;
+        G.ncode = n + 1;                       // cleared with the tickets
+        const uint32_t room = (uint32_t)A;     // the list-ranking words: one pair each
+        launch_list_rest(P, B, G, g, list, n, room, s);
+        round(EdgeSet{B.edges, P.E, list, 1, n, room}, V);
+    }
     hipLaunchKernelGGL(k_tv_compress, dim3(grid_for(V)), dim3(kT), 0, s, g, V);
     hipLaunchKernelGGL(k_tv_mark, dim3(grid_for(V)), dim3(kT), 0, s, f1, q, qs, W.first, W.in_arc, V, A, (const uint32_t*)g,
                        W.tour_len, W.tree_n, W.posof);

@@ -45,7 +45,7 @@ constexpr int kFilterWaves = kFilterBlock / 64;
 constexpr int kListCap = 128;          // edges a wavefront's list holds
 constexpr int kFilterLds = 160 * 1024;
 constexpr int kListBytes = kFilterWaves * kListCap * (int)sizeof(int2);
-constexpr int kTabBytes = kFilterLds - kListBytes;
+constexpr int kTabBytes = kFilterLds - kListBytes - 256;     // and the static LDS
 
 // row taken as the sel-th of a stage: the multiples of `mul`, or (div > 0) the
 // multiples of `mul` that are not multiples of mul * (div + 1)
@@ -118,6 +118,38 @@ __global__ void __launch_bounds__(256) k_flatten(uint32_t* q, int64_t qs, int32_
         base = __shfl(base, leader);
         const uint32_t c = base + lane_rank(m) + 1;
         if (root) rcode[x] = c <= 0xffffu ? c : 0u;
+    }
+}
+
+// The same for one union-find alone (its words q[x]); with names, every root's
+// code is written (0 without).
+__global__ void __launch_bounds__(256) k_flatten1(uint32_t* q, int32_t V, uint32_t* rcode, uint32_t* ncode, int32_t names) {
+    const int64_t n = ((int64_t)V + 63) & ~int64_t(63);
+    GRID_LOOP(x, n) {
+        bool root = false;
+        if (x < V) {
+            const uint32_t d = q[x];
+            root = d == 0;
+            uint32_t r = (uint32_t)x - d;
+            int k = 0;
+            if (!root)
+                for (uint32_t e = q[r]; e != 0; e = q[r]) {
+                    r -= e;
+                    if (++k % kFreeSteps == 0) q[x] = (uint32_t)x - r;
+                }
+            if (r != (uint32_t)x - d) q[x] = (uint32_t)x - r;
+        }
+        const uint64_t m = __ballot(root);
+        if (!m) continue;
+        uint32_t c = 0;
+        if (names) {
+            const int leader = __ffsll((unsigned long long)m) - 1;
+            uint32_t base = 0;
+            if (__lane_id() == leader) base = atomicAdd(ncode, (uint32_t)__popcll(m));
+            c = __shfl(base, leader) + lane_rank(m) + 1;
+            if (c > 0xffffu) c = 0;
+        }
+        if (root) rcode[x] = c;
     }
 }
 
@@ -215,15 +247,35 @@ __device__ __forceinline__ void offer_list(const DevBufs& B, int64_t cap, const 
     }
 }
 
+// lanes [0, n) append edges l[0..n) to out[]; past `room` they are only counted
+__device__ __forceinline__ void append_list(int2* out, uint32_t* nout, uint32_t room, const int2* l, uint32_t n) {
+    const uint32_t lane = __lane_id();
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(nout, n);
+    base = __shfl(base, 0);
+    if (lane < n && base + lane < room) out[base + lane] = l[lane];
+}
+
+// where k_filter's remaining edges go: the union-find (out null) or a list
+struct Sink {
+    int2* out;
+    uint32_t* nout;
+    uint32_t room;
+};
+
 typedef int edge2 __attribute__((ext_vector_type(4), aligned(8)));   // two edges, 8-byte aligned
 
-// Stage 3: all rows that are not multiples of div + 1.  A wavefront takes 128
+// Stage 3: all rows that are not multiples of div + 1 (div = 0: all rows).  A wavefront takes 128
 // edges (two per lane) at a time, kU such loads in flight; every wavefront
 // keeps its own list, so the stream has no barrier.
-template <int kPer, bool kSplit>
+template <int kPer, bool kSplit, bool kList>
 __global__ void __launch_bounds__(kFilterBlock) k_filter(DevBufs B, int64_t E, int32_t V, int64_t cap, uint32_t nsel,
-                                                         uint32_t div, const uint32_t* code, int32_t words) {
+                                                         uint32_t div, const uint32_t* code, int32_t words, Sink K) {
     constexpr int kU = 4;
+    auto drain = [&](const int2* l, uint32_t k) {
+        if constexpr (kList) append_list(K.out, K.nout, K.room, l, k);
+        else offer_list(B, cap, l, k);
+    };
     extern __shared__ __align__(16) uint32_t lds[];
     uint32_t* tab = lds;
     for (int32_t i = threadIdx.x; i < words / 4; i += kFilterBlock)
@@ -279,26 +331,42 @@ __global__ void __launch_bounds__(kFilterBlock) k_filter(DevBufs B, int64_t E, i
                     __builtin_amdgcn_wave_barrier();       // written by the wavefront's lanes, read back by them
                     if (n >= 64) {
                         n -= 64;
-                        offer_list(B, cap, wl + n, 64);
+                        drain(wl + n, 64);
                         __builtin_amdgcn_wave_barrier();
                     }
                 }
             }
         }
     }
-    if (n) offer_list(B, cap, wl, n);
+    if constexpr (kList) {
+        // what is left in the lists: one reservation per workgroup (one per
+        // wavefront, 4,096 on one address, took 30 us)
+        __shared__ uint32_t left[kFilterWaves + 1];
+        if (lane == 0) left[wave] = n;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t sum = 0;
+            for (int w = 0; w < kFilterWaves; w++) {
+                const uint32_t c = left[w];
+                left[w] = sum;
+                sum += c;
+            }
+            left[kFilterWaves] = sum ? atomicAdd(K.nout, sum) : 0u;
+        }
+        __syncthreads();
+        const uint32_t base = left[kFilterWaves] + left[wave];
+        if (lane < n && base + lane < K.room) K.out[base + lane] = wl[lane];
+    } else if (n) {
+        drain(wl, n);
+    }
 }
 
 template <int kPer>
 void launch_filter(const DevBufs& B, const Plan& P, uint32_t nsel, uint32_t div, const uint32_t* code, int grid,
-                   hipStream_t s) {
+                   const Sink& K, hipStream_t s) {
     const size_t lds = 4 * (size_t)P.code_words + kListBytes;
-    if (B.edges2 && B.split < P.E)
-        hipLaunchKernelGGL((k_filter<kPer, true>), dim3(grid), dim3(kFilterBlock), lds, s, B, P.E, P.V, P.cap[0], nsel, div,
-                           code, P.code_words);
-    else
-        hipLaunchKernelGGL((k_filter<kPer, false>), dim3(grid), dim3(kFilterBlock), lds, s, B, P.E, P.V, P.cap[0], nsel, div,
-                           code, P.code_words);
+    auto k = K.out ? &k_filter<kPer, false, true> : (B.edges2 && B.split < P.E ? &k_filter<kPer, true, false> : &k_filter<kPer, false, false>);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kFilterBlock), lds, s, B, P.E, P.V, P.cap[0], nsel, div, code, P.code_words, K);
 }
 
 // f(integral constant) for the codes per word
@@ -315,12 +383,42 @@ void with_per(int32_t per, Fn f) {
 
 template <int kPer>
 hipError_t raise_lds() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_filter<kPer, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kFilterLds);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_filter<kPer, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kFilterLds);
-    return e;
+    for (auto k : {&k_filter<kPer, false, false>, &k_filter<kPer, true, false>, &k_filter<kPer, false, true>}) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFilterLds - 256);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// codes for the largest components (where every root does not have one), then
+// the packed table; word 1 of a vertex's state (q[qs * x + 1]) leads to its root
+void launch_codes(const Plan& P, const uint32_t* q, int64_t qs, const FusedBufs& F, hipStream_t s, int* launches) {
+    if (P.code_per > 2) {
+        const int ncodes = (1 << (32 / P.code_per)) - 1;
+        hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPick), 0, s, q, qs, P.V, ncodes > 15 ? kPick : 256, ncodes, F.rcode);
+        ++*launches;
+    }
+    with_per(P.code_per, [&](auto per) {
+        hipLaunchKernelGGL(k_codes<decltype(per)::value>, dim3((unsigned)((P.code_words + 255) / 256)), dim3(256), 0, s, q, qs,
+                           P.V, (const uint32_t*)F.rcode, F.code, (int64_t)P.code_words);
+    });
+    ++*launches;
+}
+
+// stage 3 over every row that is not a multiple of P.s2 (every row at all with
+// a list as sink)
+void launch_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, const Sink& K, hipStream_t s) {
+    const int64_t nrows = (P.E + kRow - 1) / kRow;
+    const uint32_t nsel = (uint32_t)(K.out ? nrows : nrows - (nrows + P.s2 - 1) / P.s2);
+    const uint32_t div = K.out ? 0u : (uint32_t)(P.s2 - 1);
+    const int cus = g_cus > 0 ? g_cus : 256;
+    // a wavefront takes at least four loads' worth of the list; two
+    // workgroups share a CU where their tables allow it
+    const int64_t units = (int64_t)nsel * (kRow / 128);
+    const int per_cu = 4 * (int64_t)P.code_words + kListBytes <= kFilterLds / 2 ? 2 : 1;
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * per_cu, (units + 4 * kFilterWaves - 1) / (4 * kFilterWaves)));
+    with_per(P.code_per, [&](auto per) { launch_filter<decltype(per)::value>(B, P, nsel, div, F.code, grid, K, s); });
 }
 
 }  // namespace
@@ -339,7 +437,7 @@ void plan_fused(Plan& P) {
     P.code_words = 0;
     if (E > 16 * V && E >= (int64_t(1) << 19))
         for (int per : {2, 4, 8, 16, 32})
-            if (4 * ((V + per - 1) / per) <= kTabBytes - 16) {
+            if (4 * ((V + per - 1) / per) <= kTabBytes) {
                 P.code_per = per;
                 P.code_words = (int32_t)((((V + per - 1) / per) + 3) & ~int64_t(3));
                 break;
@@ -361,17 +459,18 @@ void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int
                        dim3(256), 0, s, reinterpret_cast<uint4*>(base), n16, off, cap, cap0);
 }
 
-// Stage 3 with the table at F.code: every row that is not a multiple of P.s2.
 void launch_filter_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s) {
-    const int64_t nrows = (P.E + kRow - 1) / kRow;
-    const uint32_t nsel = (uint32_t)(nrows - (nrows + P.s2 - 1) / P.s2), div = (uint32_t)(P.s2 - 1);
-    const int cus = g_cus > 0 ? g_cus : 256;
-    // a wavefront takes at least four loads' worth of the list; two
-    // workgroups share a CU where their tables allow it
-    const int64_t units = (int64_t)nsel * (kRow / 128);
-    const int per_cu = 4 * (int64_t)P.code_words + kListBytes <= kFilterLds / 2 ? 2 : 1;
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * per_cu, (units + 4 * kFilterWaves - 1) / (4 * kFilterWaves)));
-    with_per(P.code_per, [&](auto per) { launch_filter<decltype(per)::value>(B, P, nsel, div, F.code, grid, s); });
+    launch_rest(P, B, F, Sink{}, s);
+}
+
+int launch_list_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, uint32_t* g, int2* out, uint32_t* nout,
+                     uint32_t room, hipStream_t s) {
+    int launches = 2;
+    hipLaunchKernelGGL(k_flatten1, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(((int64_t)P.V + 255) / 256, 16384))),
+                       dim3(256), 0, s, g, P.V, F.rcode, F.ncode, P.code_per == 2 ? 1 : 0);
+    launch_codes(P, g - 1, 1, F, s, &launches);      // g's word is read as word 1
+    launch_rest(P, B, F, Sink{out, nout, room}, s);
+    return launches;
 }
 
 int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s) {
@@ -406,20 +505,9 @@ int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_
             rows(nsel, 1, div, 4 * cus);
             return launches;
         }
-        if (P.code_per > 2) {
-            const int ncodes = (1 << (32 / P.code_per)) - 1;
-            hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPick), 0, s, (const uint32_t*)B.state, B.qs, P.V,
-                               ncodes > 15 ? kPick : 256, ncodes, F.rcode);
-            launches++;
-        }
-        const dim3 wgrid((unsigned)((P.code_words + 255) / 256));
-        auto codes = [&](auto per) {
-            hipLaunchKernelGGL(k_codes<decltype(per)::value>, wgrid, dim3(256), 0, s, (const uint32_t*)B.state, B.qs, P.V,
-                               (const uint32_t*)F.rcode, F.code, (int64_t)P.code_words);
-        };
-        with_per(P.code_per, codes);
+        launch_codes(P, B.state, B.qs, F, s, &launches);
         launch_filter_rest(P, B, F, s);
-        launches += 2;
+        launches++;
     }
     return launches;
 }

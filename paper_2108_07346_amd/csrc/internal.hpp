@@ -244,6 +244,12 @@ int fused_prepare();               // once per process: the kernels' LDS limit
 void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int64_t cap0, hipStream_t s);
 int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);   // kernels enqueued
 void launch_filter_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);
+// The plan's edge list against the components of the union-find g (words
+// g[x], in place compressed): edges inside one named
+// component are dropped, the others appended to out[0..room) and counted in
+// *nout (past the room only counted; *nout and *F.ncode zero at launch).
+int launch_list_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, uint32_t* g, int2* out, uint32_t* nout,
+                     uint32_t room, hipStream_t s);
 struct Contract;
 int lds_cert_prepare();            // once per process: the kernel's LDS limit
 // mode >= 0: the final step too where the list is offered whole (arguments as launch_contract)
@@ -306,13 +312,11 @@ void device_scan1(int32_t* a, int64_t n, uint64_t* status, uint32_t* ticket, hip
 int64_t scan_first_words(int64_t E, int32_t V);
 int scan_first_certificate(const int2* edges, int64_t E, int32_t V, char* ws, hipStream_t s, uint32_t* h_small,
                            int2* h_f1, int2* h_f2, uint32_t* n1, uint32_t* n2, int* levels1, int* levels2);
-int scan_first_device(const int2* edges, int64_t E, int32_t V, char* ws, hipStream_t s, uint32_t* h_small, int* levels1,
-                      int* levels2, int2** d_f1, int2** d_f2, uint32_t** d_cnt, uint32_t** d_err, uint32_t** d_roots);
-// Articulation points of a certificate on the device (F spanning forest, roots
-// flagged 0 in q[qs * v]); ids as 64-bit keys at *d_keys, their number at *d_n
-// (the bridge step's status-block layout).
-int device_articulation_cert(const int2* f1, const int2* f2, int32_t dir, const uint32_t* cnt, const uint32_t* q,
-                             int32_t qs, int32_t V, int32_t* ws, uint64_t** d_keys, uint32_t** d_n, hipStream_t s);
+// Articulation points of the plan's edge list, after run_certificate with the
+// one-pass plan (F at node 0, roots flagged 0 in B.state); ids as 64-bit keys at
+// *d_keys, their number at *d_n (the bridge step's status-block layout).
+int device_articulation(const Plan& P, const DevBufs& B, const FusedBufs& F, int32_t* ws, uint64_t** d_keys,
+                        uint32_t** d_n, hipStream_t s);
 // copies |F|, |F'| (cnt[0..1]) and *err into the 256-byte status block whose
 // word 1 is the key count d_n of a bridge step (the keys follow the block)
 void launch_bridge_status(const uint32_t* cnt, const uint32_t* err, uint32_t* d_n, hipStream_t s);
@@ -370,6 +374,7 @@ struct br_ctx {
     size_t keys_hint = 0;          // bridges found by the previous call (first copy size)
     int final_step = 1;            // 0: host search (Algorithm 1), 1: device bridge step
     int32_t* bws = nullptr;        // device bridge-step scratch inside the workspace
+    br::FusedBufs fused;           // the one-pass certificate's table buffers inside the workspace
     br::Contract contract;         // contracted final step's scratch inside the workspace
     br_profile prof{};
     hipEvent_t ev[8] = {};

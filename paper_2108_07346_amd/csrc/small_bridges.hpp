@@ -236,10 +236,9 @@ __device__ __forceinline__ void small_bridges(SmallLds<kMaxV, kST>& L, uint32_t 
         if (e.x >= V || e.y >= V) continue;
         const uint32_t px = L.pre[e.x], py = L.pre[e.y];
         if (px >= nslots || py >= nslots) continue;
-        atomicMin(&lo[px], py);
-        atomicMax(&hi[px], py);
-        atomicMin(&lo[py], px);
-        atomicMax(&hi[py], px);
+        // a vertex's range holds its own number: only these two ends can move
+        atomicMax(&hi[min(px, py)], max(px, py));
+        atomicMin(&lo[max(px, py)], min(px, py));
     }
     __syncthreads();
     // ---- min / max trees over preorder numbers (leaves at [n, 2n))
