@@ -582,6 +582,8 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
     uint32_t n1 = 0, n2 = 0, err = 0;
     std::chrono::steady_clock::time_point t1, t2;
     c->keys.clear();
+    const uint64_t* sorted = nullptr;
+    int64_t n_sorted = 0;
     if (mode == 1) {
         // final step on the device: only the bridges come back
         uint32_t* hc = fin.h_status;
@@ -625,7 +627,12 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
         if (err & 1u) return fail(BR_ERANGE, "br_bridges_find: an edge has a vertex id outside [0, %d)", V);
         if (err != 0 || (int64_t)n1 + n2 > cap0)
             return fail(BR_EINTERNAL, "br_bridges_find: certificate region overflow");
-        c->keys.assign(hk, hk + nk);
+        if (!solved && hc[7]) {
+            sorted = hk;                   // in order already: written out from where they are
+            n_sorted = nk;
+        } else {
+            c->keys.assign(hk, hk + nk);
+        }
         t2 = std::chrono::steady_clock::now();
     } else {
         // node 0's whole region plus its counters and the error word
@@ -653,9 +660,13 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
         certificate_bridges(hx, n1, hx + cap0 - n2, n2, V, c->dfs, c->keys);
         t2 = std::chrono::steady_clock::now();
     }
-    canonical_sort(c->keys);
+    if (!sorted) {
+        canonical_sort(c->keys);
+        sorted = c->keys.data();
+        n_sorted = (int64_t)c->keys.size();
+    }
     auto t3 = std::chrono::steady_clock::now();
-    const int64_t nb = (int64_t)c->keys.size();
+    const int64_t nb = n_sorted;
     *n_bridges = nb;
     if (c->profiling) {
         c->prof.ms_phase0 = ev_ms(c, 1, 2);
@@ -684,8 +695,8 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
     c->prof.ms_total = std::chrono::duration<double, std::milli>(t3 - t0).count();
     if (nb > cap) return fail(BR_ECAP, "br_bridges_find: %lld bridges, capacity %lld", (long long)nb, (long long)cap);
     for (int64_t i = 0; i < nb; i++) {
-        h_bridges[2 * i] = (int32_t)(c->keys[i] >> 32);
-        h_bridges[2 * i + 1] = (int32_t)(c->keys[i] & 0xffffffffu);
+        h_bridges[2 * i] = (int32_t)(sorted[i] >> 32);
+        h_bridges[2 * i + 1] = (int32_t)(sorted[i] & 0xffffffffu);
     }
     return BR_OK;
 }
@@ -716,6 +727,7 @@ static int classes_common(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t 
     rc = run_certificate(c, d_edges, E, nullptr, 0, V, M, s, P, B, mode == 1, nullptr, &fin);
     if (rc) return rc;
     std::vector<uint64_t>& tkeys = c->keys;
+    bool tree_sorted = false;
     tkeys.clear();
     if (mode == 1) {
         // bridges and classes on the device: the status block, the labels and
@@ -756,6 +768,7 @@ static int classes_common(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t 
                 tkeys.assign(ht, ht + nt);
             } else {
                 tkeys.resize(nt);
+                tree_sorted = hc[7] != 0;
                 if (nt) {
                     BR_HIP(hipMemcpyAsync(tkeys.data(), d_tkeys, 8 * (size_t)nt, hipMemcpyDeviceToHost, s));
                     BR_HIP(hipStreamSynchronize(s));
@@ -809,7 +822,7 @@ static int classes_common(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t 
             }
     }
     if (!h_tree) return BR_OK;
-    canonical_sort(tkeys);
+    if (!tree_sorted) canonical_sort(tkeys);
     const int64_t nt = (int64_t)tkeys.size();
     *n_tree = nt;
     if (nt > cap) return fail(BR_ECAP, "%s: %lld tree edges, capacity %lld", who, (long long)nt, (long long)cap);
@@ -892,9 +905,9 @@ int br_articulation_points(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t
         }
         c->keys_hint = nk;
         t1 = std::chrono::steady_clock::now();
-        aps.resize(nk);
-        for (uint32_t i = 0; i < nk; i++) aps[i] = (int32_t)hk[i];
-        std::sort(aps.begin(), aps.end());
+        c->keys.assign(hk, hk + nk);
+        canonical_sort(c->keys);
+        aps.assign(c->keys.begin(), c->keys.end());
     } else {
         // Algorithm 1's search (vertex test) on the host over the copied
         // scan-first certificate

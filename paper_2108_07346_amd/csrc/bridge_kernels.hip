@@ -569,6 +569,47 @@ __global__ void k_bridges(const int2* f1, const uint32_t* q, int32_t qs, const i
     out_end(L, out, nout);
 }
 
+// ---- canonical order of many keys ------------------------------------------------
+//
+// Keys (u << 32 | v, u < v) by u: a count per u, one scan, a scatter; then each
+// u's few keys by v.  Few keys (or a u with more than kOrderRun of them) are left
+// to the host's sort, and the flag *done says so: 260,000 keys took it 570 us.
+constexpr uint32_t kOrderMin = 8192;
+constexpr uint32_t kOrderRun = 64;
+
+__global__ void __launch_bounds__(kT) k_order_count(const uint64_t* keys, const uint32_t* nkeys, uint32_t* cnt, uint32_t* pos) {
+    const int64_t n = *nkeys;
+    if (n < kOrderMin) return;
+    GRID_LOOP(i, n) pos[i] = atomicAdd(&cnt[keys[i] >> 32], 1u);
+}
+
+// (cnt now the exclusive prefix sums)
+__global__ void __launch_bounds__(kT) k_order_place(const uint64_t* keys, const uint32_t* nkeys, const uint32_t* cnt,
+                                                    const uint32_t* pos, uint64_t* out, uint32_t* done) {
+    const int64_t n = *nkeys;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *done = n >= kOrderMin;
+    GRID_LOOP(i, n) out[n < kOrderMin ? i : (int64_t)(cnt[keys[i] >> 32] + pos[i])] = keys[i];
+}
+
+__global__ void __launch_bounds__(kT) k_order_runs(const uint32_t* nkeys, const uint32_t* cnt, int32_t V, uint64_t* out,
+                                                   uint32_t* done) {
+    if (*nkeys < kOrderMin) return;
+    GRID_LOOP(u, (int64_t)V) {
+        const uint32_t a = cnt[u], b = cnt[u + 1];
+        if (b - a < 2) continue;
+        if (b - a > kOrderRun) {
+            *done = 0;
+            continue;
+        }
+        for (uint32_t i = a + 1; i < b; i++) {
+            const uint64_t k = out[i];
+            uint32_t j = i;
+            for (; j > a && out[j - 1] > k; j--) out[j] = out[j - 1];
+            out[j] = k;
+        }
+    }
+}
+
 // ---- articulation points of the certificate ------------------------------------
 //
 // The test of Tarjan and Vishkin on the rooted spanning forest F of the graph
@@ -792,8 +833,8 @@ __global__ void k_status(const uint32_t* cnt, const uint32_t* err, uint32_t* mis
 // directly, so that the counters and the keys leave in one copy.
 struct BridgeWs {
     int32_t *first, *cur, *flag, *tickets, *misc, *nxt, *posof, *tour_len, *tree_n, *tour_base, *vbase, *in_arc, *sub,
-        *pre, *tmin, *tmax;
-    uint64_t *st_tours, *st_flag, *keys, *link;
+        *pre, *tmin, *tmax, *ord;
+    uint64_t *st_tours, *st_flag, *st_ord, *keys, *link;
     int64_t zero_words;
     Rmq R;
     int32_t levels;                // of the range table
@@ -802,6 +843,10 @@ struct BridgeWs {
 
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The keys are put in order on the device where there can be many of them: a
+// count per vertex and its scan cost about 50 us at 10^6 vertices.
+static bool order_on_device(int32_t V) { return V >= (1 << 17); }
+
 static BridgeWs carve(int32_t* base, int32_t V) {
     const int64_t A = 2 * (int64_t)std::max(V - 1, 1);
     BridgeWs w{};
@@ -809,7 +854,10 @@ static BridgeWs carve(int32_t* base, int32_t V) {
     auto take = [&](int64_t n) { int32_t* p = base ? base + o : nullptr; o += (n + 63) & ~int64_t(63); return p; };
     w.first = take(V + 2);
     w.flag = take(A + 1);
-    w.tickets = take(64);   // [1] tour scan ticket, [2] flag scan ticket
+    w.tickets = take(64);   // [1] tour scan ticket, [2] flag scan ticket, [5] key order scan ticket
+    const bool order = order_on_device(V);
+    w.ord = order ? take(V + 2) : nullptr;
+    w.st_ord = order ? reinterpret_cast<uint64_t*>(take(2 * cdiv(V + 1, kSB))) : nullptr;
     w.st_tours = reinterpret_cast<uint64_t*>(take(2 * cdiv(V, kSB)));
     w.st_flag = reinterpret_cast<uint64_t*>(take(2 * cdiv(A + 1, kSB)));
     w.in_arc = take(V);
@@ -858,6 +906,19 @@ void device_scan1(int32_t* a, int64_t n, uint64_t* status, uint32_t* ticket, hip
 // its tree of F iff q[qs*v] == 0.  Writes up to V keys at *d_keys and their
 // number at *d_n; *d_n sits 4 bytes into a 256-byte status block that the keys
 // follow directly.
+// The keys at `keys` (*n of them) in canonical order at `out`, status word 7 set
+// if that is done (else the host sorts them); pos: V words.
+static void order_keys(const BridgeWs& W, int32_t V, const uint64_t* keys, const uint32_t* n, uint64_t* out, uint32_t* pos,
+                       hipStream_t s) {
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(W.ord);
+    uint32_t* done = reinterpret_cast<uint32_t*>(W.misc) + 7;
+    hipLaunchKernelGGL(k_order_count, dim3(std::min(grid_for(V), 2048)), dim3(kT), 0, s, keys, n, cnt, pos);
+    device_scan1(W.ord, (int64_t)V + 1, W.st_ord, reinterpret_cast<uint32_t*>(W.tickets) + 5, s);
+    hipLaunchKernelGGL(k_order_place, dim3(std::min(grid_for(V), 2048)), dim3(kT), 0, s, keys, n, (const uint32_t*)cnt,
+                       (const uint32_t*)pos, out, done);
+    hipLaunchKernelGGL(k_order_runs, dim3(grid_for(V)), dim3(kT), 0, s, n, (const uint32_t*)cnt, V, out, done);
+}
+
 // The part shared by the bridge and articulation-point tests: adjacency of F,
 // Euler tours ranked, preorder numbers, subtree sizes, min/max preorder numbers
 // reached through F' and their range tables.
@@ -932,9 +993,12 @@ int device_bridges_cert(const int2* f1, const int2* f2, int32_t dir, const uint3
     const int64_t A = 2 * (int64_t)std::max(V - 1, 1);
     Rmq R;
     const BridgeWs W = number_tree(f1, f2, dir, cnt, q, qs, V, ws, s, &R);
+    // the list-ranking words are free once the tree is numbered: room for V - 1 keys
+    uint64_t* keys = W.ord ? W.link : W.keys;
+    uint32_t* n = reinterpret_cast<uint32_t*>(W.misc + 1);
     hipLaunchKernelGGL(k_bridges, dim3(std::min(grid_for(V), kOutBlocks)), dim3(kT), 0, s, f1, q, qs, W.first,
-                       W.in_arc, W.pre, W.sub, R, V, A, W.keys, reinterpret_cast<uint32_t*>(W.misc + 1), cnt, err,
-                       reinterpret_cast<uint32_t*>(W.misc));
+                       W.in_arc, W.pre, W.sub, R, V, A, keys, n, cnt, err, reinterpret_cast<uint32_t*>(W.misc));
+    if (W.ord) order_keys(W, V, keys, n, W.keys, reinterpret_cast<uint32_t*>(W.cur), s);
     *d_keys = W.keys;
     *d_n = reinterpret_cast<uint32_t*>(W.misc + 1);
     return BR_OK;
@@ -1025,6 +1089,12 @@ int device_bridge_tree(const Plan& P, const DevBufs& B, int32_t* ws, int32_t** d
                        B.cnt, (const int32_t*)*d_label, tkeys, *d_n + 4);
     launch_bridge_status(B.cnt, B.err, *d_n, s);
     *d_tkeys = tkeys;
+    if (W.ord) {
+        // (the arc lists are free as well)
+        uint64_t* sorted = reinterpret_cast<uint64_t*>(W.nxt);
+        order_keys(W, P.V, tkeys, *d_n + 4, sorted, reinterpret_cast<uint32_t*>(W.posof), s);
+        *d_tkeys = sorted;
+    }
     return BR_OK;
 }
 

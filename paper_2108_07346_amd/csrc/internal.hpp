@@ -329,7 +329,8 @@ int device_classes(const Plan& P, const DevBufs& B, int32_t* ws, int32_t** d_lab
 // their number in status word 5, (*d_n)[4]) at *d_tkeys
 int device_bridge_tree(const Plan& P, const DevBufs& B, int32_t* ws, int32_t** d_label, uint32_t** d_n,
                        uint64_t** d_tkeys, hipStream_t s);
-// also fills the status block before the keys (|F|, |F'|, *err or 0)
+// also fills the status block before the keys (|F|, |F'|, *err or 0; word 7: 1 if
+// the keys are already in canonical order, in the bridge tree's case the tree's)
 int device_bridges_cert(const int2* f1, const int2* f2, int32_t dir, const uint32_t* cnt, const uint32_t* q, int32_t qs,
                         int32_t V, const uint32_t* err, int32_t* ws, uint64_t** d_keys, uint32_t** d_n, hipStream_t s);
 
