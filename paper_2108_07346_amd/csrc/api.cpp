@@ -35,7 +35,7 @@ int g_max_lds = 64 * 1024;
 // BR_SOLO (1 on, 0 off, unset: by size) and BR_SOLO_TOP (merge levels inside
 // the one-workgroup-per-node kernel) override the plan's choice
 static int env_int(const char* name, int dflt) {
-    const char* s = getenv(name);
+    const char* s = *name ? getenv(name) : nullptr;
     return s && *s ? atoi(s) : dflt;
 }
 
@@ -88,6 +88,7 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
         }
         P.fused = true;
         P.qs = (int64_t)V * 32 <= (int64_t(128) << 20) ? 8 : 2;
+        P.table = knob("", "table", 1) != 0;
         plan_fused(P);
         // on a dense list nearly every edge of F lies inside a component of F'
         P.contract = V <= 4096 || E >= 6 * (int64_t)V;
@@ -555,8 +556,10 @@ int br_cert_merge(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_b,
     return ctx_end(c, s);
 }
 
-int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t M, int32_t* h_bridges,
-                    int64_t cap, int64_t* n_bridges, void* stream) {
+}  // extern "C"
+
+int br::bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t M, int32_t* h_bridges, int64_t cap,
+                     int64_t* n_bridges, void* stream, const TuneEntry* plan_knobs) {
     if (V > kFinalStepMaxV) return fail(BR_EINVAL, "V = %d above the final step's limit 2^29", V);
     if (!c || !n_bridges || (!h_bridges && cap > 0)) return fail(BR_EINVAL, "br_bridges_find: null argument");
     int rc = check_common(d_edges, E, V);
@@ -576,7 +579,7 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
     rc = ensure_pinned(c, std::max<size_t>(64 << 10, 256 + 8 * (size_t)V));
     if (rc) return rc;
     FinalReq fin{0, static_cast<uint32_t*>(c->pinned), static_cast<char*>(c->pinned) + 256, nullptr, false};
-    rc = run_certificate(c, d_edges, E, nullptr, 0, V, M, s, P, B, mode == 1, nullptr, &fin);
+    rc = run_certificate(c, d_edges, E, nullptr, 0, V, M, s, P, B, mode == 1, plan_knobs, &fin);
     if (rc) return rc;
     const int64_t cap0 = P.cap[0];
     uint32_t n1 = 0, n2 = 0, err = 0;
@@ -699,6 +702,13 @@ int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int
         h_bridges[2 * i + 1] = (int32_t)(sorted[i] & 0xffffffffu);
     }
     return BR_OK;
+}
+
+extern "C" {
+
+int br_bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t M, int32_t* h_bridges,
+                    int64_t cap, int64_t* n_bridges, void* stream) {
+    return bridges_find(c, d_edges, E, V, M, h_bridges, cap, n_bridges, stream, nullptr);
 }
 
 // 2-edge-connected classes, and with h_tree the bridge tree's edges too

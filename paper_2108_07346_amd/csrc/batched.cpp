@@ -73,15 +73,6 @@ struct BatchPlan {
     const void* graph_edges = nullptr;
     int graph_mode = -1;
     int blocks = 0;
-    // big class, final step on the device: the node-0 certificates as one
-    // certificate of their disjoint union and one bridge step over it
-    int2 *d_f1u = nullptr, *d_f2u = nullptr;
-    uint32_t* d_cntu = nullptr;
-    int64_t* d_uoff = nullptr;
-    int32_t* d_bws = nullptr;
-    uint64_t* d_ukeys = nullptr;     // set when the step is enqueued
-    uint32_t* d_un = nullptr;        // key count (status word 1; the status block precedes the keys)
-    uint32_t* h_ustat = nullptr;     // pinned: status block + keys
     int32_t max_v = 0;
     bool owns = true;                // dmem / hmem allocated for this plan (else borrowed arenas)
     size_t dbytes = 0;
@@ -118,6 +109,10 @@ struct BatchState {
         size_t arena_h_cap = 0;
     } arenas[2];
     std::unique_ptr<BatchPlan> transient[2];
+    // graphs past the small kernel's V as one disjoint union: its edges and the
+    // table that describes it (device, pinned host); grown, never shrunk
+    void *union_d = nullptr, *union_h = nullptr;
+    size_t union_d_cap = 0, union_h_cap = 0;
 };
 
 BatchState* state_of(br_ctx* c) {
@@ -223,19 +218,10 @@ int build_plan(BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, i
     const size_t o_cert = o; o = a256(o + 8 * (size_t)std::max<int64_t>(P.cert_pairs, 1));
     const size_t o_root = o; o = a256(o + 4 * (size_t)std::max<int64_t>(P.vtot, 1));
     const size_t o_sb = o; if (!big) o = a256(o + 4 * (size_t)(P.sb_hdr + P.sb_keys));
-    size_t o_f1u = o, o_f2u = o, o_cntu = o, o_uoff = o, o_bws = o;
-    if (big && S) {
-        o_f1u = o; o = a256(o + 8 * (size_t)P.vtot);
-        o_f2u = o; o = a256(o + 8 * (size_t)P.vtot);
-        o_cntu = o; o = a256(o + 8);
-        o_uoff = o; o = a256(o + 8 * 2 * (size_t)S);
-        o_bws = o; o = a256(o + 4 * (size_t)device_bridges_words((int32_t)P.vtot));
-    }
     // pinned host staging: node-0 regions, node-0 counters, error word, keys;
     // then room for the metadata's one upload
     const size_t h_keys = a256(8 * (size_t)std::max<int64_t>(P.area0, 1)) + a256(8 * (size_t)std::max(S, 1)) + 256;
-    const size_t h_meta = h_keys + (big ? a256(256 + 8 * (size_t)std::max<int64_t>(P.vtot, 1))
-                                        : a256(4 * (size_t)(P.sb_hdr + P.sb_keys)));
+    const size_t h_meta = h_keys + (big ? 0 : a256(4 * (size_t)(P.sb_hdr + P.sb_keys)));
     const size_t hbytes = h_meta + a256(meta_bytes);
     if (arena) {
         // a plan for one call: the batch state's arenas (grown when too small)
@@ -298,13 +284,6 @@ int build_plan(BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, i
     }
     P.d_sb = reinterpret_cast<uint32_t*>(d + o_sb);
     P.d_lists = reinterpret_cast<int32_t*>(d + o_lists);
-    if (big && S) {
-        P.d_f1u = reinterpret_cast<int2*>(d + o_f1u);
-        P.d_f2u = reinterpret_cast<int2*>(d + o_f2u);
-        P.d_cntu = reinterpret_cast<uint32_t*>(d + o_cntu);
-        P.d_uoff = reinterpret_cast<int64_t*>(d + o_uoff);
-        P.d_bws = reinterpret_cast<int32_t*>(d + o_bws);
-    }
     P.cus = std::max(1, cus);
     uint32_t* clr = reinterpret_cast<uint32_t*>(d + o_clear);
     P.dev.eoff = reinterpret_cast<const int64_t*>(d + o_eoff);
@@ -328,7 +307,6 @@ int build_plan(BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, i
     P.h_err = P.h_cnt0 + 2 * (size_t)std::max(S, 1);
     P.h_sb = reinterpret_cast<uint32_t*>(h + a256(8 * (size_t)std::max<int64_t>(P.area0, 1)) +
                                          a256(8 * (size_t)std::max(S, 1)) + 256);
-    P.h_ustat = P.h_sb;                  // big class: the same room holds the status block and the keys
     // the big class fills one workgroup per CU (its LDS)
     P.blocks = std::max(1, big ? cus : cus * bpc);
     return BR_OK;
@@ -343,16 +321,6 @@ int enqueue(BatchPlan& P, const int32_t* d_edges, hipStream_t s, int mode, int p
         launch_fill_u32(P.dev.ncnt, (int64_t)P.clear_words, 0u, s);
         BR_HIP(hipGetLastError());
         if (P.dev.n_items) launch_batched(P.dev, P.blocks, s, P.big);
-        BR_HIP(hipGetLastError());
-        return BR_OK;
-    }
-    if (mode == 1 && P.big && !P.small.empty()) {
-        const int32_t S = (int32_t)P.small.size();
-        launch_union_certificate(P.dev, S, P.d_uoff, P.d_f1u, P.d_f2u, P.d_cntu, s);
-        BR_HIP(hipGetLastError());
-        int rc = device_bridges_cert(P.d_f1u, P.d_f2u, 1, P.d_cntu, P.dev.rootw, 1, (int32_t)P.vtot, P.dev.err, P.d_bws,
-                                     &P.d_ukeys, &P.d_un, s);
-        if (rc) return rc;
         BR_HIP(hipGetLastError());
         return BR_OK;
     }
@@ -374,14 +342,6 @@ int enqueue(BatchPlan& P, const int32_t* d_edges, hipStream_t s, int mode, int p
 // bridges), their counters and the error word to the host
 int copy_back(BatchPlan& P, hipStream_t s, int mode) {
     const int32_t S = (int32_t)P.small.size();
-    if (mode == 1 && P.big) {
-        if (S) {
-            const size_t guess = std::min<size_t>(std::max<size_t>(P.keys_hint, 1024), (size_t)std::max<int64_t>(P.vtot, 1));
-            BR_HIP(hipMemcpyAsync(P.h_ustat, P.d_un - 1, 256 + 8 * guess, hipMemcpyDeviceToHost, s));
-        }
-        BR_HIP(hipMemcpyAsync(P.h_err, P.dev.err, 4, hipMemcpyDeviceToHost, s));
-        return BR_OK;
-    }
     if (mode == 1) {
         if (S) {
             // header, per-graph table and the first keys in one copy
@@ -476,7 +436,7 @@ size_t batched_device_bytes(br_ctx* c) {
     for (auto& a : st->arenas) n += a.arena_d_cap;
     for (auto& P : st->plans)
         if (P->owns) n += P->dbytes;
-    return n;
+    return n + st->union_d_cap;
 }
 
 void batched_release(br_ctx* c) {
@@ -489,6 +449,8 @@ void batched_release(br_ctx* c) {
         if (a.arena_d) (void)hipFree(a.arena_d);
         if (a.arena_h) (void)hipHostFree(a.arena_h);
     }
+    if (st->union_d) (void)hipFree(st->union_d);
+    if (st->union_h) (void)hipHostFree(st->union_h);
     if (st->e0) (void)hipEventDestroy(st->e0);
     if (st->e1) (void)hipEventDestroy(st->e1);
     if (st->k0) (void)hipEventDestroy(st->k0);
@@ -503,38 +465,11 @@ void batched_release(br_ctx* c) {
     c->batched = nullptr;
 }
 
-// Bridges of every graph of a big-class plan after its launches completed:
-// from the bridge step over the union of their certificates (mode 1) or from
-// Algorithm 1 per graph on the host (mode 0); out[k] = pairs of graph small[k].
-static int gather_big(BatchState& st, BatchPlan& P, int mode, std::vector<std::vector<int32_t>>& out) {
+// Bridges of every graph of a big-class plan after its launches completed, by
+// Algorithm 1 per graph on the host; out[k] = pairs of graph small[k].
+static int gather_big(BatchState& st, BatchPlan& P, std::vector<std::vector<int32_t>>& out) {
     const int32_t S = (int32_t)P.small.size();
     out.assign(S, {});
-    if (mode == 1) {
-        if (!S) return BR_OK;
-        const uint32_t* hs = P.h_ustat;
-        const size_t guess = std::min<size_t>(std::max<size_t>(P.keys_hint, 1024), (size_t)std::max<int64_t>(P.vtot, 1));
-        const uint32_t nk = hs[1];
-        if (hs[4] != 0 || (int64_t)nk > P.vtot)
-            return fail(BR_EINTERNAL, "batched: union bridge step status %u, %u keys", hs[4], nk);
-        uint64_t* hk = reinterpret_cast<uint64_t*>(P.h_ustat + 64);
-        if (nk > guess) {
-            BR_HIP(hipMemcpyAsync(hk + guess, P.d_ukeys + guess, 8 * (size_t)(nk - guess), hipMemcpyDeviceToHost, st.stream));
-            BR_HIP(hipStreamSynchronize(st.stream));
-        }
-        P.keys_hint = nk;
-        std::vector<uint64_t> keys(hk, hk + nk);
-        canonical_sort(keys);
-        // keys in ascending global order: each graph's keys are one run
-        int32_t s = 0;
-        for (uint64_t k : keys) {
-            const int64_t u = (int64_t)(k >> 32), v = (int64_t)(k & 0xffffffffu);
-            while (s + 1 < S && P.vbase[s + 1] <= u) s++;
-            if (u < P.vbase[s] || v >= P.vbase[s + 1]) return fail(BR_EINTERNAL, "batched: a bridge joins two graphs");
-            out[s].push_back((int32_t)(u - P.vbase[s]));
-            out[s].push_back((int32_t)(v - P.vbase[s]));
-        }
-        return BR_OK;
-    }
     std::atomic<int32_t> next{0};
     std::atomic<int> bad{0};
     st.pool->run([&](int w) {
@@ -559,6 +494,79 @@ static int gather_big(BatchState& st, BatchPlan& P, int mode, std::vector<std::v
         }
     });
     if (bad) return fail(BR_EINTERNAL, "batched: certificate counts exceed their region");
+    return BR_OK;
+}
+
+// Bridges of the graphs gs (indices into the batch) through one plain query over
+// their disjoint union; out[k] = pairs of graph gs[k].  Per graph the 160 KB
+// kernel took a CU for its chunks and merges in turn (150 graphs of 100 to
+// 24,000 vertices: 1,040 of 1,860 us); the union gives every CU edges of all
+// of them.
+static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const int64_t* eoff, const int32_t* V,
+                      const std::vector<int32_t>& gs, std::vector<std::vector<int32_t>>& out) {
+    const int32_t n = (int32_t)gs.size();
+    out.assign(n, {});
+    for (int32_t k0 = 0; k0 < n;) {
+        // as many graphs as the final step takes vertices
+        int64_t vt = 0, et = 0, longest = 0;
+        int32_t k1 = k0;
+        std::vector<int64_t> vbase;
+        while (k1 < n && vt + V[gs[k1]] <= kFinalStepMaxV) {
+            const int64_t m = eoff[gs[k1] + 1] - eoff[gs[k1]];
+            vbase.push_back(vt);
+            vt += V[gs[k1]];
+            et += m;
+            longest = std::max(longest, m);
+            k1++;
+        }
+        vbase.push_back(vt);
+        const size_t ebytes = a256(8 * (size_t)et), tbytes = sizeof(UnionItem) * (size_t)(k1 - k0);
+        if (st.union_d_cap < ebytes + tbytes) {
+            BR_HIP(hipStreamSynchronize(st.stream));
+            if (st.union_d) BR_HIP(hipFree(st.union_d));
+            st.union_d = nullptr;
+            st.union_d_cap = 0;
+            BR_HIP(hipMalloc(&st.union_d, ebytes + tbytes));
+            st.union_d_cap = ebytes + tbytes;
+        }
+        if (st.union_h_cap < tbytes) {
+            if (st.union_h) BR_HIP(hipHostFree(st.union_h));
+            st.union_h = nullptr;
+            st.union_h_cap = 0;
+            BR_HIP(hipHostMalloc(&st.union_h, tbytes, hipHostMallocDefault));
+            st.union_h_cap = tbytes;
+        }
+        UnionItem* it = static_cast<UnionItem*>(st.union_h);
+        int64_t at = 0;
+        for (int32_t k = k0; k < k1; k++) {
+            const int32_t g = gs[k];
+            const int64_t m = eoff[g + 1] - eoff[g];
+            it[k - k0] = UnionItem{d_edges + 2 * eoff[g], at, m, (int32_t)vbase[k - k0], V[g]};
+            at += m;
+        }
+        int32_t* du = static_cast<int32_t*>(st.union_d);
+        UnionItem* dt = reinterpret_cast<UnionItem*>(static_cast<char*>(st.union_d) + ebytes);
+        BR_HIP(hipMemcpyAsync(dt, it, tbytes, hipMemcpyHostToDevice, st.stream));
+        launch_union_edges(dt, k1 - k0, longest, du, st.stream);
+        BR_HIP(hipGetLastError());
+        const TuneEntry knobs{{"fuse", 1}, {"table", k1 - k0 == 1 ? 1 : 0}};
+        std::vector<int32_t> pairs(2 * (size_t)std::max<int64_t>(vt - (k1 - k0), 1));
+        int64_t nb = 0;
+        const int rc = bridges_find(c, du, et, (int32_t)vt, 1, pairs.data(), (int64_t)pairs.size() / 2, &nb, st.stream, &knobs);
+        if (rc == BR_ERANGE) return fail(BR_ERANGE, "batched: an edge has a vertex id outside its graph's [0, V)");
+        if (rc) return rc;
+        // ascending: each graph's pairs are one run
+        int32_t k = k0;
+        for (int64_t i = 0; i < nb; i++) {
+            const int64_t u = pairs[2 * i], v = pairs[2 * i + 1];
+            while (k + 1 < k1 && vbase[k + 1 - k0] <= u) k++;
+            const int64_t b = vbase[k - k0];
+            if (u < b || v >= vbase[k + 1 - k0]) return fail(BR_EINTERNAL, "batched: a bridge joins two graphs");
+            out[k].push_back((int32_t)(u - b));
+            out[k].push_back((int32_t)(v - b));
+        }
+        k0 = k1;
+    }
     return BR_OK;
 }
 
@@ -673,23 +681,33 @@ int batched_query(br_ctx* c, const int32_t* d_edges, const int64_t* h_edge_off, 
     int rc = transient ? get_transient(c, st, h_edge_off, h_V, G, C, bpc, &P, false)
                        : get_plan(c, st, h_edge_off, h_V, G, C, bpc, &P);
     if (rc) return rc;
-    // graphs above the small kernel's V and within a CU's LDS: the 160 KB
-    // kernel, one workgroup per CU, in the same call
-    BatchPlan* PM = nullptr;
-    for (int32_t g = 0; g < G; g++)
-        if (h_V[g] > batched_max_v_dev() && h_V[g] <= batched_max_v_big()) {
-            rc = transient ? get_transient(c, st, h_edge_off, h_V, G, C, 1, &PM, true)
-                           : get_plan(c, st, h_edge_off, h_V, G, C, 1, &PM, true);
-            if (rc) return rc;
-            break;
-        }
+    // graphs above the small kernel's V and within a CU's LDS: one query over
+    // their union (final step on the device), or the 160 KB kernel, one
+    // workgroup per CU, and the host's search of each certificate
     const int mode = c->final_step;
+    BatchPlan* PM = nullptr;
+    std::vector<int32_t> mid;
+    for (int32_t g = 0; g < G; g++)
+        if (h_V[g] > batched_max_v_dev() && h_V[g] <= batched_max_v_big()) mid.push_back(g);
+    if (!mid.empty() && mode != 1) {
+        rc = transient ? get_transient(c, st, h_edge_off, h_V, G, C, 1, &PM, true)
+                       : get_plan(c, st, h_edge_off, h_V, G, C, 1, &PM, true);
+        if (rc) return rc;
+    }
     if (c->profiling) BR_HIP(hipEventRecord(st.e0, st.stream));
     rc = run_device(st, *P, d_edges, mode, !transient);
     if (rc) return rc;
     if (PM) {
         rc = run_device(st, *PM, d_edges, mode, !transient);
         if (rc) return rc;
+    }
+    std::vector<std::vector<int32_t>> mid_out;
+    if (!mid.empty() && mode == 1) {
+        rc = find_union(c, st, d_edges, h_edge_off, h_V, mid, mid_out);
+        if (rc) {
+            (void)hipStreamSynchronize(st.stream);
+            return rc;
+        }
     }
     if (c->profiling) BR_HIP(hipEventRecord(st.e1, st.stream));
     BR_HIP(hipStreamSynchronize(st.stream));
@@ -699,9 +717,8 @@ int batched_query(br_ctx* c, const int32_t* d_edges, const int64_t* h_edge_off, 
         if (*Q->h_err & 1u) return fail(BR_ERANGE, "batched: an edge has a vertex id outside its graph's [0, V)");
         if (*Q->h_err) return fail(BR_EINTERNAL, "batched: certificate region overflow");
     }
-    std::vector<std::vector<int32_t>> mid_out;
     if (PM) {
-        rc = gather_big(st, *PM, mode, mid_out);
+        rc = gather_big(st, *PM, mid_out);
         if (rc) return rc;
     }
 
@@ -709,8 +726,7 @@ int batched_query(br_ctx* c, const int32_t* d_edges, const int64_t* h_edge_off, 
     // pairs, compacted afterwards
     const int32_t S = (int32_t)P->small.size();
     std::vector<int64_t> slot(S + 1, 0), nb(G, 0);
-    if (PM)
-        for (size_t k = 0; k < PM->small.size(); k++) nb[PM->small[k]] = (int64_t)mid_out[k].size() / 2;
+    for (size_t k = 0; k < mid.size(); k++) nb[mid[k]] = (int64_t)mid_out[k].size() / 2;
     for (int32_t s = 0; s < S; s++) slot[s + 1] = slot[s] + std::max(P->V[P->small[s]] - 1, 0);
     uint64_t* outk = nullptr;
     const uint32_t* keys = nullptr;     // mode 1: the device's sorted keys, (u | v << 16)
@@ -804,9 +820,8 @@ int batched_query(br_ctx* c, const int32_t* d_edges, const int64_t* h_edge_off, 
         }
         for (size_t k = 0; k < P->large.size(); k++)
             std::copy(large_out[k].begin(), large_out[k].end(), h_bridges + 2 * h_bridge_off[P->large[k]]);
-        if (PM)
-            for (size_t k = 0; k < PM->small.size(); k++)
-                std::copy(mid_out[k].begin(), mid_out[k].end(), h_bridges + 2 * h_bridge_off[PM->small[k]]);
+        for (size_t k = 0; k < mid.size(); k++)
+            std::copy(mid_out[k].begin(), mid_out[k].end(), h_bridges + 2 * h_bridge_off[mid[k]]);
     }
     auto t3 = std::chrono::steady_clock::now();
     if (c->profiling) {

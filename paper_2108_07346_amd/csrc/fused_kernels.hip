@@ -435,7 +435,7 @@ void plan_fused(Plan& P) {
     }
     P.code_per = 0;
     P.code_words = 0;
-    if (E > 16 * V && E >= (int64_t(1) << 19))
+    if (P.table && E > 16 * V && E >= (int64_t(1) << 19))
         for (int per : {2, 4, 8, 16, 32})
             if (4 * ((V + per - 1) / per) <= kTabBytes) {
                 P.code_per = per;

@@ -123,6 +123,7 @@ struct Plan {
     // the whole list certified in one pass (fused_kernels.hip); M is 1 then
     bool fused = false;
     int32_t s1 = 1, s2 = 1;        // rows r of stage 1: r % s1 == 0; of stages 1 and 2: r % s2 == 0
+    bool table = true;             // the list may use a table (one graph's components; not for unions of many)
     int32_t code_per = 0;          // codes per word of the stage 3 table (0: no table)
     int32_t code_words = 0;
     bool contract = false;         // final step over the contracted certificate first (contract_kernels.hip)
@@ -197,9 +198,6 @@ struct BatchDev {
 // workgroup per CU); else up to batched_max_v_dev()
 void launch_batched(const BatchDev& B, int blocks, hipStream_t s, bool big = false);
 int32_t batched_max_v_big();
-// node-0 certificates of the batch's graphs 0..S-1 as one certificate of their
-// disjoint union (ids shifted by vbase): F edges at f1u, F' edges at f2u,
-// their numbers at cntu[0], cntu[1]; uoff [2S] scratch
 // one device edge list to gather: n edges from src to edge offset `at`
 struct GatherItem {
     const int32_t* src;
@@ -208,8 +206,15 @@ struct GatherItem {
 // copies every item's edges into dst in one launch (items in device memory;
 // max_edges = the largest n)
 void launch_gather_edges(const GatherItem* d_items, int32_t n, int64_t max_edges, int32_t* dst, hipStream_t s);
-void launch_union_certificate(const BatchDev& B, int32_t S, int64_t* uoff, int2* f1u, int2* f2u, uint32_t* cntu,
-                              hipStream_t s);
+// One graph of a disjoint union: n edges at src, its first vertex base, its V.
+struct UnionItem {
+    const int32_t* src;
+    int64_t at, n;
+    int32_t base, V;
+};
+// copies every item's edges to dst + at, ids moved up by base (an id outside
+// [0, V) becomes -1)
+void launch_union_edges(const UnionItem* d_items, int32_t n, int64_t max_edges, int32_t* dst, hipStream_t s);
 // Final step on the device for the batched path: one workgroup per small graph
 // finds the bridges of node 0's certificate in LDS; keys (u << 16 | v, sorted)
 // go to out_keys at a base taken from out_hdr[0]; out_hdr[16 + 2s] / [17 + 2s]
@@ -394,6 +399,9 @@ struct br_ctx {
 
 namespace br {
 int ensure_workspace(br_ctx* c, size_t bytes, hipStream_t s);
+// br_bridges_find; plan_knobs: plan with these knobs instead of the tuner's entry
+int bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t M, int32_t* h_bridges, int64_t cap,
+                 int64_t* n_bridges, void* stream, const TuneEntry* plan_knobs);
 // br_bridges_find_batched after argument checks; transient: the batch shape
 // is used once (serving ticks): plans built in reused arenas, launched
 // without graph capture, chunk size from the tuner's cache or a default

@@ -140,8 +140,9 @@ void charge(Request& r, bool host_edges, int mode, int device) {
 // packed edges, its certificate regions (per merge level at most its edges,
 // per node at most 2(V-1) pairs), per-node counters and metadata, root flags
 // and bridge keys, and for graphs above the small kernel's limit its part of
-// the union certificate and of the bridge step's scratch.  Chunks of at least
-// 4,096 edges (the smallest chunk size the batched path uses).
+// the union's edges and of the query over it (state, certificate, bridge step,
+// and the fixed scratch once per request).  Chunks of at least 4,096 edges (the
+// smallest chunk size the batched path uses).
 int64_t lane_need(const Request& r) {
     const int64_t C = 4096, M = std::max<int64_t>(1, (r.E + C - 1) / C);
     int R = 0;
@@ -149,7 +150,8 @@ int64_t lane_need(const Request& r) {
     const int64_t V = r.V;
     const int64_t regions = std::min<int64_t>(r.E * (R + 1), 2 * V * M);
     int64_t b = 8 * r.E + 8 * regions + (96 + 4 * (int64_t)R) * M + 8 * V + 8192;
-    if (r.V > batched_max_v_dev()) b += 16 * V + 4 * device_bridges_words(r.V) + 8192;
+    if (r.V > batched_max_v_dev())
+        b += 8 * r.E + 72 * V + 4 * device_bridges_words(r.V) + 4 * (int64_t)contract_words() + 16384;
     return b;
 }
 
@@ -388,9 +390,11 @@ int lane_run(LaneWorker& L, const std::vector<std::shared_ptr<Request>>& batch, 
     return BR_OK;
 }
 
-// what a worker holds between ticks: its packed edge buffer and its context's
-// plan arenas
-int64_t lane_held_now(const LaneWorker& L) { return (int64_t)L.cap + (int64_t)batched_device_bytes(L.ctx); }
+// what a worker holds between ticks: its packed edge buffer, its context's plan
+// arenas and the workspace of its queries over unions
+int64_t lane_held_now(const LaneWorker& L) {
+    return (int64_t)L.cap + (int64_t)batched_device_bytes(L.ctx) + (int64_t)L.ctx->ws.size;
+}
 
 void lane_loop(br_server* S, LaneWorker* L) {
     (void)hipSetDevice(S->device);
@@ -470,6 +474,10 @@ void release_lane(br_server* S, LaneWorker& L) {
     (void)hipSetDevice(S->device);
     (void)hipStreamSynchronize(L.stream);
     batched_release(L.ctx);
+    if (L.ctx->ws.base) (void)hipFree(L.ctx->ws.base);
+    L.ctx->ws.base = nullptr;
+    L.ctx->ws.size = 0;
+    L.ctx->solo_key_base = nullptr;
     if (L.buf) (void)hipFree(L.buf);
     L.buf = nullptr;
     L.cap = 0;
@@ -692,6 +700,7 @@ int br_server_create(br_server** out, int device, int64_t mem_budget, int32_t ma
     for (int i = 0; i < kLaneWorkers; i++) {
         auto L = std::make_unique<LaneWorker>();
         int rc = br_create(&L->ctx, device);
+        if (rc == BR_OK) L->ctx->exact_ws = true;
         if (rc == BR_OK && hipStreamCreateWithFlags(&L->stream, hipStreamNonBlocking) != hipSuccess)
             rc = hip_fail(hipGetLastError(), "hipStreamCreate");
         if (rc) {
