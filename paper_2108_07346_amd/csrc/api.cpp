@@ -328,7 +328,7 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
         if (rc == BR_OK && P.contract && device_final) rc = contract_prepare();
         if (rc) return rc;
         c->solo_key_base = nullptr;    // this call's layout overwrites where slots may have been
-        FusedBufs F;
+        FusedBufs F = c->fused;            // a union's row items
         F.rcode = reinterpret_cast<uint32_t*>(base + L.rcode);
         F.ncode = F.rcode + P.V;
         F.code = reinterpret_cast<uint32_t*>(base + L.code);

@@ -502,6 +502,7 @@ static int gather_big(BatchState& st, BatchPlan& P, std::vector<std::vector<int3
 // kernel took a CU for its chunks and merges in turn (150 graphs of 100 to
 // 24,000 vertices: 1,040 of 1,860 us); the union gives every CU edges of all
 // of them.
+constexpr int64_t kUnionRun = 64;        // rows per workgroup of the list's long part (32,768 edges per table)
 static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const int64_t* eoff, const int32_t* V,
                       const std::vector<int32_t>& gs, std::vector<std::vector<int32_t>>& out) {
     const int32_t n = (int32_t)gs.size();
@@ -510,17 +511,26 @@ static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const i
         // as many graphs as the final step takes vertices
         int64_t vt = 0, et = 0, longest = 0;
         int32_t k1 = k0;
-        std::vector<int64_t> vbase;
+        std::vector<int64_t> vbase, at;
+        std::vector<RowItem> rows;       // runs of rows of one graph: a workgroup's share of the list
+        int32_t max_v = 0;
+        const int64_t row = union_row();
         while (k1 < n && vt + V[gs[k1]] <= kFinalStepMaxV) {
-            const int64_t m = eoff[gs[k1] + 1] - eoff[gs[k1]];
+            const int64_t m = eoff[gs[k1] + 1] - eoff[gs[k1]], nr = (m + row - 1) / row;
             vbase.push_back(vt);
+            at.push_back(et);
+            for (int64_t r = 0; r < nr; r += kUnionRun)
+                rows.push_back(RowItem{(uint32_t)(et / row + r), (uint32_t)(et / row + std::min(nr, r + kUnionRun)), (int32_t)vt,
+                                       V[gs[k1]]});
             vt += V[gs[k1]];
-            et += m;
+            et += nr * row;
+            max_v = std::max(max_v, V[gs[k1]]);
             longest = std::max(longest, m);
             k1++;
         }
         vbase.push_back(vt);
-        const size_t ebytes = a256(8 * (size_t)et), tbytes = sizeof(UnionItem) * (size_t)(k1 - k0);
+        const size_t ebytes = a256(8 * (size_t)et), rbytes = a256(sizeof(RowItem) * rows.size());
+        const size_t tbytes = rbytes + sizeof(UnionItem) * (size_t)(k1 - k0);
         if (st.union_d_cap < ebytes + tbytes) {
             BR_HIP(hipStreamSynchronize(st.stream));
             if (st.union_d) BR_HIP(hipFree(st.union_d));
@@ -536,19 +546,20 @@ static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const i
             BR_HIP(hipHostMalloc(&st.union_h, tbytes, hipHostMallocDefault));
             st.union_h_cap = tbytes;
         }
-        UnionItem* it = static_cast<UnionItem*>(st.union_h);
-        int64_t at = 0;
+        std::copy(rows.begin(), rows.end(), static_cast<RowItem*>(st.union_h));
+        UnionItem* it = reinterpret_cast<UnionItem*>(static_cast<char*>(st.union_h) + rbytes);
         for (int32_t k = k0; k < k1; k++) {
             const int32_t g = gs[k];
-            const int64_t m = eoff[g + 1] - eoff[g];
-            it[k - k0] = UnionItem{d_edges + 2 * eoff[g], at, m, (int32_t)vbase[k - k0], V[g]};
-            at += m;
+            it[k - k0] = UnionItem{d_edges + 2 * eoff[g], at[k - k0], eoff[g + 1] - eoff[g], (int32_t)vbase[k - k0], V[g]};
         }
         int32_t* du = static_cast<int32_t*>(st.union_d);
-        UnionItem* dt = reinterpret_cast<UnionItem*>(static_cast<char*>(st.union_d) + ebytes);
-        BR_HIP(hipMemcpyAsync(dt, it, tbytes, hipMemcpyHostToDevice, st.stream));
-        launch_union_edges(dt, k1 - k0, longest, du, st.stream);
+        char* dt = static_cast<char*>(st.union_d) + ebytes;
+        BR_HIP(hipMemcpyAsync(dt, st.union_h, tbytes, hipMemcpyHostToDevice, st.stream));
+        launch_union_edges(reinterpret_cast<const UnionItem*>(dt + rbytes), k1 - k0, longest, (int32_t)row, du, st.stream);
         BR_HIP(hipGetLastError());
+        c->fused.items = reinterpret_cast<const RowItem*>(dt);
+        c->fused.n_items = (int32_t)rows.size();
+        c->fused.item_words = (int32_t)(((max_v + 1) / 2 + 3) & ~3);
         const TuneEntry knobs{{"fuse", 1}, {"table", k1 - k0 == 1 ? 1 : 0}};
         std::vector<int32_t> pairs(2 * (size_t)std::max<int64_t>(vt - (k1 - k0), 1));
         int64_t nb = 0;

@@ -367,7 +367,7 @@ void launch_gather_edges(const GatherItem* d_items, int32_t n, int64_t max_edges
 }
 
 namespace {
-__global__ void __launch_bounds__(256) k_union_edges(const UnionItem* items, int2* dst) {
+__global__ void __launch_bounds__(256) k_union_edges(const UnionItem* items, int32_t row, int2* dst) {
     const UnionItem it = items[blockIdx.x];
     const int2* src = reinterpret_cast<const int2*>(it.src);
     for (int64_t lo = blockIdx.y * kGatherRun; lo < it.n; lo += (int64_t)gridDim.y * kGatherRun) {
@@ -378,13 +378,16 @@ __global__ void __launch_bounds__(256) k_union_edges(const UnionItem* items, int
             dst[it.at + k] = ok ? make_int2(e.x + it.base, e.y + it.base) : make_int2(-1, -1);
         }
     }
+    const int64_t end = (it.n + row - 1) / row * row;
+    if (blockIdx.y == 0)
+        for (int64_t k = it.n + threadIdx.x; k < end; k += 256) dst[it.at + k] = make_int2(it.base, it.base);
 }
 }  // namespace
 
-void launch_union_edges(const UnionItem* d_items, int32_t n, int64_t max_edges, int32_t* dst, hipStream_t s) {
+void launch_union_edges(const UnionItem* d_items, int32_t n, int64_t max_edges, int32_t row, int32_t* dst, hipStream_t s) {
     if (n <= 0 || max_edges <= 0) return;
     const int64_t runs = std::min<int64_t>((max_edges + kGatherRun - 1) / kGatherRun, 1024);
-    hipLaunchKernelGGL(k_union_edges, dim3((unsigned)n, (unsigned)runs), dim3(256), 0, s, d_items,
+    hipLaunchKernelGGL(k_union_edges, dim3((unsigned)n, (unsigned)runs), dim3(256), 0, s, d_items, row,
                        reinterpret_cast<int2*>(dst));
 }
 

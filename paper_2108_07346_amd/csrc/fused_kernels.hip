@@ -268,32 +268,49 @@ typedef int edge2 __attribute__((ext_vector_type(4), aligned(8)));   // two edge
 // Stage 3: all rows that are not multiples of div + 1 (div = 0: all rows).  A wavefront takes 128
 // edges (two per lane) at a time, kU such loads in flight; every wavefront
 // keeps its own list, so the stream has no barrier.
-template <int kPer, bool kSplit, bool kList>
+//
+// kItems: the list is a union of graphs whose edges start at whole rows;
+// workgroup b takes the rows of item b that are not multiples of div + 1, with
+// a table of its graph alone -- every component named by its root.
+template <int kPer, bool kSplit, bool kList, bool kItems>
 __global__ void __launch_bounds__(kFilterBlock) k_filter(DevBufs B, int64_t E, int32_t V, int64_t cap, uint32_t nsel,
-                                                         uint32_t div, const uint32_t* code, int32_t words, Sink K) {
+                                                         uint32_t div, const uint32_t* code, int32_t words, Sink K,
+                                                         const RowItem* items) {
     constexpr int kU = 4;
+    static_assert(!kItems || kPer == 2, "a graph of a union has 16-bit codes");
+    RowItem it{};
+    if constexpr (kItems) it = items[blockIdx.x];
     auto drain = [&](const int2* l, uint32_t k) {
         if constexpr (kList) append_list(K.out, K.nout, K.room, l, k);
         else offer_list(B, cap, l, k);
     };
     extern __shared__ __align__(16) uint32_t lds[];
     uint32_t* tab = lds;
-    for (int32_t i = threadIdx.x; i < words / 4; i += kFilterBlock)
-        reinterpret_cast<uint4*>(tab)[i] = reinterpret_cast<const uint4*>(code)[i];
+    if constexpr (kItems) {
+        for (int32_t x = threadIdx.x; x < it.V; x += kFilterBlock) {
+            const uint32_t d = B.state[B.qs * ((int64_t)it.base + x) + 1];
+            reinterpret_cast<uint16_t*>(tab)[x] = (uint16_t)(x - (int32_t)d + 1);
+        }
+    } else {
+        for (int32_t i = threadIdx.x; i < words / 4; i += kFilterBlock)
+            reinterpret_cast<uint4*>(tab)[i] = reinterpret_cast<const uint4*>(code)[i];
+    }
     __syncthreads();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     int2* wl = reinterpret_cast<int2*>(lds + words) + wave * kListCap;
     uint32_t n = 0;                                                     // edges in the list (uniform)
-    const int64_t units = (int64_t)nsel * (kRow / 128), stride = (int64_t)gridDim.x * kFilterWaves;
-    for (int64_t u = (int64_t)blockIdx.x * kFilterWaves + wave; u < units; u += stride * kU) {
+    const int64_t units = (int64_t)(kItems ? it.r1 - it.r0 : nsel) * (kRow / 128);
+    const int64_t stride = kItems ? kFilterWaves : (int64_t)gridDim.x * kFilterWaves;
+    for (int64_t u = kItems ? wave : (int64_t)blockIdx.x * kFilterWaves + wave; u < units; u += stride * kU) {
         int2 e[kU][2];
         uint32_t have = 0;
 #pragma unroll
         for (int j = 0; j < kU; j++) {
             const int64_t uu = u + j * stride;
             e[j][0] = e[j][1] = make_int2(0, 0);
-            if (uu < units) {
-                const int64_t i = stage_row((uint32_t)(uu >> 2), 1, div) * kRow + (uu & 3) * 128 + 2 * lane;
+            const uint32_t sel = (uint32_t)(uu >> 2);
+            if (uu < units && !(kItems && (it.r0 + sel) % (div + 1) == 0)) {
+                const int64_t i = (kItems ? (int64_t)(it.r0 + sel) : stage_row(sel, 1, div)) * kRow + (uu & 3) * 128 + 2 * lane;
                 if (i + 1 < E) {
                     if constexpr (kSplit) {
                         e[j][0] = edge_at(B, i);
@@ -317,7 +334,12 @@ __global__ void __launch_bounds__(kFilterBlock) k_filter(DevBufs B, int64_t E, i
                 const uint32_t x = (uint32_t)e[j][t].x, y = (uint32_t)e[j][t].y;
                 bool hard = false;
                 if (have >> (2 * j + t) & 1u) {
-                    if (x < (uint32_t)V && y < (uint32_t)V) {
+                    if (kItems) {
+                        // (-1: an id that was out of its graph's range)
+                        const uint32_t a = x - (uint32_t)it.base, b = y - (uint32_t)it.base;
+                        if (a < (uint32_t)it.V && b < (uint32_t)it.V) hard = code_of<kPer>(tab, a) != code_of<kPer>(tab, b);
+                        else atomicOr(B.err, 1u);
+                    } else if (x < (uint32_t)V && y < (uint32_t)V) {
                         const uint32_t cx = code_of<kPer>(tab, x), cy = code_of<kPer>(tab, y);
                         hard = cx != cy || cx == 0;
                     } else {
@@ -365,8 +387,10 @@ template <int kPer>
 void launch_filter(const DevBufs& B, const Plan& P, uint32_t nsel, uint32_t div, const uint32_t* code, int grid,
                    const Sink& K, hipStream_t s) {
     const size_t lds = 4 * (size_t)P.code_words + kListBytes;
-    auto k = K.out ? &k_filter<kPer, false, true> : (B.edges2 && B.split < P.E ? &k_filter<kPer, true, false> : &k_filter<kPer, false, false>);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(kFilterBlock), lds, s, B, P.E, P.V, P.cap[0], nsel, div, code, P.code_words, K);
+    auto k = K.out ? &k_filter<kPer, false, true, false>
+                   : (B.edges2 && B.split < P.E ? &k_filter<kPer, true, false, false> : &k_filter<kPer, false, false, false>);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kFilterBlock), lds, s, B, P.E, P.V, P.cap[0], nsel, div, code, P.code_words, K,
+                       (const RowItem*)nullptr);
 }
 
 // f(integral constant) for the codes per word
@@ -383,7 +407,10 @@ void with_per(int32_t per, Fn f) {
 
 template <int kPer>
 hipError_t raise_lds() {
-    for (auto k : {&k_filter<kPer, false, false>, &k_filter<kPer, true, false>, &k_filter<kPer, false, true>}) {
+    std::vector<void (*)(DevBufs, int64_t, int32_t, int64_t, uint32_t, uint32_t, const uint32_t*, int32_t, Sink, const RowItem*)> ks{
+        &k_filter<kPer, false, false, false>, &k_filter<kPer, true, false, false>, &k_filter<kPer, false, true, false>};
+    if constexpr (kPer == 2) ks.push_back(&k_filter<2, false, false, true>);
+    for (auto k : ks) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kFilterLds - 256);
         if (e != hipSuccess) return e;
@@ -444,6 +471,8 @@ void plan_fused(Plan& P) {
             }
 }
 
+int32_t union_row() { return kRow; }
+
 int fused_prepare() {
     static const hipError_t e = [] {
         for (hipError_t r : {raise_lds<2>(), raise_lds<4>(), raise_lds<8>(), raise_lds<16>(), raise_lds<32>()})
@@ -501,6 +530,14 @@ int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_
     if (P.s2 > 1) {
         const uint32_t nsel = (uint32_t)(nrows - m2), div = (uint32_t)(P.s2 - 1);
         flatten(P.code_per == 2);
+        if (!P.table && P.s2 < P.s1) {
+            // (after stage 1 alone too many edges still join components of F':
+            // 405 us here for 9e6 edges over 560,000 vertices in 48 graphs)
+            hipLaunchKernelGGL((k_filter<2, false, false, true>), dim3((unsigned)F.n_items), dim3(kFilterBlock),
+                               4 * (size_t)F.item_words + kListBytes, s, B, P.E, P.V, P.cap[0], 0u, div,
+                               (const uint32_t*)nullptr, F.item_words, Sink{}, F.items);
+            return launches + 1;
+        }
         if (P.code_per == 0) {
             rows(nsel, 1, div, 4 * cus);
             return launches;

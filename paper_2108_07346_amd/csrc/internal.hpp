@@ -212,9 +212,10 @@ struct UnionItem {
     int64_t at, n;
     int32_t base, V;
 };
-// copies every item's edges to dst + at, ids moved up by base (an id outside
-// [0, V) becomes -1)
-void launch_union_edges(const UnionItem* d_items, int32_t n, int64_t max_edges, int32_t* dst, hipStream_t s);
+// copies every item's edges to dst + at, ids moved up by base (an edge with an id
+// outside [0, V) becomes (-1, -1)), and fills up to the next multiple of `row`
+// with loops
+void launch_union_edges(const UnionItem* d_items, int32_t n, int64_t max_edges, int32_t row, int32_t* dst, hipStream_t s);
 // Final step on the device for the batched path: one workgroup per small graph
 // finds the bridges of node 0's certificate in LDS; keys (u << 16 | v, sorted)
 // go to out_keys at a base taken from out_hdr[0]; out_hdr[16 + 2s] / [17 + 2s]
@@ -236,12 +237,22 @@ int32_t batched_max_blocks_per_cu();
 // certificate's forest tours in 30-bit fields (and the host search in int32).
 constexpr int32_t kFinalStepMaxV = 1 << 29;
 
+// Rows [r0, r1) of a union of graphs, all of the graph of V vertices from `base`.
+struct RowItem {
+    uint32_t r0, r1;
+    int32_t base, V;
+};
 // The one-pass certificate (fused_kernels.hip).
 struct FusedBufs {
     uint32_t* rcode = nullptr;     // [V] code of each root of F' (zero at launch)
     uint32_t* ncode = nullptr;     // [1] codes given (zero at launch)
     uint32_t* code = nullptr;      // [code_words]
+    // a union of graphs (Plan.table false): runs of whole rows of one graph, and
+    // the words of the largest graph's table
+    const RowItem* items = nullptr;
+    int32_t n_items = 0, item_words = 0;
 };
+int32_t union_row();               // edges per row: a graph of a union starts at a whole row
 void plan_fused(Plan& P);
 bool plan_lds(Plan& P);            // false: V is past what that plan is for
 int fused_prepare();               // once per process: the kernels' LDS limit
@@ -402,6 +413,7 @@ int ensure_workspace(br_ctx* c, size_t bytes, hipStream_t s);
 // br_bridges_find; plan_knobs: plan with these knobs instead of the tuner's entry
 int bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t M, int32_t* h_bridges, int64_t cap,
                  int64_t* n_bridges, void* stream, const TuneEntry* plan_knobs);
+// (knobs with "table" 0: c->fused holds the union's row items)
 // br_bridges_find_batched after argument checks; transient: the batch shape
 // is used once (serving ticks): plans built in reused arenas, launched
 // without graph capture, chunk size from the tuner's cache or a default
