@@ -62,19 +62,42 @@ namespace {
 
 // Certify edges [t0, t1) of graph g (ids < V) into an empty LDS state and write
 // the accepted edges to node region (off, cap).  Counts go to S.n12.
-// Each thread takes kU edges per step and the next step's edges are loaded
+// Each thread takes 2 kU edges per step and the next step's edges are loaded
 // before the current ones are offered, so that enough loads are in flight to
 // cover HBM latency while the LDS work proceeds.
 constexpr int kU = 4;
 
-__device__ __forceinline__ void load_step(const BatchDev& B, int64_t base, int64_t t1, int2 (&e)[kU]) {
+typedef int edge2 __attribute__((ext_vector_type(4), aligned(8)));   // two edges, 8-byte aligned
+
+// The edges of a step: kU pairs per thread.  ok: which of them exist.
+__device__ __forceinline__ uint32_t load_step(const BatchDev& B, int64_t base, int64_t t1, int2 (&e)[2 * kU]) {
+    uint32_t ok = 0;
+    const int64_t i0 = base + 2 * threadIdx.x;
+    if (base + 2 * kBB * kU <= t1) {             // a whole step (the same for every thread)
 #pragma unroll
-    for (int j = 0; j < kU; j++) {
-        const int64_t i = base + j * kBB + threadIdx.x;
-        e[j] = i < t1 ? B.edges[i] : make_int2(-1, -1);
+        for (int j = 0; j < kU; j++) {
+            const edge2 w = *reinterpret_cast<const edge2*>(B.edges + i0 + j * 2 * kBB);
+            e[2 * j] = make_int2(w.x, w.y);
+            e[2 * j + 1] = make_int2(w.z, w.w);
+        }
+        return (1u << 2 * kU) - 1u;
     }
+#pragma unroll
+    for (int j = 0; j < 2 * kU; j++) {
+        const int64_t i = i0 + (j >> 1) * 2 * kBB + (j & 1);
+        e[j] = make_int2(0, 0);
+        if (i < t1) {
+            e[j] = B.edges[i];
+            ok |= 1u << j;
+        }
+    }
+    return ok;
 }
 
+// What bounds it: instructions.  Most edges of a dense chunk end at the shared
+// parent in F' (two 16-bit LDS reads and a compare, which rejects the edge in F
+// too); loaded two to a 16-byte load and tested without 64-bit index arithmetic
+// per edge, they leave the time to the ones that search.
 template <class LS>
 __device__ void certify_chunk(LS& S, const BatchDev& B, int64_t t0, int64_t t1, uint32_t V, int64_t off,
                               int64_t cap) {
@@ -84,9 +107,10 @@ __device__ void certify_chunk(LS& S, const BatchDev& B, int64_t t0, int64_t t1, 
     // compress after the first 2V and 8V edges (dense chunks are then mostly
     // rejected by the shared-parent test)
     int64_t next_cmp = t0 + 2 * (int64_t)V;
-    constexpr int64_t kStep = (int64_t)kBB * kU;
-    int2 cur[kU], nxt[kU];
-    if (t0 < t1) load_step(B, t0, t1, cur);
+    constexpr int64_t kStep = (int64_t)kBB * 2 * kU;
+    int2 cur[2 * kU], nxt[2 * kU];
+    uint32_t ok = load_step(B, t0, t1, cur), nok = 0;
+    const lds_half* h2 = reinterpret_cast<const lds_half*>(S.q) + 1;     // x - parent in F' at h2[2 x]
     for (int64_t base = t0; base < t1; base += kStep) {
         if (base >= next_cmp) {
             __syncthreads();
@@ -94,31 +118,29 @@ __device__ void certify_chunk(LS& S, const BatchDev& B, int64_t t0, int64_t t1, 
             __syncthreads();
             next_cmp = next_cmp == t0 + 2 * (int64_t)V ? t0 + 8 * (int64_t)V : INT64_MAX;
         }
-        if (base + kStep < t1) load_step(B, base + kStep, t1, nxt);
-        if constexpr (LS::kStage >= kBB * kU) {
+        nok = load_step(B, base + kStep, t1, nxt);
+        if constexpr (LS::kStage >= kBB * 2 * kU) {
             // Where the stage area is free (it only serves merges), each
             // wavefront first applies the shared-parent test to all of its
-            // kU x 64 edges and packs the ones the test cannot reject into a
+            // 2 kU x 64 edges and packs the ones the test cannot reject into a
             // list of its own there; those are then offered 64 at a time, so
             // that the searches of a few lanes no longer hold a whole
             // wavefront (in a dense chunk most edges are rejected by the test).
-            uint32_t* wl = S.stage + (threadIdx.x / 64) * (64 * kU);
+            uint32_t* wl = S.stage + (threadIdx.x / 64) * (128 * kU);
             uint32_t nh = 0;
 #pragma unroll
-            for (int j = 0; j < kU; j++) {
+            for (int j = 0; j < 2 * kU; j++) {
                 const uint32_t x = (uint32_t)cur[j].x, y = (uint32_t)cur[j].y;
                 bool hard = false;
-                if (base + j * kBB + threadIdx.x < t1) {
-                    if (x < V && y < V) {
-                        const uint32_t wu = S.q[x], wv = S.q[y];
-                        hard = x - (wu & 0xffffu) != y - (wv & 0xffffu) || x - (wu >> 16) != y - (wv >> 16);
-                    } else {
-                        atomicOr(B.err, 1u);
-                    }
+                if (ok >> j & 1u) {
+                    if (max(x, y) < V) hard = x - h2[2 * x] != y - h2[2 * y];
+                    else atomicOr(B.err, 1u);
                 }
                 const uint64_t m = __ballot(hard);
-                if (hard) wl[nh + lane_rank(m)] = x | (y << 16);
-                nh += (uint32_t)__popcll(m);
+                if (m) {
+                    if (hard) wl[nh + lane_rank(m)] = x | (y << 16);
+                    nh += (uint32_t)__popcll(m);
+                }
             }
             __builtin_amdgcn_wave_barrier();     // the list, written by the wavefront's lanes, is read back by them
             for (uint32_t k0 = 0; k0 < nh; k0 += 64) {
@@ -138,11 +160,10 @@ __device__ void certify_chunk(LS& S, const BatchDev& B, int64_t t0, int64_t t1, 
             __builtin_amdgcn_wave_barrier();     // every lane's reads of the list before the next step's writes
         } else {
 #pragma unroll
-            for (int j = 0; j < kU; j++) {
+            for (int j = 0; j < 2 * kU; j++) {
                 const int2 e = cur[j];
-                const bool live = base + j * kBB + threadIdx.x < t1;
                 bool a1 = false, a2 = false;
-                if (live) {
+                if (ok >> j & 1u) {
                     if ((uint32_t)e.x < V && (uint32_t)e.y < V) loffer(S.q, (uint32_t)e.x, (uint32_t)e.y, a1, a2);
                     else atomicOr(B.err, 1u);
                 }
@@ -153,7 +174,8 @@ __device__ void certify_chunk(LS& S, const BatchDev& B, int64_t t0, int64_t t1, 
             }
         }
 #pragma unroll
-        for (int j = 0; j < kU; j++) cur[j] = nxt[j];
+        for (int j = 0; j < 2 * kU; j++) cur[j] = nxt[j];
+        ok = nok;
     }
     __syncthreads();
 }
