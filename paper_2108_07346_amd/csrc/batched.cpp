@@ -60,7 +60,7 @@ struct BatchPlan {
     // and count of small graph s; the keys follow the header directly
     uint32_t* d_sb = nullptr;
     uint32_t* h_sb = nullptr;
-    int32_t* d_lists = nullptr;      // small graphs by size class: [na] then [nb]
+    int32_t* d_lists = nullptr;      // graphs left to the second kernel, by size class: [S] and [S]
     int32_t na = 0, nb = 0;
     int cus = 1;
     int64_t sb_hdr = 0;              // header words (16 + 2S)
@@ -213,8 +213,8 @@ int build_plan(BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, i
     const size_t o_ncap = o; o = a256(o + 8 * (size_t)P.nodes);
     const size_t o_items = o; o = a256(o + 8 * std::max<size_t>(P.items.size(), 1));
     const size_t o_vb = o; o = a256(o + 8 * (size_t)(S + 1));
-    const size_t o_lists = o; if (!big) o = a256(o + 4 * (size_t)std::max(S, 1));
     const size_t meta_bytes = o - o_meta;
+    const size_t o_lists = o; if (!big) o = a256(o + 8 * (size_t)std::max(S, 1));
     const size_t o_cert = o; o = a256(o + 8 * (size_t)std::max<int64_t>(P.cert_pairs, 1));
     const size_t o_root = o; o = a256(o + 4 * (size_t)std::max<int64_t>(P.vtot, 1));
     const size_t o_sb = o; if (!big) o = a256(o + 4 * (size_t)(P.sb_hdr + P.sb_keys));
@@ -270,14 +270,8 @@ int build_plan(BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, i
         put(o_ncap, P.ncap.data(), 8 * (size_t)P.nodes);
         put(o_items, P.items.data(), 8 * P.items.size());
         put(o_vb, P.vbase.data(), 8 * (size_t)S);
-        if (!big) {
-            std::vector<int32_t> la, lb;
-            for (int32_t s = 0; s < S; s++) (V[P.small[s]] <= small_bridges_split_v() ? la : lb).push_back(s);
-            P.na = (int32_t)la.size();
-            P.nb = (int32_t)lb.size();
-            la.insert(la.end(), lb.begin(), lb.end());
-            put(o_lists, la.data(), 4 * (size_t)S);
-        }
+        if (!big)
+            for (int32_t s = 0; s < S; s++) (V[P.small[s]] <= small_bridges_split_v() ? P.na : P.nb)++;
         // ordered before the plan's launches (the same stream); the pinned
         // source is rewritten only by a later call, after that call's wait
         BR_HIP(hipMemcpyAsync(d + o_meta, m, meta_bytes, hipMemcpyHostToDevice, upload));
@@ -319,18 +313,23 @@ int enqueue(BatchPlan& P, const int32_t* d_edges, hipStream_t s, int mode, int p
     P.dev.edges = reinterpret_cast<const int2*>(d_edges);
     if (part == 0) {
         launch_fill_u32(P.dev.ncnt, (int64_t)P.clear_words, 0u, s);
+        const bool fin = mode == 1 && !P.big;
+        P.dev.out_hdr = fin ? P.d_sb : nullptr;
+        P.dev.out_keys = P.d_sb + P.sb_hdr;
+        P.dev.list_a = P.d_lists;
+        P.dev.list_b = P.d_lists + P.small.size();
+        P.dev.split_v = small_bridges_split_v();
+        if (fin) launch_fill_u32(P.d_sb, 16, 0u, s);
         BR_HIP(hipGetLastError());
         if (P.dev.n_items) launch_batched(P.dev, P.blocks, s, P.big);
         BR_HIP(hipGetLastError());
         return BR_OK;
     }
     if (mode == 1 && !P.small.empty()) {
-        launch_fill_u32(P.d_sb, 16, 0u, s);
         // fork: the two size classes run side by side, then join back on s
         BR_HIP(hipEventRecord(st->fork, s));
         BR_HIP(hipStreamWaitEvent(st->stream2, st->fork, 0));
-        launch_small_bridges(P.dev, P.d_lists, P.na, P.d_lists + P.na, P.nb, P.d_sb, P.d_sb + P.sb_hdr, P.cus, s,
-                             st->stream2);
+        launch_small_bridges(P.dev, P.na, P.nb, P.cus, s, st->stream2);
         BR_HIP(hipGetLastError());
         BR_HIP(hipEventRecord(st->join, st->stream2));
         BR_HIP(hipStreamWaitEvent(s, st->join, 0));

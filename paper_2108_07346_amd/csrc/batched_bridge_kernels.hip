@@ -1,5 +1,7 @@
-// Final step of the batched path on the device: the bridges of each small
-// graph's certificate, one workgroup per graph, entirely in LDS.
+// Final step of the batched path on the device for the graphs the persistent
+// kernel could not finish itself (the contracted certificate keeps a core of
+// cycles): the bridges of each one's certificate, one workgroup per graph,
+// entirely in LDS.
 //
 // The certificate is the one the persistent batched kernel leaves in node 0's
 // region of each graph (F from the front, F' from the back, graph-local ids),
@@ -18,12 +20,13 @@ constexpr int kLimitV = 4096;                 // vertices per small graph (the b
 constexpr int kSplitV = 1024;                 // graphs up to this size run in smaller workgroups, several per CU
 
 template <int kMaxV, int kST>
-__global__ void __launch_bounds__(kST) k_small_bridges(const BatchDev B, const int32_t* list, int32_t nlist,
+__global__ void __launch_bounds__(kST) k_small_bridges(const BatchDev B, const int32_t* list, const uint32_t* nlist,
                                                        uint32_t* out_hdr, uint32_t* out_keys) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     SmallLds<kMaxV, kST>& L = *reinterpret_cast<SmallLds<kMaxV, kST>*>(lds_raw);
     const int tid = threadIdx.x;
-    for (int64_t it = blockIdx.x; it < nlist; it += gridDim.x) {
+    const int64_t left = *nlist;
+    for (int64_t it = blockIdx.x; it < left; it += gridDim.x) {
         const int64_t g = list[it];
         const uint32_t V = (uint32_t)B.V[g];
         const int64_t off = B.noff[g], cap = B.ncap[g], vb = B.vbase[g];
@@ -94,14 +97,13 @@ __global__ void __launch_bounds__(kST) k_small_bridges(const BatchDev B, const i
 int32_t small_bridges_max_v() { return kLimitV; }
 int32_t small_bridges_split_v() { return kSplitV; }
 
-void launch_small_bridges(const BatchDev& B, const int32_t* list_a, int32_t na, const int32_t* list_b, int32_t nb,
-                          uint32_t* out_hdr, uint32_t* out_keys, int cus, hipStream_t s, hipStream_t s_b) {
+void launch_small_bridges(const BatchDev& B, int32_t na, int32_t nb, int cus, hipStream_t s, hipStream_t s_b) {
     if (nb > 0)
-        hipLaunchKernelGGL((k_small_bridges<kLimitV, 1024>), dim3((unsigned)std::min(nb, 4 * cus)), dim3(1024),
-                           sizeof(SmallLds<kLimitV, 1024>), s_b, B, list_b, nb, out_hdr, out_keys);
+        hipLaunchKernelGGL((k_small_bridges<kLimitV, 1024>), dim3((unsigned)std::min(nb, cus)), dim3(1024),
+                           sizeof(SmallLds<kLimitV, 1024>), s_b, B, (const int32_t*)B.list_b, B.out_hdr + 3, B.out_hdr, B.out_keys);
     if (na > 0)
-        hipLaunchKernelGGL((k_small_bridges<kSplitV, 256>), dim3((unsigned)std::min(na, 16 * cus)), dim3(256),
-                           sizeof(SmallLds<kSplitV, 256>), s, B, list_a, na, out_hdr, out_keys);
+        hipLaunchKernelGGL((k_small_bridges<kSplitV, 256>), dim3((unsigned)std::min(na, 4 * cus)), dim3(256),
+                           sizeof(SmallLds<kSplitV, 256>), s, B, (const int32_t*)B.list_a, B.out_hdr + 2, B.out_hdr, B.out_keys);
 }
 
 int prepare_small_bridges() {

@@ -256,6 +256,102 @@ __device__ void offer_region_append(LS& S, const BatchDev& B, int64_t offj, int6
 
 }  // namespace
 
+namespace {
+
+// parent in H's forest (roots of F' as vertices; H may be read while it changes)
+__device__ __forceinline__ uint32_t c_find(uint32_t* par, uint32_t x) {
+    for (uint32_t p = par[x]; p != x; p = par[x]) {
+        const uint32_t g = par[p];
+        par[x] = g;
+        x = g;
+    }
+    return x;
+}
+__device__ __forceinline__ bool c_unite(uint32_t* par, uint32_t a, uint32_t b) {
+    for (;;) {
+        a = c_find(par, a);
+        b = c_find(par, b);
+        if (a == b) return false;
+        if (a < b) { const uint32_t t = a; a = b; b = t; }
+        if (atomicCAS(&par[a], a, b) == a) return true;
+    }
+}
+
+// Bridges of the graph whose certificate is in region (off, cap) and whose
+// union-find state is in S.q, by contracting the components of F' (contract.hpp
+// has the reason): the edges of F that cross components are all bridges if they
+// form a forest; otherwise the graph goes to the list of those the second kernel
+// roots and numbers.  Everything stays in the workgroup's LDS: the crossing
+// edges in the stage, their forest, then the sorted keys in the state's place.
+template <class LS>
+__device__ void finish_graph(LS& S, const BatchDev& B, int32_t g, uint32_t V, int64_t off, uint32_t n1) {
+    uint32_t* he = S.stage;                      // [n1] a | b << 16, roots of F'
+    uint16_t* hk = reinterpret_cast<uint16_t*>(S.stage + kMaxV);     // [n1] place in F
+    uint32_t* ctr = S.stage + kMaxV + kMaxV / 2;  // 0: crossing edges, 1: one of them closes a cycle, 2: keys' base
+    lcompress(S.q, V);
+    if (threadIdx.x < 3) ctr[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < n1; k += kBB) {
+        const int2 e = region_edge(B, off, 0, n1, 0, k);
+        const uint32_t a = (uint32_t)e.x - (S.q[e.x] >> 16), b = (uint32_t)e.y - (S.q[e.y] >> 16);
+        if (a != b) {
+            const uint32_t p = atomicAdd(&ctr[0], 1u);
+            he[p] = a | b << 16;
+            hk[p] = (uint16_t)k;
+        }
+    }
+    __syncthreads();
+    const uint32_t m = ctr[0];
+    uint32_t* par = S.q;
+    for (uint32_t x = threadIdx.x; x < V; x += kBB) par[x] = x;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < m; j += kBB)
+        if (!c_unite(par, he[j] & 0xffffu, he[j] >> 16)) ctr[1] = 1;
+    __syncthreads();
+    if (ctr[1]) {
+        if (threadIdx.x == 0) {
+            const bool a = (int32_t)V <= B.split_v;
+            (a ? B.list_a : B.list_b)[atomicAdd(&B.out_hdr[a ? 2 : 3], 1u)] = g;
+        }
+        __syncthreads();
+        return;
+    }
+    // keys, sorted (bitonic), and their place in the output
+    uint32_t* key = S.q;
+    uint32_t P = 1;
+    while (P < m) P <<= 1;
+    for (uint32_t j = threadIdx.x; j < P; j += kBB) {
+        uint32_t w = 0xffffffffu;
+        if (j < m) {
+            const int2 e = region_edge(B, off, 0, n1, 0, hk[j]);
+            w = (uint32_t)min(e.x, e.y) << 16 | (uint32_t)max(e.x, e.y);
+        }
+        key[j] = w;
+    }
+    __syncthreads();
+    for (uint32_t k = 2; k <= P; k <<= 1)
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+            for (uint32_t i = threadIdx.x; i < P; i += kBB) {
+                const uint32_t q = i ^ j;
+                if (q > i) {
+                    const uint32_t x = key[i], y = key[q];
+                    if (((i & k) == 0) == (x > y)) { key[i] = y; key[q] = x; }
+                }
+            }
+            __syncthreads();
+        }
+    if (threadIdx.x == 0) {
+        ctr[2] = m ? atomicAdd(B.out_hdr, m) : 0u;
+        B.out_hdr[16 + 2 * g] = ctr[2];
+        B.out_hdr[16 + 2 * g + 1] = m;
+    }
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < m; j += kBB) B.out_keys[ctr[2] + j] = key[j];
+    __syncthreads();
+}
+
+}  // namespace
+
 template <int MaxV, bool Staged>
 __global__ void __launch_bounds__(kBB) k_batched(BatchDev B) {
     using LS = LdsState<MaxV, Staged>;
@@ -289,6 +385,11 @@ __global__ void __launch_bounds__(kBB) k_batched(BatchDev B) {
                 // the LDS state encodes its F: publish the roots of F's trees
                 const int64_t vb = B.vbase[g];
                 for (uint32_t x = threadIdx.x; x < V; x += kBB) B.rootw[vb + x] = (S.q[x] & 0xffffu) ? 1u : 0u;
+                if constexpr (Staged)
+                    if (B.out_hdr) {
+                        __syncthreads();
+                        finish_graph(S, B, g, V, B.noff[g], n1);
+                    }
                 break;
             }
             const int64_t i = node & ~(2 * step - 1);       // left node of this round's pair

@@ -193,6 +193,15 @@ struct BatchDev {
     uint32_t* err;            // bit 0: id out of range; bit 1: region overflow
     const int64_t* vbase;     // [S] first vertex of graph s in the combined numbering
     uint32_t* rootw;          // [sum V] 0 at each root of F of the graph's final certificate, else 1
+    // final step on the device, in the same launch where the contracted
+    // certificate is a forest; null: none.  out_hdr[0]: keys so far, [2], [3]: graphs left to
+    // launch_small_bridges (zero at launch), [16 + 2s], [17 + 2s]: graph s's base
+    // and count; the keys (u << 16 | v) at out_keys; lists of the graphs left, of
+    // up to small_bridges_split_v() vertices and of more
+    uint32_t* out_hdr;
+    uint32_t* out_keys;
+    int32_t *list_a, *list_b;
+    int32_t split_v;
 };
 // big: the kernel for graphs of up to batched_max_v_big() vertices (one
 // workgroup per CU); else up to batched_max_v_dev()
@@ -216,15 +225,13 @@ struct UnionItem {
 // outside [0, V) becomes (-1, -1)), and fills up to the next multiple of `row`
 // with loops
 void launch_union_edges(const UnionItem* d_items, int32_t n, int64_t max_edges, int32_t row, int32_t* dst, hipStream_t s);
-// Final step on the device for the batched path: one workgroup per small graph
-// finds the bridges of node 0's certificate in LDS; keys (u << 16 | v, sorted)
-// go to out_keys at a base taken from out_hdr[0]; out_hdr[16 + 2s] / [17 + 2s]
-// receive graph s's base and count.  out_hdr[0] must be zero at launch.
-// list_a holds the graphs with V <= small_bridges_split_v(), list_b the rest.
-// The two size classes go to streams s (small) and s_b (large) so that they
-// can overlap; the caller orders s_b after earlier work on s and joins it back.
-void launch_small_bridges(const BatchDev& B, const int32_t* list_a, int32_t na, const int32_t* list_b, int32_t nb,
-                          uint32_t* out_hdr, uint32_t* out_keys, int cus, hipStream_t s, hipStream_t s_b);
+// Final step on the device for the graphs k_batched left at B.list_a (at most na,
+// their number at out_hdr[2]) and B.list_b (nb, [3]): one workgroup per graph
+// finds the bridges of node 0's certificate in LDS; keys (sorted per graph) and
+// their place as k_batched writes them.  The two size classes go to streams s
+// (small) and s_b (large) so that they can overlap; the caller orders s_b after
+// earlier work on s and joins it back.
+void launch_small_bridges(const BatchDev& B, int32_t na, int32_t nb, int cus, hipStream_t s, hipStream_t s_b);
 // Allows the kernels above their LDS sizes (once per process, before any launch or capture).
 int prepare_small_bridges();
 int32_t small_bridges_split_v();
