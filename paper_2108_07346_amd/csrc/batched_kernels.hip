@@ -14,6 +14,12 @@
 // high half = x - parent in F' (0 = root; V <= 65,536 keeps both in 16 bits).
 // Two instances: graphs up to 4,096 vertices (three workgroups per CU) and
 // graphs up to 40,944 vertices (the whole LDS of a CU, one workgroup).
+// Graphs with many edges per vertex are not split at all: every chunk would hook
+// its own forests and every merge hook them again, in a chain that the largest
+// graph's chunks set the length of.  One item takes rows spread over the list,
+// about 4V to 6V edges, after which nearly every other edge lies inside a
+// component of F'; a second launch sends the rest past that state in independent
+// runs, and a third offers what those kept to it (launch_batched_long).
 // Hooking is a 32-bit LDS compare-and-swap that changes one half; a swap that
 // fails because the other half moved is simply retried.  The larger root is
 // hooked under the smaller representative, so chains decrease and the loop
@@ -69,24 +75,40 @@ constexpr int kU = 4;
 
 typedef int edge2 __attribute__((ext_vector_type(4), aligned(8)));   // two edges, 8-byte aligned
 
-// The edges of a step: kU pairs per thread.  ok: which of them exist.
-__device__ __forceinline__ uint32_t load_step(const BatchDev& B, int64_t base, int64_t t1, int2 (&e)[2 * kU]) {
-    uint32_t ok = 0;
-    const int64_t i0 = base + 2 * threadIdx.x;
-    if (base + 2 * kBB * kU <= t1) {             // a whole step (the same for every thread)
+// The edges a workgroup certifies: [t0, t1), or of those (stride > 1) the rows
+// of kLongRow that are multiples of stride, counted as one sequence of n.  Rows
+// are no longer than four 128-byte lines: a list sorted by vertex shows as many
+// of its vertices as the sample can hold.
+struct Seq {
+    int64_t t0, t1, n;
+    int32_t stride;
+    __device__ Seq(int64_t a, int64_t b, int32_t s) : t0(a), t1(b), n(b - a), stride(s) {
+        if (s > 1) {
+            const int64_t rows = (b - a + kLongRow - 1) / kLongRow;
+            n = (rows + s - 1) / s * kLongRow;
+        }
+    }
+    __device__ int64_t at(int64_t r) const { return stride > 1 ? t0 + r / kLongRow * stride * kLongRow + r % kLongRow : t0 + r; }
+};
+
+// The edges of a step: kU pairs per thread.  The result tells which of them exist.
+__device__ __forceinline__ uint32_t load_step(const BatchDev& B, const Seq& Q, int64_t rel, int2 (&e)[2 * kU]) {
+    const int64_t r0 = rel + 2 * threadIdx.x;
+    if (rel + 2 * kBB * kU <= (Q.stride > 1 ? Q.n - kLongRow : Q.n)) {      // a whole step (the same for every thread)
 #pragma unroll
         for (int j = 0; j < kU; j++) {
-            const edge2 w = *reinterpret_cast<const edge2*>(B.edges + i0 + j * 2 * kBB);
+            const edge2 w = *reinterpret_cast<const edge2*>(B.edges + Q.at(r0 + j * 2 * kBB));
             e[2 * j] = make_int2(w.x, w.y);
             e[2 * j + 1] = make_int2(w.z, w.w);
         }
         return (1u << 2 * kU) - 1u;
     }
+    uint32_t ok = 0;
 #pragma unroll
     for (int j = 0; j < 2 * kU; j++) {
-        const int64_t i = i0 + (j >> 1) * 2 * kBB + (j & 1);
+        const int64_t r = r0 + (j >> 1) * 2 * kBB + (j & 1), i = Q.at(r);
         e[j] = make_int2(0, 0);
-        if (i < t1) {
+        if (r < Q.n && i < Q.t1) {
             e[j] = B.edges[i];
             ok |= 1u << j;
         }
@@ -99,26 +121,25 @@ __device__ __forceinline__ uint32_t load_step(const BatchDev& B, int64_t base, i
 // too); loaded two to a 16-byte load and tested without 64-bit index arithmetic
 // per edge, they leave the time to the ones that search.
 template <class LS>
-__device__ void certify_chunk(LS& S, const BatchDev& B, int64_t t0, int64_t t1, uint32_t V, int64_t off,
-                              int64_t cap) {
+__device__ void certify_chunk(LS& S, const BatchDev& B, const Seq& Q, uint32_t V, int64_t off, int64_t cap) {
     for (uint32_t x = threadIdx.x; x < V; x += kBB) S.q[x] = 0;
     if (threadIdx.x == 0) S.n12 = 0;
     __syncthreads();
     // compress after the first 2V and 8V edges (dense chunks are then mostly
     // rejected by the shared-parent test)
-    int64_t next_cmp = t0 + 2 * (int64_t)V;
+    int64_t next_cmp = 2 * (int64_t)V;
     constexpr int64_t kStep = (int64_t)kBB * 2 * kU;
     int2 cur[2 * kU], nxt[2 * kU];
-    uint32_t ok = load_step(B, t0, t1, cur), nok = 0;
+    uint32_t ok = load_step(B, Q, 0, cur), nok = 0;
     const lds_half* h2 = reinterpret_cast<const lds_half*>(S.q) + 1;     // x - parent in F' at h2[2 x]
-    for (int64_t base = t0; base < t1; base += kStep) {
-        if (base >= next_cmp) {
+    for (int64_t rel = 0; rel < Q.n; rel += kStep) {
+        if (rel >= next_cmp) {
             __syncthreads();
             lcompress(S.q, V);
             __syncthreads();
-            next_cmp = next_cmp == t0 + 2 * (int64_t)V ? t0 + 8 * (int64_t)V : INT64_MAX;
+            next_cmp = next_cmp == 2 * (int64_t)V ? 8 * (int64_t)V : INT64_MAX;
         }
-        nok = load_step(B, base + kStep, t1, nxt);
+        nok = load_step(B, Q, rel + kStep, nxt);
         if constexpr (LS::kStage >= kBB * 2 * kU) {
             // Where the stage area is free (it only serves merges), each
             // wavefront first applies the shared-parent test to all of its
@@ -371,9 +392,23 @@ __global__ void __launch_bounds__(kBB) k_batched(BatchDev B) {
         const int64_t rb = B.rbase[g];
         auto nidx = [&](int64_t k) { return k ? rb + k - 1 : (int64_t)g; };
         // phase 0: chunk `node` of graph g
-        certify_chunk(S, B, e0 + part_lo(Eg, Mg, node), e0 + part_lo(Eg, Mg, node + 1), V, B.noff[nidx(node)],
-                      B.ncap[nidx(node)]);
+        const int32_t stride = Staged && B.stride ? B.stride[g] : 0;
+        certify_chunk(S, B, Seq(e0 + part_lo(Eg, Mg, node), e0 + part_lo(Eg, Mg, node + 1), max(stride, 1)), V,
+                      B.noff[nidx(node)], B.ncap[nidx(node)]);
         uint32_t n1 = S.n12 & 0xffffu, n2 = S.n12 >> 16;
+        if (stride > 0) {
+            // a long graph: its state goes to memory
+            lcompress(S.q, V);
+            __syncthreads();
+            const int64_t vb = B.vbase[g];
+            for (uint32_t x = threadIdx.x; x < V; x += kBB) B.stq[vb + x] = S.q[x];
+            if (threadIdx.x == 0) {
+                B.ncnt[2 * g] = n1;
+                B.ncnt[2 * g + 1] = n2;
+            }
+            __syncthreads();
+            continue;
+        }
         // merge rounds: climb while this workgroup is the second of a pair to finish
         int64_t step = 1, level = 0, cb = B.cbase[g];
         for (;;) {
@@ -457,6 +492,142 @@ __global__ void __launch_bounds__(kBB) k_batched(BatchDev B) {
         }
         __syncthreads();
     }
+}
+
+namespace {
+
+// A run of a long graph's list (all but the rows its first item took) on a copy
+// of the state after those rows.  An edge whose ends have the same parent in F'
+// is rejected by both forests: two LDS reads, which nearly every edge ends at.
+// The others go through the searches a full wavefront at a time, from a list
+// that each wavefront keeps; those that either forest takes go to the graph's
+// list.  A run keeps at most what its forests still had room for, so the lists
+// are bounded also where the first rows told nothing.
+// What bounds it: HBM.  4,096 graphs of 64 to 4,096 vertices (1.4 GB, of which
+// the 375 long graphs hold 0.94): these runs 165 us (5.7 TB/s) and k_batch_finish
+// 22 us, k_batched's part 310 us; all in chunks and merges, k_batched took 603 us.
+__global__ void __launch_bounds__(kBB) k_batch_runs(BatchDev B) {
+    constexpr int kW = kBB / 64, kCap = 128, kP = 4;
+    __shared__ uint32_t q[kMaxV];
+    __shared__ uint32_t lists[kW][kCap];
+    const int64_t code = B.fitems[blockIdx.x];
+    const int32_t g = (int32_t)(code >> 32);
+    const uint32_t V = (uint32_t)B.V[g], stride = (uint32_t)B.stride[g];
+    const int64_t e0 = B.eoff[2 * g], vb = B.vbase[g], sb = B.sbase[g];
+    const int64_t i0 = (int64_t)(uint32_t)code * kLongRun, i1 = min(i0 + kLongRun, B.eoff[2 * g + 1] - e0);
+    const uint32_t row0 = (uint32_t)(i0 / kLongRow);
+    for (uint32_t x = threadIdx.x; x < V; x += kBB) q[x] = B.stq[vb + x];
+    __syncthreads();
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const lds_half* par = reinterpret_cast<const lds_half*>(q) + 1;
+    uint32_t* wl = lists[wave];
+    uint32_t n = 0;
+    auto offer = [&](uint32_t first, bool mine) {
+        bool a1 = false, a2 = false;
+        uint32_t w = 0;
+        if (mine) {
+            w = wl[first + lane];
+            loffer(q, w & 0xffffu, w >> 16, a1, a2);
+        }
+        const uint64_t m = __ballot(a1 || a2);
+        if (m) {
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&B.scnt[g], (uint32_t)__popcll(m));
+            at = __shfl(at, 0) + lane_rank(m);
+            if (a1 || a2) {
+                if (sb + at < B.sbase[g + 1]) B.surv[sb + at] = w;
+                else atomicOr(B.err, 2u);
+            }
+        }
+    };
+    const uint32_t n_units = (uint32_t)((i1 - i0 + 127) >> 7);         // 128 edges: two rows
+    for (uint32_t u = wave; u < n_units; u += kW * kP) {
+        int2 e[2 * kP];
+        uint32_t ok = 0;
+#pragma unroll
+        for (int j = 0; j < kP; j++) {
+            const uint32_t uu = u + j * kW;
+            const int64_t i = i0 + uu * 128 + 2 * lane;
+            const uint32_t rem = (row0 + 2 * uu) % stride;             // the same for the wavefront
+            e[2 * j] = e[2 * j + 1] = make_int2(0, 0);
+            if (i < i1 && rem != (lane < 32 ? 0u : stride - 1)) {
+                if (i + 1 < i1) {
+                    const edge2 w = *reinterpret_cast<const edge2*>(B.edges + e0 + i);
+                    e[2 * j] = make_int2(w.x, w.y);
+                    e[2 * j + 1] = make_int2(w.z, w.w);
+                    ok |= 3u << (2 * j);
+                } else {
+                    e[2 * j] = B.edges[e0 + i];
+                    ok |= 1u << (2 * j);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2 * kP; j++) {
+            const uint32_t x = (uint32_t)e[j].x, y = (uint32_t)e[j].y;
+            bool hard = false;
+            if (ok >> j & 1u) {
+                if (max(x, y) < V) hard = x - par[2 * x] != y - par[2 * y];
+                else atomicOr(B.err, 1u);
+            }
+            const uint64_t m = __ballot(hard);
+            if (m) {
+                if (hard) wl[n + lane_rank(m)] = x | y << 16;
+                n += (uint32_t)__popcll(m);
+                __builtin_amdgcn_wave_barrier();
+                if (n >= 64) {
+                    n -= 64;
+                    offer(n, true);
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+        }
+    }
+    if (n) offer(0, lane < n);
+}
+
+// The edges that the runs kept offered to the state after the first rows, and
+// the graph's final step.
+__global__ void __launch_bounds__(kBB) k_batch_finish(BatchDev B) {
+    using LS = LdsState<kMaxV, true>;
+    __shared__ LS S;
+    const int32_t g = B.longs[blockIdx.x];
+    const uint32_t V = (uint32_t)B.V[g];
+    const int64_t vb = B.vbase[g], sb = B.sbase[g], off = B.noff[g], cap = B.ncap[g];
+    for (uint32_t x = threadIdx.x; x < V; x += kBB) S.q[x] = B.stq[vb + x];
+    if (threadIdx.x == 0) S.n12 = B.ncnt[2 * g] | B.ncnt[2 * g + 1] << 16;
+    __syncthreads();
+    const uint32_t ns = (uint32_t)min((int64_t)B.scnt[g], B.sbase[g + 1] - sb);
+    uint32_t next = threadIdx.x < ns ? B.surv[sb + threadIdx.x] : 0u;
+    for (uint32_t base = 0; base < ns; base += kBB) {
+        const uint32_t k = base + threadIdx.x, w = next;
+        if (k + kBB < ns) next = B.surv[sb + k + kBB];
+        bool a1 = false, a2 = false;
+        if (k < ns) loffer(S.q, w & 0xffffu, w >> 16, a1, a2);
+        uint32_t p1, p2;
+        reserve2(&S.n12, a1, a2, p1, p2);
+        const int2 e = make_int2((int32_t)(w & 0xffffu), (int32_t)(w >> 16));
+        if (a1) { if (p1 < cap) B.cert[off + p1] = e; else atomicOr(B.err, 2u); }
+        if (a2) { if (p2 < cap) B.cert[off + cap - 1 - p2] = e; else atomicOr(B.err, 2u); }
+    }
+    __syncthreads();
+    const uint32_t n1 = S.n12 & 0xffffu, n2 = S.n12 >> 16;
+    if (threadIdx.x == 0) {
+        if ((int64_t)n1 + n2 > cap) atomicOr(B.err, 2u);
+        B.ncnt[2 * g] = n1;
+        B.ncnt[2 * g + 1] = n2;
+    }
+    for (uint32_t x = threadIdx.x; x < V; x += kBB) B.rootw[vb + x] = (S.q[x] & 0xffffu) ? 1u : 0u;
+    __syncthreads();
+    if (B.out_hdr) finish_graph(S, B, g, V, off, n1);
+}
+
+}  // namespace
+
+void launch_batched_long(const BatchDev& B, hipStream_t s) {
+    if (B.n_long <= 0) return;
+    if (B.n_fitems > 0) hipLaunchKernelGGL(k_batch_runs, dim3((unsigned)B.n_fitems), dim3(kBB), 0, s, B);
+    hipLaunchKernelGGL(k_batch_finish, dim3((unsigned)B.n_long), dim3(kBB), 0, s, B);
 }
 
 void launch_batched(const BatchDev& B, int blocks, hipStream_t s, bool big) {

@@ -202,11 +202,27 @@ struct BatchDev {
     uint32_t* out_keys;
     int32_t *list_a, *list_b;
     int32_t split_v;
+    // long graphs (many edges per vertex): one item takes the rows of kLongRow
+    // edges that are multiples of stride[s], then launch_batched_long the others.
+    // Null stride: none; stride[s] = 0: s is not one of them.
+    const int32_t* stride;    // [S]
+    uint32_t* stq;            // [sum V] the state after those rows
+    const int64_t* sbase;     // [S + 1] places for the edges that the runs keep
+    uint32_t* surv;           // ... u | v << 16
+    uint32_t* scnt;           // [S] ... and their number (zero at launch)
+    const int64_t* fitems;    // [n_fitems] s << 32 | run (of kLongRun edges)
+    const int32_t* longs;     // [n_long]
+    int64_t n_fitems;
+    int32_t n_long;
 };
+constexpr int32_t kLongRow = 64, kLongRun = 32768;
 // big: the kernel for graphs of up to batched_max_v_big() vertices (one
 // workgroup per CU); else up to batched_max_v_dev()
 void launch_batched(const BatchDev& B, int blocks, hipStream_t s, bool big = false);
 int32_t batched_max_v_big();
+// the long graphs' remaining rows, then their certificates (and, with out_hdr,
+// their final step); after launch_batched on the same stream
+void launch_batched_long(const BatchDev& B, hipStream_t s);
 // one device edge list to gather: n edges from src to edge offset `at`
 struct GatherItem {
     const int32_t* src;

@@ -150,6 +150,7 @@ int64_t lane_need(const Request& r) {
     const int64_t V = r.V;
     const int64_t regions = std::min<int64_t>(r.E * (R + 1), 2 * V * M);
     int64_t b = 8 * r.E + 8 * regions + (96 + 4 * (int64_t)R) * M + 8 * V + 8192;
+    b += 4 * V + r.E / 2048 + 8192;        // a long graph's state and runs (what they keep is less than the regions)
     if (r.V > batched_max_v_dev())
         b += 8 * r.E + 72 * V + 4 * device_bridges_words(r.V) + 4 * (int64_t)contract_words() + 16384 +
              r.E / 1024;       // rows filled up, row items
