@@ -18,12 +18,10 @@
 // by pointer jumping gives every arc its position in its tour.
 //
 // Launches: one clear, the arc lists, the ranking (one launch whose threads
-// jump asynchronously), tour sizes, downward arcs, one scan, preorder numbers,
-// the F' ranges, the range tables (three launches up to 2^24 vertices), the test
-// -- twelve in all.
+// jump asynchronously; four with splitters past 2^18 arcs), tour sizes, downward
+// arcs, one scan, preorder numbers, the F' ranges, the range tables (three
+// launches up to 2^24 vertices), the test -- twelve in all.
 #include <hip/hip_runtime.h>
-
-#include <mutex>
 
 #include "device_util.hpp"
 #include "internal.hpp"
@@ -187,53 +185,134 @@ __device__ __forceinline__ uint64_t tour_jump(const int2* f1, const int32_t* fir
     return d >= (uint64_t)A ? lk_pack(~a, (uint32_t)A) : lk_pack(lk_lo(u), d);
 }
 
-// K arcs per thread held in registers (arcs t, t + stride, ...).  (Ranking
-// inside one XCD, with plain loads through its L2, measured slower: dense
-// 0.156 against 0.119 ms for the whole bridge step.)
-template <int K>
+// One arc per thread, its word in a register.  (Ranking inside one XCD, with
+// plain loads through its L2, measured slower: dense 0.156 against 0.119 ms for
+// the whole bridge step.)
 __global__ void __launch_bounds__(kT) k_rank(const int2* f1, const uint32_t* cnt, const int32_t* first,
                                              const int32_t* nxt, const uint32_t* q, int32_t qs, uint64_t* link) {
     const int64_t A = 2 * (int64_t)cnt[0];
-    const int64_t t = blockIdx.x * (int64_t)kT + threadIdx.x, stride = (int64_t)gridDim.x * kT;
-    uint64_t w[K];
-    uint32_t live = 0;
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        const int64_t a = t + k * stride;
-        w[k] = 0;
-        if (a < A) {
-            w[k] = tour_step(f1, first, nxt, q, qs, (int32_t)a);
-            lk_store(link + a, w[k]);
-            if (lk_lo(w[k]) >= 0) live |= 1u << k;
-        }
+    const int64_t a = blockIdx.x * (int64_t)kT + threadIdx.x;
+    if (a >= A) return;
+    uint64_t w = tour_step(f1, first, nxt, q, qs, (int32_t)a);
+    lk_store(link + a, w);
+    while (lk_lo(w) >= 0) {
+        w = tour_jump(f1, first, nxt, q, qs, link, A, (int32_t)a, w);
+        lk_store(link + a, w);
     }
-    while (live) {
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            if (!((live >> k) & 1u)) continue;
-            w[k] = tour_jump(f1, first, nxt, q, qs, link, A, (int32_t)(t + k * stride), w[k]);
-            lk_store(link + t + k * stride, w[k]);
-            if (lk_lo(w[k]) < 0) live &= ~(1u << k);
+}
+
+// Long lists: every jump of every arc is a random line, about log2 of the tour
+// of them per arc.  Instead one arc of every kGroup (a hashed place in its group,
+// so that no input order lines the gaps up) is a splitter.  k_succ writes every
+// arc's successor; k_walk follows each splitter's arcs to the next splitter, one
+// load per arc, and leaves in each arc's word the splitter and its distance from
+// it; k_rank_split jumps over the splitters alone; k_spread adds the two up.
+// The arcs before a tour's first splitter are walked from the tour's head, twice:
+// the first walk finds the splitter (or the tour's end), the second writes.
+// What bounds it: random lines, about three per arc in k_walk and k_spread and
+// log2(splitters) per splitter.  At 1.9 M arcs: k_succ 30, k_walk 85,
+// k_rank_split 71, k_spread 21 us (groups of 8: 69 + 129, of 32: 119 + 41)
+// against 313 us for jumps of every arc; the tour of a path over 10^6 vertices,
+// all in one list, 2.1 ms for the whole query.
+constexpr int32_t kGroup = 16;
+
+__device__ __forceinline__ int32_t splitter_of(int32_t g) {
+    return g * kGroup + (int32_t)(((uint32_t)g * 0x9E3779B1u) >> 16) % kGroup;
+}
+__device__ __forceinline__ bool is_splitter(int32_t a) { return splitter_of(a / kGroup) == a; }
+
+__global__ void __launch_bounds__(kT) k_succ(const int2* f1, const uint32_t* cnt, const int32_t* first,
+                                             const int32_t* nxt, const uint32_t* q, int32_t qs, uint64_t* link) {
+    const int64_t A = 2 * (int64_t)cnt[0];
+    GRID_LOOP(a, A) link[a] = tour_step(f1, first, nxt, q, qs, (int32_t)a);
+}
+
+// Every arc has one predecessor at most and a walk ends at the first splitter,
+// so no arc is walked by two threads and no walk goes round.
+__global__ void __launch_bounds__(kT) k_walk(const uint32_t* cnt, const int32_t* first, const uint32_t* q, int32_t qs,
+                                             int32_t V, uint64_t* link) {
+    const int32_t A = 2 * (int32_t)cnt[0], G = (A + kGroup - 1) / kGroup;
+    GRID_LOOP(i, (int64_t)G + V) {
+        if (i < G) {
+            const int32_t s = splitter_of((int32_t)i);
+            if (s >= A) continue;
+            uint64_t w = link[s];
+            uint32_t d = 0;
+            for (int32_t at = lk_lo(w); at >= 0; at = lk_lo(w)) {
+                d++;
+                if (is_splitter(at)) { w = lk_pack(at, 0); break; }
+                w = link[at];
+                link[at] = lk_pack(s, d);
+            }
+            link[s] = lk_pack(lk_lo(w), d);                            // the next splitter, or ~ the tour's last arc
+        } else {
+            const int32_t v = (int32_t)(i - G);
+            if (first[v] == 0 || q[qs * (size_t)v] != 0) continue;
+            const int32_t h = first[v] - 1;
+            if (is_splitter(h)) continue;
+            int32_t at = h;
+            uint32_t d = 0;
+            for (int32_t n = h;;) {
+                n = lk_lo(link[at]);
+                if (n < 0) break;
+                at = n;
+                d++;
+                if (is_splitter(at)) break;
+            }
+            // d arcs on lies the splitter at, or the last arc at
+            const bool split = is_splitter(at);
+            for (int32_t x = h; d != 0 || !split; d--) {
+                const int32_t n = lk_lo(link[x]);
+                link[x] = split ? lk_pack(at, 0u - d) : lk_pack(~at, d);
+                if (d == 0) break;
+                x = n;
+            }
         }
     }
 }
 
-// any number of arcs per thread, their words kept in memory (lists longer
-// than the resident threads can hold in registers)
-__global__ void __launch_bounds__(kT) k_rank_mem(const int2* f1, const uint32_t* cnt, const int32_t* first,
-                                                 const int32_t* nxt, const uint32_t* q, int32_t qs, uint64_t* link) {
+__global__ void __launch_bounds__(kT) k_rank_split(const uint32_t* cnt, uint64_t* link) {
     const int64_t A = 2 * (int64_t)cnt[0];
-    const int64_t t = blockIdx.x * (int64_t)kT + threadIdx.x, stride = (int64_t)gridDim.x * kT;
-    for (int64_t a = t; a < A; a += stride) lk_store(link + a, tour_step(f1, first, nxt, q, qs, (int32_t)a));
+    const int32_t G = (int32_t)((A + kGroup - 1) / kGroup);
+    const int32_t t = (int32_t)(blockIdx.x * kT + threadIdx.x), stride = (int32_t)(gridDim.x * kT);
+    if (t + stride >= G) {                                             // one splitter at most: its word in registers
+        const int32_t a = t < G ? splitter_of(t) : INT32_MAX;
+        if (a >= A) return;
+        uint64_t w = lk_load(link + a);
+        while (lk_lo(w) >= 0) {
+            const uint64_t u = lk_load(link + lk_lo(w));
+            const uint64_t d = (uint64_t)lk_dist(w) + lk_dist(u);
+            w = d >= (uint64_t)A ? lk_pack(~a, (uint32_t)A) : lk_pack(lk_lo(u), (uint32_t)d);
+            lk_store(link + a, w);
+        }
+        return;
+    }
     for (bool live = true; live;) {
         live = false;
-        for (int64_t a = t; a < A; a += stride) {
+        for (int32_t g = t; g < G; g += stride) {
+            const int32_t a = splitter_of(g);
+            if (a >= A) continue;
             uint64_t w = lk_load(link + a);
             if (lk_lo(w) < 0) continue;
-            w = tour_jump(f1, first, nxt, q, qs, link, A, (int32_t)a, w);
+            const uint64_t u = lk_load(link + lk_lo(w));
+            const uint64_t d = (uint64_t)lk_dist(w) + lk_dist(u);
+            w = d >= (uint64_t)A ? lk_pack(~a, (uint32_t)A) : lk_pack(lk_lo(u), (uint32_t)d);
             lk_store(link + a, w);
             live |= lk_lo(w) >= 0;
         }
+    }
+}
+
+// A word still without its tour's end here is an ordinary arc's: splitter and
+// distance from it.  (On an inconsistent forest a cycle without a splitter keeps
+// its successors: closed at A steps, a position no tour has.)
+__global__ void __launch_bounds__(kT) k_spread(const uint32_t* cnt, uint64_t* link) {
+    const int64_t A = 2 * (int64_t)cnt[0];
+    GRID_LOOP(a, A) {
+        const uint64_t w = link[a];
+        if (lk_lo(w) < 0) continue;
+        const uint64_t u = link[lk_lo(w)];
+        link[a] = lk_lo(u) < 0 ? lk_pack(lk_lo(u), lk_dist(u) - lk_dist(w)) : lk_pack(~(int32_t)a, (uint32_t)A);
     }
 }
 
@@ -919,41 +998,34 @@ static void order_keys(const BridgeWs& W, int32_t V, const uint64_t* keys, const
     hipLaunchKernelGGL(k_order_runs, dim3(grid_for(V)), dim3(kT), 0, s, n, (const uint32_t*)cnt, V, out, done);
 }
 
+// Jumps of every arc while they are few (every thread resident), splitters past
+// 2^18 arcs: 400,000 arcs 384 against 409 us for a whole query, 800,000 555
+// against 670; 200,000 the same (four launches against one).
+constexpr int64_t kRankJump = int64_t(1) << 18;
+
+static void launch_rank(const int2* f1, const uint32_t* cnt, const int32_t* first, const int32_t* nxt,
+                        const uint32_t* q, int32_t qs, int32_t V, uint64_t* link, int64_t A, hipStream_t s) {
+    if (A <= kRankJump) {
+        hipLaunchKernelGGL(k_rank, dim3((unsigned)cdiv(A, kT)), dim3(kT), 0, s, f1, cnt, first, nxt, q, qs, link);
+        return;
+    }
+    hipLaunchKernelGGL(k_succ, dim3(grid_for(A)), dim3(kT), 0, s, f1, cnt, first, nxt, q, qs, link);
+    hipLaunchKernelGGL(k_walk, dim3(grid_for(A / kGroup + V)), dim3(kT), 0, s, cnt, first, q, qs, V, link);
+    hipLaunchKernelGGL(k_rank_split, dim3((unsigned)std::min<int64_t>(8 * std::max(1, g_cus), cdiv(A, kGroup * kT))),
+                       dim3(kT), 0, s, cnt, link);
+    hipLaunchKernelGGL(k_spread, dim3(grid_for(A)), dim3(kT), 0, s, cnt, link);
+}
+
 // The part shared by the bridge and articulation-point tests: adjacency of F,
 // Euler tours ranked, preorder numbers, subtree sizes, min/max preorder numbers
 // reached through F' and their range tables.
-// The ranking launch: K arcs per thread in registers while the grid stays
-// within what the device holds resident at once, else the words in memory.
-static void launch_rank(const int2* f1, const uint32_t* cnt, const int32_t* first, const int32_t* nxt,
-                        const uint32_t* q, int32_t qs, uint64_t* link, int64_t A, hipStream_t s) {
-    static int resident = 0;      // workgroups of k_rank resident on the device
-    static std::once_flag once;
-    std::call_once(once, [] {
-        int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rank<1>, kT, 0) != hipSuccess || per_cu < 1) {
-            (void)hipGetLastError();
-            per_cu = 1;
-        }
-        resident = std::max(1, per_cu) * std::max(1, g_cus);
-    });
-    const int64_t cap = (int64_t)resident * kT;   // threads
-    if (A <= cap)
-        hipLaunchKernelGGL(k_rank<1>, dim3((unsigned)cdiv(A, kT)), dim3(kT), 0, s, f1, cnt, first, nxt, q, qs, link);
-    else if (A <= 2 * cap)
-        hipLaunchKernelGGL(k_rank<2>, dim3((unsigned)cdiv(A, 2 * kT)), dim3(kT), 0, s, f1, cnt, first, nxt, q, qs, link);
-    else if (A <= 4 * cap)
-        hipLaunchKernelGGL(k_rank<4>, dim3((unsigned)cdiv(A, 4 * kT)), dim3(kT), 0, s, f1, cnt, first, nxt, q, qs, link);
-    else
-        hipLaunchKernelGGL(k_rank_mem, dim3((unsigned)resident), dim3(kT), 0, s, f1, cnt, first, nxt, q, qs, link);
-}
-
 static BridgeWs number_vertices(const int2* f1, const uint32_t* cnt, const uint32_t* q, int32_t qs, int32_t V, int32_t* ws,
                                 hipStream_t s) {
     const int64_t A = 2 * (int64_t)std::max(V - 1, 1);
     const BridgeWs W = carve(ws, V);
     hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(W.zero_words)), dim3(kT), 0, s, W.first, W.zero_words);
     hipLaunchKernelGGL(k_link, dim3(grid_for(A)), dim3(kT), 0, s, f1, cnt, W.first, W.nxt);
-    launch_rank(f1, cnt, W.first, W.nxt, q, qs, W.link, A, s);
+    launch_rank(f1, cnt, W.first, W.nxt, q, qs, V, W.link, A, s);
     hipLaunchKernelGGL(k_tours, dim3((unsigned)cdiv(V, kSB)), dim3(kT), 0, s, W.first, (const uint64_t*)W.link, q, qs, V,
                        W.tour_len, W.tree_n, W.tour_base, W.vbase, W.st_tours, reinterpret_cast<uint32_t*>(W.tickets) + 1);
     hipLaunchKernelGGL(k_down, dim3(grid_for(A)), dim3(kT), 0, s, f1, cnt, (const uint64_t*)W.link, W.tour_len,
