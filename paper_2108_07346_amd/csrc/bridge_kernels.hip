@@ -18,7 +18,7 @@
 // by pointer jumping gives every arc its position in its tour.
 //
 // Launches: one clear, the arc lists, the ranking (one launch whose threads
-// jump asynchronously; four with splitters past 2^18 arcs), tour sizes, downward
+// jump asynchronously; four with splitters past 2^17 arcs), tour sizes, downward
 // arcs, one scan, preorder numbers, the F' ranges, the range tables (three
 // launches up to 2^24 vertices), the test -- twelve in all.
 #include <hip/hip_runtime.h>
@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(kT) k_rank(const int2* f1, const uint32_t* cnt
 }
 
 // Long lists: every jump of every arc is a random line, about log2 of the tour
-// of them per arc.  Instead one arc of every kGroup (a hashed place in its group,
+// of them per arc.  Instead one arc of every 8 or 16 (a hashed place in its group,
 // so that no input order lines the gaps up) is a splitter.  k_succ writes every
 // arc's successor; k_walk follows each splitter's arcs to the next splitter, one
 // load per arc, and leaves in each arc's word the splitter and its distance from
@@ -213,13 +213,13 @@ __global__ void __launch_bounds__(kT) k_rank(const int2* f1, const uint32_t* cnt
 // log2(splitters) per splitter.  At 1.9 M arcs: k_succ 30, k_walk 85,
 // k_rank_split 71, k_spread 21 us (groups of 8: 69 + 129, of 32: 119 + 41)
 // against 313 us for jumps of every arc; the tour of a path over 10^6 vertices,
-// all in one list, 2.1 ms for the whole query.
-constexpr int32_t kGroup = 16;
-
+// all in one list, 1.2 ms for the whole query.
+template <int kGroup>
 __device__ __forceinline__ int32_t splitter_of(int32_t g) {
     return g * kGroup + (int32_t)(((uint32_t)g * 0x9E3779B1u) >> 16) % kGroup;
 }
-__device__ __forceinline__ bool is_splitter(int32_t a) { return splitter_of(a / kGroup) == a; }
+template <int kGroup>
+__device__ __forceinline__ bool is_splitter(int32_t a) { return splitter_of<kGroup>(a / kGroup) == a; }
 
 __global__ void __launch_bounds__(kT) k_succ(const int2* f1, const uint32_t* cnt, const int32_t* first,
                                              const int32_t* nxt, const uint32_t* q, int32_t qs, uint64_t* link) {
@@ -229,18 +229,19 @@ __global__ void __launch_bounds__(kT) k_succ(const int2* f1, const uint32_t* cnt
 
 // Every arc has one predecessor at most and a walk ends at the first splitter,
 // so no arc is walked by two threads and no walk goes round.
+template <int kGroup>
 __global__ void __launch_bounds__(kT) k_walk(const uint32_t* cnt, const int32_t* first, const uint32_t* q, int32_t qs,
                                              int32_t V, uint64_t* link) {
     const int32_t A = 2 * (int32_t)cnt[0], G = (A + kGroup - 1) / kGroup;
     GRID_LOOP(i, (int64_t)G + V) {
         if (i < G) {
-            const int32_t s = splitter_of((int32_t)i);
+            const int32_t s = splitter_of<kGroup>((int32_t)i);
             if (s >= A) continue;
             uint64_t w = link[s];
             uint32_t d = 0;
             for (int32_t at = lk_lo(w); at >= 0; at = lk_lo(w)) {
                 d++;
-                if (is_splitter(at)) { w = lk_pack(at, 0); break; }
+                if (is_splitter<kGroup>(at)) { w = lk_pack(at, 0); break; }
                 w = link[at];
                 link[at] = lk_pack(s, d);
             }
@@ -249,7 +250,7 @@ __global__ void __launch_bounds__(kT) k_walk(const uint32_t* cnt, const int32_t*
             const int32_t v = (int32_t)(i - G);
             if (first[v] == 0 || q[qs * (size_t)v] != 0) continue;
             const int32_t h = first[v] - 1;
-            if (is_splitter(h)) continue;
+            if (is_splitter<kGroup>(h)) continue;
             int32_t at = h;
             uint32_t d = 0;
             for (int32_t n = h;;) {
@@ -257,10 +258,10 @@ __global__ void __launch_bounds__(kT) k_walk(const uint32_t* cnt, const int32_t*
                 if (n < 0) break;
                 at = n;
                 d++;
-                if (is_splitter(at)) break;
+                if (is_splitter<kGroup>(at)) break;
             }
             // d arcs on lies the splitter at, or the last arc at
-            const bool split = is_splitter(at);
+            const bool split = is_splitter<kGroup>(at);
             for (int32_t x = h; d != 0 || !split; d--) {
                 const int32_t n = lk_lo(link[x]);
                 link[x] = split ? lk_pack(at, 0u - d) : lk_pack(~at, d);
@@ -271,12 +272,13 @@ __global__ void __launch_bounds__(kT) k_walk(const uint32_t* cnt, const int32_t*
     }
 }
 
+template <int kGroup>
 __global__ void __launch_bounds__(kT) k_rank_split(const uint32_t* cnt, uint64_t* link) {
     const int64_t A = 2 * (int64_t)cnt[0];
     const int32_t G = (int32_t)((A + kGroup - 1) / kGroup);
     const int32_t t = (int32_t)(blockIdx.x * kT + threadIdx.x), stride = (int32_t)(gridDim.x * kT);
     if (t + stride >= G) {                                             // one splitter at most: its word in registers
-        const int32_t a = t < G ? splitter_of(t) : INT32_MAX;
+        const int32_t a = t < G ? splitter_of<kGroup>(t) : INT32_MAX;
         if (a >= A) return;
         uint64_t w = lk_load(link + a);
         while (lk_lo(w) >= 0) {
@@ -290,7 +292,7 @@ __global__ void __launch_bounds__(kT) k_rank_split(const uint32_t* cnt, uint64_t
     for (bool live = true; live;) {
         live = false;
         for (int32_t g = t; g < G; g += stride) {
-            const int32_t a = splitter_of(g);
+            const int32_t a = splitter_of<kGroup>(g);
             if (a >= A) continue;
             uint64_t w = lk_load(link + a);
             if (lk_lo(w) < 0) continue;
@@ -998,10 +1000,20 @@ static void order_keys(const BridgeWs& W, int32_t V, const uint64_t* keys, const
     hipLaunchKernelGGL(k_order_runs, dim3(grid_for(V)), dim3(kT), 0, s, n, (const uint32_t*)cnt, V, out, done);
 }
 
-// Jumps of every arc while they are few (every thread resident), splitters past
-// 2^18 arcs: 400,000 arcs 384 against 409 us for a whole query, 800,000 555
-// against 670; 200,000 the same (four launches against one).
-constexpr int64_t kRankJump = int64_t(1) << 18;
+// Jumps of every arc while they are few (every thread resident), else splitters,
+// more of them where a walk's length is what the launch takes.  All four kernels,
+// jumps / groups of 8 / of 16: 100,000 arcs 39 / 58 / 74 us, 200,000
+// 74 / 57 / 81, 400,000 101 / 78 / 85, 800,000 - / 121 / 111.
+constexpr int64_t kRankJump = int64_t(1) << 17, kRankShort = int64_t(1) << 19;
+
+template <int kGroup>
+static void launch_split(const uint32_t* cnt, const int32_t* first, const uint32_t* q, int32_t qs, int32_t V,
+                         uint64_t* link, int64_t A, hipStream_t s) {
+    hipLaunchKernelGGL(k_walk<kGroup>, dim3(grid_for(A / kGroup + V)), dim3(kT), 0, s, cnt, first, q, qs, V, link);
+    hipLaunchKernelGGL(k_rank_split<kGroup>,
+                       dim3((unsigned)std::min<int64_t>(8 * std::max(1, g_cus), cdiv(A, kGroup * kT))), dim3(kT), 0, s,
+                       cnt, link);
+}
 
 static void launch_rank(const int2* f1, const uint32_t* cnt, const int32_t* first, const int32_t* nxt,
                         const uint32_t* q, int32_t qs, int32_t V, uint64_t* link, int64_t A, hipStream_t s) {
@@ -1010,9 +1022,8 @@ static void launch_rank(const int2* f1, const uint32_t* cnt, const int32_t* firs
         return;
     }
     hipLaunchKernelGGL(k_succ, dim3(grid_for(A)), dim3(kT), 0, s, f1, cnt, first, nxt, q, qs, link);
-    hipLaunchKernelGGL(k_walk, dim3(grid_for(A / kGroup + V)), dim3(kT), 0, s, cnt, first, q, qs, V, link);
-    hipLaunchKernelGGL(k_rank_split, dim3((unsigned)std::min<int64_t>(8 * std::max(1, g_cus), cdiv(A, kGroup * kT))),
-                       dim3(kT), 0, s, cnt, link);
+    if (A <= kRankShort) launch_split<8>(cnt, first, q, qs, V, link, A, s);
+    else launch_split<16>(cnt, first, q, qs, V, link, A, s);
     hipLaunchKernelGGL(k_spread, dim3(grid_for(A)), dim3(kT), 0, s, cnt, link);
 }
 
