@@ -45,8 +45,8 @@ def check(ctx, e, V, M=16, certificate=False):
     return d, want
 
 
-# the stages change at 4 V and 16 V edges
-@pytest.mark.parametrize("E", [1, 511, 513, 4 * 45_001, 4 * 45_001 + 1, 16 * 45_001, 16 * 45_001 + 1, 20 * 45_001 + 77])
+# the stages change at 3 V, 4 V and 16 V edges
+@pytest.mark.parametrize("E", [1, 511, 513, 3 * 45_001, 3 * 45_001 + 1, 4 * 45_001, 4 * 45_001 + 1, 16 * 45_001, 16 * 45_001 + 1, 20 * 45_001 + 77])
 def test_stage_limits(ctx, monkeypatch, E):
     monkeypatch.setenv("BR_FUSE", "1")
     V = 45_001
