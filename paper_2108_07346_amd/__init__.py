@@ -204,7 +204,7 @@ class Context:
     def _cert_result(self, out, counts, stream):
         import torch
         if stream is None:
-            torch.cuda.current_stream().synchronize()
+            pass                                # the copy of the counts waits: it is on the same stream
         elif hasattr(stream, "synchronize"):
             stream.synchronize()
         else:                                   # a raw hipStream_t handle
@@ -220,7 +220,7 @@ class Context:
         ptr, E = _edges_arg(edges)
         cap = max(min(E, 2 * (int(V) - 1)), 1)
         out = torch.empty((cap, 2), dtype=torch.int32, device=edges.device)
-        counts = torch.zeros(3, dtype=torch.int64, device=edges.device)
+        counts = torch.empty(3, dtype=torch.int64, device=edges.device)      # all written by the call
         _check(self._lib.br_cert_build(self._h, ptr, E, int(V), int(M), ctypes.c_void_p(out.data_ptr()), cap,
                                        ctypes.c_void_p(counts.data_ptr()), _stream(stream)))
         return self._cert_result(out, counts, stream)
@@ -248,7 +248,7 @@ class Context:
         pb, Eb = _edges_arg(b)
         cap = max(min(Ea + Eb, 2 * (int(V) - 1)), 1)
         out = torch.empty((cap, 2), dtype=torch.int32, device=a.device)
-        counts = torch.zeros(3, dtype=torch.int64, device=a.device)
+        counts = torch.empty(3, dtype=torch.int64, device=a.device)
         _check(self._lib.br_cert_merge(self._h, pa, Ea, pb, Eb, int(V), ctypes.c_void_p(out.data_ptr()), cap,
                                        ctypes.c_void_p(counts.data_ptr()), _stream(stream)))
         return self._cert_result(out, counts, stream)
