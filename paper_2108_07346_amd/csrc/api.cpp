@@ -66,8 +66,8 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     const int64_t bound = 2 * (int64_t(V) - 1);
     // The whole list in one pass unless a plan is asked for by name: on one
     // GPU the chunks' own certificates and their merges only add work (large
-    // workload: M = 4096 / 64 / 4 chunks 120 / 18 / 12 ms per query; dense
-    // workload: M = 16 / 1 chunks 0.59 / 0.37 ms).
+    // workload: M = 4096 / 64 / 4 chunks 120 / 18 / 12 ms per query, one pass
+    // 1.8; dense workload: M = 16 / 1 chunks 0.59 / 0.37 ms, one pass 0.20).
     const int lds_want = knob("BR_LDS", "lds", -1);
     const bool plan_env = env_int("BR_SOLO", -1) >= 0 || env_int("BR_LDS", -1) >= 0;   // wins over a tuned "fuse"
     const int fuse = plan_env ? env_int("BR_FUSE", -1) : knob("BR_FUSE", "fuse", -1);
@@ -90,8 +90,16 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
         P.qs = (int64_t)V * 32 <= (int64_t(128) << 20) ? 8 : 2;
         P.table = knob("", "table", 1) != 0;
         plan_fused(P);
-        // on a dense list nearly every edge of F lies inside a component of F'
-        P.contract = V <= 4096 || E >= 6 * (int64_t)V;
+        // On a dense list nearly every edge of F lies inside a component of F'.
+        // Of random lists about V(1 + d)exp(-d), d = 2E / V, do not, and the
+        // contraction holds 16,384: 3V edges up to 2^18 vertices, 4V up to 2^21.
+        // Contracted / by tours, us per query: V = 20,000 with 2V edges 174 / 158,
+        // 3V 114 / 151, 4V 111 / 161; V = 100,000 329 / 298, 206 / 268, 158 / 264;
+        // V = 262,144 with 3V 389 / 489; V = 1,000,000 with 3V 1,304 / 1,188 (over the
+        // limit, so both steps ran), 4V 612 / 1,184; V = 4,000,000 with 4V the same
+        // (4,280 / 4,119).
+        P.contract = V <= 4096 || E >= 6 * (int64_t)V || (E >= 4 * (int64_t)V && V <= (1 << 21)) ||
+                     (E >= 3 * (int64_t)V && V <= (1 << 18));
         return P;
     }
     while ((int64_t(1) << P.rounds) < M) P.rounds++;

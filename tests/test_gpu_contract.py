@@ -110,3 +110,16 @@ def test_small_graphs_of_any_density(ctx, monkeypatch):
     for V in (2, 50, 4096):
         for name, h in shapes(V, rng):
             check(ctx, h.astype(np.int32), V, name)
+
+
+# sparse lists at the edges per vertex from which the contraction is tried
+@pytest.mark.parametrize("V, E", [(20_000, 60_000), (20_000, 59_999), (262_144, 786_432), (262_145, 786_435),
+                                  (300_000, 1_200_000), (300_000, 1_199_999)])
+def test_sparse_limits(ctx, V, E):
+    rng = np.random.default_rng(E)
+    check(ctx, rng.integers(0, V, size=(E, 2)).astype(np.int32), V, "random")
+    # a tree takes a third of the edges: every edge of it is a bridge, more than the contraction holds at the larger sizes
+    n = E // 3
+    t = tree(min(n, V // 2), rng)
+    e = np.concatenate([t, V // 2 + rng.integers(0, V - V // 2, size=(E - len(t), 2))])
+    check(ctx, rng.permutation(V)[e][rng.permutation(E)].astype(np.int32), V, "tree and random")
