@@ -1,8 +1,9 @@
 """Benchmark of the bridge path on one MI355X.
 
-One step = one br_bridges_find call: per-chunk certificates (phase 0), the
-merge rounds, the bridges of the merged certificate (the library's default
-bridge step on the GPU), the copy of the bridges to the host and the
+One step = one br_bridges_find call: the certificate of the list (by default
+one pass that folds the merge tree over the M chunks; per-chunk certificates
+and merge rounds where a tree plan is chosen), its bridges (the library's
+default final step on the GPU), the copy of the bridges to the host and the
 canonical sort -- every step of the path, on input already resident in HBM.
 The same steps with Algorithm 1's depth-first search on the host as the final
 step are reported under "detail".  Prints one JSON line (rank 0, N = 1).
@@ -48,11 +49,11 @@ PEAK_GBS = 8000.0
 # the roofline line times for each: the launches from the first certificate
 # kernel to the end of phase 0 (of the merge levels inside the kernel, for the
 # one-workgroup-per-node plan)
-PLAN_NAMES = {0: "many workgroups per chunk", 1: "one workgroup per node", 2: "whole tree in LDS",
+PLAN_NAMES = {0: "many workgroups per chunk", 1: "one workgroup per node", 2: "one pass, small graph",
               3: "whole list in one pass"}
 UNIT_NAMES = {0: "phase 0 per query (k_phase0 stages and the compressions between them)",
               1: "k_solo per query (phase 0 and the merge levels it runs, one workgroup per node)",
-              2: "k_batched per query (phase 0 and every merge, in LDS)",
+              2: "certificate per query (k_lds_cert, with k_filter past its whole lists; the one-pass kernels past 8,192 vertices)",
               3: "certificate per query (k_rows stages, path compressions, code table and k_filter)"}
 CSRC = os.path.join(ROOT, "paper_2108_07346_amd", "csrc")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
@@ -219,7 +220,7 @@ def bench_batched(args):
         "config": {"workload": "batched", "graphs": b.G, "E": E, "chunk_edges": chunk, "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / PEAK_GBS, "traffic": load_traffic("batched", 0),
-                     "kernel": "k_batched (persistent, all graphs)", "algorithmic_bytes_per_launch": 8 * E},
+                     "kernel": "k_batched, k_batch_runs and k_batch_finish (all graphs)", "algorithmic_bytes_per_launch": 8 * E},
         "cpu_baseline": cpu,
         "detail": {"phases_ms": {k: round(v, 4) for k, v in phases.items()},
                    "one_call_per_graph": {"ms": 1000 * t_base, "edges_per_s": E / t_base,

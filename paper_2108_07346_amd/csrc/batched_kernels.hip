@@ -1,4 +1,5 @@
-// Batched certificates for many small graphs in one persistent launch.
+// Batched certificates for many small graphs in one persistent launch (and two
+// more for those with long lists).
 //
 // Work items are (graph, chunk) pairs: graph g's edge list is split into M_g
 // chunks exactly as in the paper's phase tree (Section III), and the items are
@@ -13,7 +14,9 @@
 // LDS union-find: one 32-bit word per vertex, low half = x - parent in F,
 // high half = x - parent in F' (0 = root; V <= 65,536 keeps both in 16 bits).
 // Two instances: graphs up to 4,096 vertices (three workgroups per CU) and
-// graphs up to 40,944 vertices (the whole LDS of a CU, one workgroup).
+// graphs up to 40,944 vertices (the whole LDS of a CU, one workgroup; only with
+// the search on the host, else those are one query over their union).
+//
 // Graphs with many edges per vertex are not split at all: every chunk would hook
 // its own forests and every merge hook them again, in a chain that the largest
 // graph's chunks set the length of.  One item takes rows spread over the list,
