@@ -18,7 +18,7 @@
 // by pointer jumping gives every arc its position in its tour.
 //
 // Launches: one clear, the arc lists, the ranking (one launch whose threads
-// jump asynchronously; four with splitters past 2^17 arcs), tour sizes, downward
+// jump asynchronously; four with splitters past 160,000 arcs), tour sizes, downward
 // arcs, one scan, preorder numbers, the F' ranges, the range tables (three
 // launches up to 2^24 vertices), the test -- twelve in all.
 #include <hip/hip_runtime.h>
@@ -1002,9 +1002,9 @@ static void order_keys(const BridgeWs& W, int32_t V, const uint64_t* keys, const
 
 // Jumps of every arc while they are few (every thread resident), else splitters,
 // more of them where a walk's length is what the launch takes.  All four kernels,
-// jumps / groups of 8 / of 16: 100,000 arcs 39 / 58 / 74 us, 200,000
-// 74 / 57 / 81, 400,000 101 / 78 / 85, 800,000 - / 121 / 111.
-constexpr int64_t kRankJump = int64_t(1) << 17, kRankShort = int64_t(1) << 19;
+// jumps / groups of 8 / of 16: 100,000 arcs 39 / 58 / 74 us, 133,000 50 / 58 / -,
+// 200,000 74 / 57 / 81, 400,000 101 / 78 / 85, 800,000 - / 121 / 111.
+constexpr int64_t kRankJump = 160'000, kRankShort = int64_t(1) << 19;
 
 template <int kGroup>
 static void launch_split(const uint32_t* cnt, const int32_t* first, const uint32_t* q, int32_t qs, int32_t V,

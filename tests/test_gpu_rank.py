@@ -42,7 +42,7 @@ def forest(kind, V, rng):
     return e
 
 
-@pytest.mark.parametrize("V", [65_537, 65_538, 262_145, 262_146])
+@pytest.mark.parametrize("V", [80_001, 80_002, 262_145, 262_146])
 @pytest.mark.parametrize("kind", ["path", "star", "caterpillar", "random", 2, 3, 8, 9, 17, 1000])
 def test_forests(ctx, V, kind):
     rng = np.random.default_rng(V)
