@@ -607,6 +607,8 @@ static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const i
         std::vector<int32_t> pairs(2 * (size_t)std::max<int64_t>(vt - (k1 - k0), 1));
         int64_t nb = 0;
         const int rc = bridges_find(c, du, et, (int32_t)vt, 1, pairs.data(), (int64_t)pairs.size() / 2, &nb, st.stream, &knobs);
+        c->fused.items = nullptr;          // this union's rows: no other call may take them
+        c->fused.n_items = 0;
         if (rc == BR_ERANGE) return fail(BR_ERANGE, "batched: an edge has a vertex id outside its graph's [0, V)");
         if (rc) return rc;
         // ascending: each graph's pairs are one run

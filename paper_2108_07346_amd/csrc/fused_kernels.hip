@@ -532,7 +532,7 @@ int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_
     if (P.s2 > 1) {
         const uint32_t nsel = (uint32_t)(nrows - m2), div = (uint32_t)(P.s2 - 1);
         flatten(P.code_per == 2);
-        if (!P.table && P.s2 < P.s1) {
+        if (!P.table && F.items && P.s2 < P.s1) {
             // (after stage 1 alone too many edges still join components of F':
             // 405 us here for 9e6 edges over 560,000 vertices in 48 graphs)
             hipLaunchKernelGGL((k_filter<2, false, false, true>), dim3((unsigned)F.n_items), dim3(kFilterBlock),
