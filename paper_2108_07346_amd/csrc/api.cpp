@@ -566,6 +566,21 @@ int br_cert_merge(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_b,
 
 }  // extern "C"
 
+// The contracted final step (unless the certificate's launch held it), waited for
+static int contracted_step(br_ctx* c, const Plan& P, const DevBufs& B, const FinalReq& fin, hipStream_t s, bool* solved) {
+    for (bool again = false;; again = true) {
+        if (again) launch_contract_again(P, B, c->contract, fin.mode, fin.h_status, fin.h_data, fin.h_tree, s);
+        else if (!fin.done) launch_contract(P, B, c->contract, fin.mode, fin.h_status, fin.h_data, fin.h_tree, s);
+        BR_HIP(hipGetLastError());
+        ev_record(c, 5, s);
+        const int rc = ctx_end(c, s);
+        if (rc) return rc;
+        BR_HIP(hipStreamSynchronize(s));
+        *solved = fin.h_status[6] != 0;
+        if (*solved || again || !fin.h_status[8]) return BR_OK;
+    }
+}
+
 int br::bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t M, int32_t* h_bridges, int64_t cap,
                      int64_t* n_bridges, void* stream, const TuneEntry* plan_knobs) {
     if (V > kFinalStepMaxV) return fail(BR_EINVAL, "V = %d above the final step's limit 2^29", V);
@@ -602,13 +617,8 @@ int br::bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, in
         uint32_t nk = 0;
         bool solved = false;
         if (P.contract) {
-            if (!fin.done) launch_contract(P, B, c->contract, 0, hc, hk, nullptr, s);
-            BR_HIP(hipGetLastError());
-            ev_record(c, 5, s);
-            rc = ctx_end(c, s);
+            rc = contracted_step(c, P, B, fin, s, &solved);
             if (rc) return rc;
-            BR_HIP(hipStreamSynchronize(s));
-            solved = hc[6] != 0;
             nk = hc[1];
         }
         if (!solved) {
@@ -755,12 +765,8 @@ static int classes_common(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t 
         uint64_t* d_tkeys = nullptr;
         bool solved = false;
         if (P.contract) {
-            if (!fin.done) launch_contract(P, B, c->contract, fin.mode, hc, fin.h_data, ht, s);
-            BR_HIP(hipGetLastError());
-            rc = ctx_end(c, s);
+            rc = contracted_step(c, P, B, fin, s, &solved);
             if (rc) return rc;
-            BR_HIP(hipStreamSynchronize(s));
-            solved = hc[6] != 0;
         }
         if (!solved) {
             int32_t* d_label = nullptr;

@@ -219,6 +219,7 @@ __device__ __forceinline__ void report_contracted(SolveLds& L, const int2* f1, u
         out[4] = err;
         out[5] = L.nout;
         out[6] = ok ? 1u : 0u;
+        out[8] = 0;
     }
 }
 

@@ -14,10 +14,21 @@ namespace br {
 
 namespace {
 
-// root of x in F' (no shortcut stores: the state is read by every workgroup)
-__device__ __forceinline__ uint32_t root2(const uint32_t* q, int64_t qs, uint32_t x) {
-    for (uint32_t d = q[qs * (int64_t)x + 1]; d; d = q[qs * (int64_t)x + 1]) x -= d;
-    return x;
+// Steps up a chain of F' that k_cross takes.  A shuffled list leaves chains of
+// a few steps; one in vertex order chains of up to V (200,000 vertices on a
+// path, each edge four times: 75 ms in k_cross).  k_cross then gives up, and the
+// call compresses the state and takes the step again (launch_contract_again).
+constexpr int kRootSteps = 128;
+
+// x moved up to its root in F' (no shortcut stores: the state is read by every
+// workgroup); false if that is more than kRootSteps away
+__device__ __forceinline__ bool root2(const uint32_t* q, int64_t qs, uint32_t& x) {
+    for (int n = 0; n < kRootSteps; n++) {
+        const uint32_t d = q[qs * (int64_t)x + 1];
+        if (d == 0) return true;
+        x -= d;
+    }
+    return false;
 }
 
 // Collects the crossing edges of F: the roots of their ends at C.he, their
@@ -36,9 +47,11 @@ __global__ void __launch_bounds__(kSolveT) k_cross(const int2* f1, const uint32_
         bool cross = false, took[2] = {false, false};
         if (k < n1) {
             const int2 e = f1[k];
-            r[0] = root2(q, qs, (uint32_t)e.x);
-            r[1] = root2(q, qs, (uint32_t)e.y);
-            cross = r[0] != r[1];
+            r[0] = (uint32_t)e.x;
+            r[1] = (uint32_t)e.y;
+            const bool near = root2(q, qs, r[0]) && root2(q, qs, r[1]);
+            cross = near && r[0] != r[1];
+            if (!near) *C.deep = 1;
         }
         const uint64_t m = __ballot(cross);
         if (m) {
@@ -78,23 +91,29 @@ __global__ void __launch_bounds__(kSolveT) k_solve(const int2* f1, const uint32_
                                                    Contract C, int32_t mode, uint32_t* out, uint64_t* keys) {
     extern __shared__ __align__(16) unsigned char raw[];
     SolveLds& L = *reinterpret_cast<SolveLds*>(raw);
-    const uint32_t n = C.hcnt[0], m = C.hcnt[1];
-    bool ok = n <= (uint32_t)kMaxCross && m <= (uint32_t)kMaxCross;
+    const uint32_t n = C.hcnt[0], m = C.hcnt[1], deep = *C.deep;
+    bool ok = !deep && n <= (uint32_t)kMaxCross && m <= (uint32_t)kMaxCross;
     if (ok) ok = solve_contracted(L, C, n, m, mode != 0, [&](uint32_t j) {
             const uint2 r = C.he[j];
             return make_uint2(C.hid[r.x] - 1, C.hid[r.y] - 1);
         });
     __syncthreads();
     report_contracted(L, f1, cnt[0], cnt[1], *err, (uint32_t)V, C, m, ok, mode, out, keys);
-    if (threadIdx.x == 0) *C.solved = ok ? 1u : 0u;
+    if (threadIdx.x == 0) {
+        *C.solved = ok ? 1u : 0u;
+        if (deep) out[8] = 1;
+    }
 }
 
-// class labels of all vertices, straight to host memory
+// class labels of all vertices, straight to host memory (every vertex that is not
+// alone is an end of an edge of F, so k_cross has been up its chain)
 __global__ void __launch_bounds__(256) k_labels(const uint32_t* q, int64_t qs, int32_t V, Contract C,
                                                 const uint32_t* solved, int32_t* label) {
     if (!*solved) return;
     GRID_LOOP(x, (int64_t)V) {
-        const uint32_t r = root2(q, qs, (uint32_t)x), h = C.hid[r];
+        uint32_t r = (uint32_t)x;
+        root2(q, qs, r);
+        const uint32_t h = C.hid[r];
         label[x] = (int32_t)(h ? C.hcls[h - 1] : r);
     }
 }
@@ -115,6 +134,7 @@ Contract contract_carve(uint32_t* cleared, uint32_t* scratch, int32_t V) {
     C.hid = cleared;
     C.hcnt = cleared + V;
     C.solved = C.hcnt + 2;
+    C.deep = C.hcnt + 3;
     uint32_t* p = scratch;
     auto take = [&](size_t k) { uint32_t* r = p; p += k * kMaxCross; return r; };
     C.he = reinterpret_cast<uint2*>(take(2));
@@ -143,6 +163,13 @@ void launch_contract(const Plan& P, const DevBufs& B, const Contract& C, int mod
     if (mode != 0)
         hipLaunchKernelGGL(k_labels, dim3(grid_for(P.V)), dim3(256), 0, s, (const uint32_t*)B.state, B.qs, P.V, C,
                            (const uint32_t*)C.solved, reinterpret_cast<int32_t*>(h_data));
+}
+
+void launch_contract_again(const Plan& P, const DevBufs& B, const Contract& C, int mode, uint32_t* h_status, void* h_data,
+                           uint64_t* h_tree, hipStream_t s) {
+    launch_flatten(P, B, s);
+    launch_fill_u32(C.hid, (int64_t)contract_clear_words(P.V), 0u, s);
+    launch_contract(P, B, C, mode, h_status, h_data, h_tree, s);
 }
 
 }  // namespace br

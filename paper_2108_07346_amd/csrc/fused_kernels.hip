@@ -504,6 +504,13 @@ int launch_list_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, uint32
     return launches;
 }
 
+static void launch_flatten(const Plan& P, const DevBufs& B, uint32_t* rcode, uint32_t* ncode, hipStream_t s) {
+    hipLaunchKernelGGL(k_flatten, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(((int64_t)P.V + 255) / 256, 16384))),
+                       dim3(256), 0, s, B.state, B.qs, P.V, rcode, ncode);
+}
+
+void launch_flatten(const Plan& P, const DevBufs& B, hipStream_t s) { launch_flatten(P, B, nullptr, nullptr, s); }
+
 int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s) {
     if (P.E == 0) return 0;
     int launches = 0;
@@ -519,9 +526,8 @@ int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_
                            (uint32_t)nsel, mul, div, rpw);
         launches++;
     };
-    const dim3 vgrid((unsigned)std::max<int64_t>(1, std::min<int64_t>(((int64_t)P.V + 255) / 256, 16384)));
     auto flatten = [&](bool codes) {
-        hipLaunchKernelGGL(k_flatten, vgrid, dim3(256), 0, s, B.state, B.qs, P.V, codes ? F.rcode : nullptr, F.ncode);
+        launch_flatten(P, B, codes ? F.rcode : nullptr, F.ncode, s);
         launches++;
     };
     rows(m1, P.s1, 0, 4 * cus);

@@ -282,6 +282,7 @@ int fused_prepare();               // once per process: the kernels' LDS limit
 // zeroes `bytes` (a multiple of 16) at base and writes node 0's region table
 void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int64_t cap0, hipStream_t s);
 int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);   // kernels enqueued
+void launch_flatten(const Plan& P, const DevBufs& B, hipStream_t s);    // full path compression of node 0's state
 void launch_filter_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);
 // The plan's edge list against the components of the union-find g (words
 // g[x], in place compressed): edges inside one named
@@ -302,6 +303,7 @@ struct Contract {
     uint32_t* hid = nullptr;       // [V] 1 + number in H of a root of F' (zero at launch)
     uint32_t* hcnt = nullptr;      // [2] H's vertices and edges (zero at launch)
     uint32_t* solved = nullptr;    // [1]
+    uint32_t* deep = nullptr;      // [1] 1: a chain of F' too long for k_cross (zero at launch)
     uint2* he = nullptr;           // per edge of H: the roots of its ends
     uint32_t* hk = nullptr;        // ... its place in F
     uint32_t* isbr = nullptr;      // ... 1 if it is a bridge
@@ -314,10 +316,14 @@ size_t contract_clear_words(int32_t V);    // words that must be zero at launch
 size_t contract_words();                   // scratch words
 Contract contract_carve(uint32_t* cleared, uint32_t* scratch, int32_t V);
 // mode 0 bridges, 1 classes, 2 classes and bridge tree.  h_status: 64 words of
-// pinned memory (the status block of a bridge step, word 6: 1 if solved);
+// pinned memory (the status block of a bridge step, word 6: 1 if solved, else
+// word 8: 1 if only launch_contract_again can tell);
 // h_data: keys (mode 0) or labels, also pinned; h_tree: the tree's keys.
 void launch_contract(const Plan& P, const DevBufs& B, const Contract& C, int mode, uint32_t* h_status, void* h_data,
                      uint64_t* h_tree, hipStream_t s);
+// the same on the state compressed first
+void launch_contract_again(const Plan& P, const DevBufs& B, const Contract& C, int mode, uint32_t* h_status, void* h_data,
+                           uint64_t* h_tree, hipStream_t s);
 
 void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 void launch_phase0(const Plan& P, DevBufs& B, hipStream_t s);

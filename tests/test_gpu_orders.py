@@ -1,0 +1,103 @@
+"""Lists in vertex order: ids that follow the graph (a path, a ring, a mesh row by
+row, a hub and its leaves).  The union-find hooks larger ids under smaller ones,
+so such lists are the ones that make long chains and crowded words; they have to
+take about as long as the same graphs with their ids relabelled at random.
+Results must equal the oracle's, times stay within the bounds that each test
+derives."""
+import sys
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2108_07346_amd as br
+    c = br.Context(0)
+    yield c
+    c.close()
+
+
+def path(V):
+    a = np.arange(V, dtype=np.int32)
+    return np.stack([a[:-1], a[1:]], 1)
+
+
+def ring(V):
+    return np.concatenate([path(V), np.array([[V - 1, 0]], np.int32)])
+
+
+def band(V, k):
+    i = np.repeat(np.arange(V, dtype=np.int32), k)
+    j = i + np.tile(np.arange(1, k + 1, dtype=np.int32), V)
+    return np.stack([i, j], 1)[j < V]
+
+
+def star(V, hub):
+    x = np.delete(np.arange(V, dtype=np.int32), hub)
+    return np.stack([np.full(V - 1, hub, np.int32), x], 1)
+
+
+def relabelled(e, V):
+    return np.random.default_rng(V).permutation(V).astype(np.int32)[e]
+
+
+def dev(e):
+    return torch.from_numpy(np.ascontiguousarray(e)).cuda()
+
+
+def best_ms(fn, reps=5):
+    """The shortest of reps calls, after one more (buffers grow in the first)."""
+    fn()
+    t = []
+    for _ in range(reps):
+        a = time.perf_counter()
+        fn()
+        torch.cuda.synchronize()
+        t.append(1000 * (time.perf_counter() - a))
+    return min(t)
+
+
+@pytest.mark.parametrize("copies", [4, 6, 20])
+def test_long_chains_of_f2(ctx, copies):
+    """A path, each edge `copies` times: F' is the path too, and its chains are what
+    the contracted final step climbs.  It may take one more compression and the
+    step again, so within 5 times the relabelled list's time."""
+    V = 200_000
+    e = np.repeat(path(V), copies, 0)
+    d, r = dev(e), dev(relabelled(e, V))
+    wl, wt = oracle.bridge_tree(e, V)
+    assert ctx.find(d, V, 8).shape == (0, 2)
+    assert np.array_equal(ctx.two_edge_components(d, V, 8)[0], wl)
+    lab, t = ctx.bridge_tree(d, V, 8)
+    assert np.array_equal(lab, wl) and np.array_equal(t, wt)
+    for name, fn in (("find", lambda x: ctx.find(x, V, 8)), ("classes", lambda x: ctx.two_edge_components(x, V, 8))):
+        a, b = best_ms(lambda: fn(d)), best_ms(lambda: fn(r))
+        say(name, "copies", copies, "in order %.3f ms, relabelled %.3f ms" % (a, b))
+        assert a < 5 * b
+
+
+@pytest.mark.parametrize("V", [100, 5000, 30_000])
+def test_path_with_bridges(ctx, V):
+    """The same with every seventh edge once: the crossing edges come from the step
+    taken again, answers and order alike."""
+    p = path(V)
+    e = np.concatenate([np.repeat(p[np.arange(V - 1) % 7 != 3], 5, 0), p[np.arange(V - 1) % 7 == 3]])
+    wl, wt = oracle.bridge_tree(e, V)
+    d = dev(e)
+    assert np.array_equal(ctx.find(d, V, 8), oracle.bridges(e, V))
+    lab, t = ctx.bridge_tree(d, V, 8)
+    assert np.array_equal(lab, wl) and np.array_equal(t, wt)
