@@ -783,13 +783,7 @@ __global__ void __launch_bounds__(kT) k_tv_cross(EdgeSet S, int32_t V, const int
 }
 
 __global__ void k_tv_compress(uint32_t* g, int32_t V) {
-    GRID_LOOP(x, (int64_t)V) {
-        const uint32_t d = g[x];
-        if (d == 0) continue;
-        uint32_t r = (uint32_t)x - d;
-        for (uint32_t e = g[r]; e != 0; e = g[r]) r -= e;
-        g[x] = (uint32_t)x - r;
-    }
+    GRID_LOOP(x, (int64_t)V) uf_compress(g, 1, (uint32_t)x);
 }
 
 // per tree edge (w, v): compare v's block with the block of w's own parent edge

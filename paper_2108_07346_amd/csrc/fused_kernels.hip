@@ -96,18 +96,8 @@ __global__ void __launch_bounds__(256) k_flatten(uint32_t* q, int64_t qs, int32_
     GRID_LOOP(x, n) {
         bool root = false;
         if (x < V) {
-            for (int f = 0; f < 2; f++) {
-                const uint32_t d = q[qs * x + f];
-                if (d == 0) { root = f == 1; continue; }
-                uint32_t r = (uint32_t)x - d;
-                int n = 0;
-                for (uint32_t e = q[qs * (int64_t)r + f]; e != 0; e = q[qs * (int64_t)r + f]) {
-                    r -= e;
-                    // a long chain: leave the way so far to whoever comes by here
-                    if (++n % kFreeSteps == 0) q[qs * x + f] = (uint32_t)x - r;
-                }
-                if (r != (uint32_t)x - d) q[qs * x + f] = (uint32_t)x - r;
-            }
+            uf_compress(q, qs, (uint32_t)x);
+            root = uf_compress(q + 1, qs, (uint32_t)x) == (uint32_t)x;
         }
         if (!rcode) continue;
         const uint64_t m = __ballot(root);
@@ -126,19 +116,7 @@ __global__ void __launch_bounds__(256) k_flatten(uint32_t* q, int64_t qs, int32_
 __global__ void __launch_bounds__(256) k_flatten1(uint32_t* q, int32_t V, uint32_t* rcode, uint32_t* ncode, int32_t names) {
     const int64_t n = ((int64_t)V + 63) & ~int64_t(63);
     GRID_LOOP(x, n) {
-        bool root = false;
-        if (x < V) {
-            const uint32_t d = q[x];
-            root = d == 0;
-            uint32_t r = (uint32_t)x - d;
-            int k = 0;
-            if (!root)
-                for (uint32_t e = q[r]; e != 0; e = q[r]) {
-                    r -= e;
-                    if (++k % kFreeSteps == 0) q[x] = (uint32_t)x - r;
-                }
-            if (r != (uint32_t)x - d) q[x] = (uint32_t)x - r;
-        }
+        const bool root = x < V && uf_compress(q, 1, (uint32_t)x) == (uint32_t)x;
         const uint64_t m = __ballot(root);
         if (!m) continue;
         uint32_t c = 0;

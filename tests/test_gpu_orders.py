@@ -101,3 +101,31 @@ def test_path_with_bridges(ctx, V):
     assert np.array_equal(ctx.find(d, V, 8), oracle.bridges(e, V))
     lab, t = ctx.bridge_tree(d, V, 8)
     assert np.array_equal(lab, wl) and np.array_equal(t, wt)
+
+
+@pytest.mark.parametrize("n", [1, 2, 17, 18, 300, 4097])
+def test_compression_at_step_limits(ctx, n):
+    """Chains of n steps (16 is where a thread begins to leave its steps behind) in
+    the class and block groups and in the state."""
+    e = np.concatenate([np.repeat(path(n + 1), 3, 0), ring(n + 2) + n + 1])
+    V = 2 * n + 3
+    wl, _ = oracle.bridge_tree(e, V)
+    d = dev(e)
+    assert np.array_equal(ctx.two_edge_components(d, V, 2)[0], wl)
+    assert np.array_equal(ctx.articulation_points(d, V), oracle.articulation_points(e, V))
+
+
+def test_long_chains_of_classes_and_blocks(ctx):
+    """Every vertex joined to the next two: one class and one block, grouped along
+    chains of V vertices.  Compression takes the logarithm of that in steps, so
+    within twice the relabelled list's time."""
+    V = 1_000_000
+    e = band(V, 2)
+    d, r = dev(e), dev(relabelled(e, V))
+    lab, n = ctx.two_edge_components(d, V, 8)
+    assert n == 1 and not lab.any()
+    assert ctx.articulation_points(d, V).shape == (0,)
+    for name, fn in (("classes", lambda x: ctx.two_edge_components(x, V, 8)), ("cut", lambda x: ctx.articulation_points(x, V))):
+        a, b = best_ms(lambda: fn(d)), best_ms(lambda: fn(r))
+        say(name, "in order %.3f ms, relabelled %.3f ms" % (a, b))
+        assert a < 2 * b
