@@ -711,8 +711,8 @@ __global__ void __launch_bounds__(kT) k_order_runs(const uint32_t* nkeys, const 
 // only the edges of the list that join different groups -- k_filter finds them
 // at the rate the list streams.  (Rows of 8V edges in place of F' in the first
 // round: 96 us in k_tv_range alone on the dense workload.)
-__device__ __forceinline__ void tv_unite(uint32_t* g, uint32_t a, uint32_t b) {
-    uf_unite<0>(g, 1, a, a - ld(g + a), b, b - ld(g + b));
+__device__ __forceinline__ void tv_unite(uint32_t* g, bool on, uint32_t a, uint32_t b) {
+    uf_unite(g, 1, on, a, on ? a - ld(g + a) : 0u, b, on ? b - ld(g + b) : 0u);
 }
 
 // The edges of one round: list[dir * k] for k < *n, or all of edges[0..E) where
@@ -726,19 +726,22 @@ struct EdgeSet {
     uint32_t room;
 };
 
+// f(valid, edge), by whole wavefronts
 template <class Fn>
 __device__ __forceinline__ void for_edges(const EdgeSet& S, int32_t V, Fn f) {
     const bool listed = S.list && *S.n <= S.room;
     const int64_t n = listed ? (int64_t)*S.n : S.E;
-    GRID_LOOP(k, n) {
-        const int2 e = listed ? S.list[S.dir * k] : S.edges[k];
-        if ((uint32_t)e.x < (uint32_t)V && (uint32_t)e.y < (uint32_t)V && e.x != e.y) f(e);
+    WAVE_LOOP(k, n) {
+        int2 e = make_int2(-1, -1);
+        if (k < n) e = listed ? S.list[S.dir * k] : S.edges[k];
+        f((uint32_t)e.x < (uint32_t)V && (uint32_t)e.y < (uint32_t)V && e.x != e.y, e);
     }
 }
 
 // smallest and largest preorder number next to each vertex
 __global__ void __launch_bounds__(kT) k_tv_range(EdgeSet S, int32_t V, const int32_t* pre, int32_t* tmin, int32_t* tmax) {
-    for_edges(S, V, [&](int2 e) {
+    for_edges(S, V, [&](bool valid, int2 e) {
+        if (!valid) return;
         const int32_t px = pre[e.x], py = pre[e.y];
         if (px >= 0 && py >= 0) range_touch(tmin, tmax, px, py);
     });
@@ -756,29 +759,41 @@ __global__ void k_tv_init(int32_t V, uint32_t* g, int32_t* rmin, int32_t* rmax, 
 // tree edge (w, v), w not a root: joins (parent(w), w) when v's subtree escapes w's
 __global__ void k_tv_tree(const int2* f1, const uint32_t* q, int32_t qs, const int32_t* first, const int32_t* in_arc,
                           const int32_t* pre, const int32_t* sub, Rmq R, int32_t V, int64_t A, uint32_t* g) {
-    GRID_LOOP(v, (int64_t)V) {
-        if (first[v] == 0 || q[qs * (size_t)v] == 0) continue;
-        const int32_t a = in_arc[v];
-        if (a < 0 || a >= A) continue;
-        const int32_t w = arc_src(f1, a);
-        if (q[qs * (size_t)w] == 0) continue;
-        const int32_t l = pre[v], r = pre[v] + sub[v] - 1, pw = pre[w];
-        if (l < 0 || r < l || r >= V || pw < 0) continue;
-        int32_t mn, mx;
-        range_minmax(R, l, r, mn, mx);
-        if (mn < pw || mx >= pw + sub[w]) tv_unite(g, (uint32_t)v, (uint32_t)w);
+    WAVE_LOOP(v, V) {
+        int32_t w = 0;
+        const auto joins = [&] {
+            if (v >= V || first[v] == 0 || q[qs * (size_t)v] == 0) return false;
+            const int32_t a = in_arc[v];
+            if (a < 0 || a >= A) return false;
+            w = arc_src(f1, a);
+            if (q[qs * (size_t)w] == 0) return false;
+            const int32_t l = pre[v], r = pre[v] + sub[v] - 1, pw = pre[w];
+            if (l < 0 || r < l || r >= V || pw < 0) return false;
+            int32_t mn, mx;
+            range_minmax(R, l, r, mn, mx);
+            return mn < pw || mx >= pw + sub[w];
+        };
+        const bool on = joins();
+        tv_unite(g, on, (uint32_t)v, (uint32_t)w);
     }
 }
 
 // edges between unrelated vertices join their parent edges
 __global__ void __launch_bounds__(kT) k_tv_cross(EdgeSet S, int32_t V, const int32_t* pre, const int32_t* sub, uint32_t* g) {
-    for_edges(S, V, [&](int2 e) {
-        const uint32_t x = (uint32_t)e.x, y = (uint32_t)e.y, gx = x - ld(g + x), gy = y - ld(g + y);
-        if (gx == gy) return;
-        const int32_t px = pre[x], py = pre[y];
-        if (px < 0 || py < 0) return;
-        const bool related = (px <= py && py < px + sub[x]) || (py <= px && px < py + sub[y]);
-        if (!related) uf_unite<0>(g, 1, x, gx, y, gy);
+    for_edges(S, V, [&](bool valid, int2 e) {
+        const uint32_t x = (uint32_t)e.x, y = (uint32_t)e.y;
+        uint32_t gx = 0, gy = 0;
+        bool on = valid;
+        if (on) {
+            gx = x - ld(g + x);
+            gy = y - ld(g + y);
+            on = gx != gy;
+        }
+        if (on) {
+            const int32_t px = pre[x], py = pre[y];
+            on = px >= 0 && py >= 0 && !((px <= py && py < px + sub[x]) || (py <= px && px < py + sub[y]));
+        }
+        uf_unite(g, 1, on, x, gx, y, gy);
     });
 }
 
@@ -827,24 +842,30 @@ __global__ void k_tv_list(const uint32_t* q, int32_t qs, const int32_t* first, i
 // after full compression each vertex's root is the smallest id of its class.
 __global__ void k_class_tree(const int2* f1, const uint32_t* q, int32_t qs, const int32_t* first, const int32_t* in_arc,
                              const int32_t* pre, const int32_t* sub, Rmq R, int32_t V, int64_t A, uint32_t* g) {
-    GRID_LOOP(v, (int64_t)V) {
-        if (first[v] == 0 || q[qs * (size_t)v] == 0) continue;      // no tree edge above v
-        const int32_t a = in_arc[v];
-        if (a < 0 || a >= A) continue;
-        const int32_t l = pre[v], r = pre[v] + sub[v] - 1;
-        if (l < 0 || r < l || r >= V) continue;
-        int32_t mn, mx;
-        range_minmax(R, l, r, mn, mx);
-        if (mn >= l && mx <= r) continue;                                  // a bridge
-        tv_unite(g, (uint32_t)v, (uint32_t)arc_src(f1, a));
+    WAVE_LOOP(v, V) {
+        int32_t w = 0;
+        const auto joins = [&] {
+            if (v >= V || first[v] == 0 || q[qs * (size_t)v] == 0) return false;      // no tree edge above v
+            const int32_t a = in_arc[v];
+            if (a < 0 || a >= A) return false;
+            const int32_t l = pre[v], r = pre[v] + sub[v] - 1;
+            if (l < 0 || r < l || r >= V) return false;
+            int32_t mn, mx;
+            range_minmax(R, l, r, mn, mx);
+            w = arc_src(f1, a);
+            return !(mn >= l && mx <= r);                                             // not a bridge
+        };
+        const bool on = joins();
+        tv_unite(g, on, (uint32_t)v, (uint32_t)w);
     }
 }
 
 __global__ void k_class_cross(const int2* f2, int32_t dir, const uint32_t* cnt, uint32_t* g) {
     const int64_t n2 = cnt[1];
-    GRID_LOOP(k, n2) {
-        const int2 e = f2[dir * k];
-        if (e.x != e.y) tv_unite(g, (uint32_t)e.x, (uint32_t)e.y);
+    WAVE_LOOP(k, n2) {
+        int2 e = make_int2(0, 0);
+        if (k < n2) e = f2[dir * k];
+        tv_unite(g, e.x != e.y, (uint32_t)e.x, (uint32_t)e.y);
     }
 }
 

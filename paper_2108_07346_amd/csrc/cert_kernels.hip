@@ -54,9 +54,9 @@ __device__ __forceinline__ void offer_tile(Stage& S, uint32_t* q, int64_t qs, in
             const int64_t i = base + threadIdx.x;
             bool a1 = false, a2 = false;
             int2 e = make_int2(0, 0);
-            if (i < t1 && load(i, e))
-                offer_from(q, qs, (uint32_t)e.x, (uint32_t)e.y, ld2(q + qs * (int64_t)e.x), ld2(q + qs * (int64_t)e.y),
-                           a1, a2);
+            const bool ok = i < t1 && load(i, e);
+            offer_from(q, qs, ok, (uint32_t)e.x, (uint32_t)e.y, ok ? ld2(q + qs * (int64_t)e.x) : 0,
+                       ok ? ld2(q + qs * (int64_t)e.y) : 0, a1, a2);
             stage_put(S, a1, a2, e);
         }
         return;
@@ -85,7 +85,7 @@ __device__ __forceinline__ void offer_tile(Stage& S, uint32_t* q, int64_t qs, in
             nv = ld2(q + qs * (int64_t)e[j + 1].y);
         }
         bool a1 = false, a2 = false;
-        if (ok >> j & 1u) offer_from(q, qs, (uint32_t)e[j].x, (uint32_t)e[j].y, su, sv, a1, a2);
+        offer_from(q, qs, ok >> j & 1u, (uint32_t)e[j].x, (uint32_t)e[j].y, su, sv, a1, a2);
         stage_put(S, a1, a2, e[j]);
         su = nu;
         sv = nv;

@@ -11,6 +11,10 @@
 #define GRID_LOOP(i, n) \
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (n); i += (int64_t)gridDim.x * blockDim.x)
 
+// the same in whole wavefronts: every lane takes part until the wavefront's last
+// item is done (i may be n or more), so that the body may use ballots
+#define WAVE_LOOP(i, n) GRID_LOOP(i, ((int64_t)(n) + 63) & ~int64_t(63))
+
 namespace br {
 
 // blocks of 256 threads for n items, at least 1 and at most 16384 (the

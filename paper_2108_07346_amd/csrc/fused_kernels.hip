@@ -77,13 +77,19 @@ __global__ void __launch_bounds__(kRowBlock) k_rows(DevBufs B, int64_t E, int32_
         const int64_t i = stage_row(sel, mul, div) * kRow + threadIdx.x;
         bool a1 = false, a2 = false;
         int2 e = make_int2(0, 0);
+        uint64_t su = 0, sv = 0;
+        bool ok = false;
         if (i < E) {
             e = edge_at(B, i);
-            if ((uint32_t)e.x < (uint32_t)V && (uint32_t)e.y < (uint32_t)V)
-                offer_from(B.state, B.qs, (uint32_t)e.x, (uint32_t)e.y, ld2(B.state + B.qs * (int64_t)e.x),
-                           ld2(B.state + B.qs * (int64_t)e.y), a1, a2);
-            else atomicOr(B.err, 1u);
+            ok = (uint32_t)e.x < (uint32_t)V && (uint32_t)e.y < (uint32_t)V;
+            if (ok) {
+                su = ld2(B.state + B.qs * (int64_t)e.x);
+                sv = ld2(B.state + B.qs * (int64_t)e.y);
+            } else {
+                atomicOr(B.err, 1u);
+            }
         }
+        offer_from(B.state, B.qs, ok, (uint32_t)e.x, (uint32_t)e.y, su, sv, a1, a2);
         stage_put(S, a1, a2, e);
     }
     stage_flush(S, B.cnt, B.cert, cap, B.err);
@@ -203,12 +209,14 @@ __device__ __forceinline__ uint32_t code_of(const uint32_t* tab, uint32_t x) {
 __device__ __forceinline__ void offer_list(const DevBufs& B, int64_t cap, const int2* l, uint32_t n) {
     bool a1 = false, a2 = false;
     int2 e = make_int2(0, 0);
+    uint64_t su = 0, sv = 0;
     const uint32_t lane = __lane_id();
     if (lane < n) {
         e = l[lane];
-        offer_from(B.state, B.qs, (uint32_t)e.x, (uint32_t)e.y, ld2(B.state + B.qs * (int64_t)e.x),
-                   ld2(B.state + B.qs * (int64_t)e.y), a1, a2);
+        su = ld2(B.state + B.qs * (int64_t)e.x);
+        sv = ld2(B.state + B.qs * (int64_t)e.y);
     }
+    offer_from(B.state, B.qs, lane < n, (uint32_t)e.x, (uint32_t)e.y, su, sv, a1, a2);
     for (int f = 0; f < 2; f++) {
         const bool a = f ? a2 : a1;
         const uint64_t m = __ballot(a);

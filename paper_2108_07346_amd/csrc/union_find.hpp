@@ -24,14 +24,21 @@ __device__ __forceinline__ uint64_t ld2(const uint32_t* p) {
 }
 
 constexpr int kFreeSteps = 16;   // steps of a search before it begins to shorten the chain
+// Steps after which a search stops and its wavefront walks for it.  A walk costs
+// up to 2 us per 256 ids, so it has to be rare: with 512 steps the articulation
+// points of a mesh row by row (3V edges, V = 10^6) took 2.6 ms, with 2,048 2.0 (as
+// without walks); a ring of 20,000 vertices 0.55 and 0.83 ms (5.5 without).
+constexpr int kDeepSteps = 2048;
 
 // Unite u and v, whose parents were seen as pu and pv (however stale, each
 // names an ancestor or the vertex itself); true iff this call merged their
-// components.  The end whose parent is larger moves up, so the search stops
-// where the two chains meet (Rem's order; no need to reach the roots), and a
-// root that is reached hooks under the other end's parent.  Long searches halve
-// the chain as they go; short ones leave no dirty lines behind, which hooks
-// (swaps at the memory side) would have to write back first.
+// components, else pu == pv if they are one component already.  The end whose
+// parent is larger moves up, so the search stops where the two chains meet (Rem's
+// order; no need to reach the roots), and a root that is reached hooks under the
+// other end's parent.  Long searches halve the chain as they go; short ones leave
+// no dirty lines behind, which hooks (swaps at the memory side) would have to
+// write back first.  A search that is not over after kSteps steps stops where it
+// stands (false, pu != pv).
 //
 // A root that many lanes want to hook is one address, and compare-and-swaps on
 // one address queue at the memory side whether they win or fail.  By the time
@@ -43,10 +50,9 @@ constexpr int kFreeSteps = 16;   // steps of a search before it begins to shorte
 // two full searches and no load before the swap, 215 with the load, 200 in
 // Rem's order; 133,072 over 66,536 vertices 300-800, 77, 62 us; 534,288 over
 // 267,144 vertices (load) 153, 133 us.
-template <int F>
-__device__ __forceinline__ bool uf_unite(uint32_t* q, int64_t qs, uint32_t u, uint32_t pu, uint32_t v, uint32_t pv) {
-    for (int n = 0;; n++) {
-        if (pu == pv) return false;
+template <int kSteps = kDeepSteps>
+__device__ __forceinline__ bool uf_search(uint32_t* q, int64_t qs, uint32_t& u, uint32_t& pu, uint32_t& v, uint32_t& pv) {
+    for (int n = 0; pu != pv && n < kSteps; n++) {
         if (pu < pv) {
             uint32_t t = u;
             u = v;
@@ -56,7 +62,7 @@ __device__ __forceinline__ bool uf_unite(uint32_t* q, int64_t qs, uint32_t u, ui
             pv = t;
         }
         if (u == pu) {
-            uint32_t* w = q + qs * (int64_t)u + F;
+            uint32_t* w = q + qs * (int64_t)u;
             uint32_t d = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (d == 0 && __hip_atomic_compare_exchange_strong(w, &d, u - pv, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                                __HIP_MEMORY_SCOPE_AGENT))
@@ -64,10 +70,48 @@ __device__ __forceinline__ bool uf_unite(uint32_t* q, int64_t qs, uint32_t u, ui
             pu = u - d;   // u was hooked meanwhile
             continue;
         }
-        const uint32_t g = pu - ld(q + qs * (int64_t)pu + F);
-        if (n >= kFreeSteps && g != pu) st(q + qs * (int64_t)u + F, u - g);
+        const uint32_t g = pu - ld(q + qs * (int64_t)pu);
+        if (n >= kFreeSteps && g != pu) st(q + qs * (int64_t)u, u - g);
         u = pu;
         pu = g;
+    }
+    return false;
+}
+
+// Root of x (the same in every lane of the wavefront, all of them active), or
+// what a stale word shows as one.  The lanes read the words of the 256 ids down
+// from x and jump among them, which is where a chain of near ids leads, so a
+// walk takes at most one round of about 2 us per 256 ids between x and its
+// root, however long the chain.  What it has seen it leaves shortened.
+__device__ __forceinline__ uint32_t uf_walk(uint32_t* q, int64_t qs, uint32_t x) {
+    constexpr int kW = 4;
+    const uint32_t lane = __lane_id();
+    for (;;) {
+        uint32_t at[kW];                       // offset below x that lane's id leads to
+        for (int k = 0; k < kW; k++) {
+            const uint32_t o = k * 64 + lane;
+            at[k] = o + (o <= x ? ld(q + qs * (int64_t)(x - o)) : 0u);
+        }
+        uint32_t p = 0;
+        bool root = false;
+        for (int k = 0; k < kW; k++) {
+            const uint32_t lo = k * 64, first = at[k];
+            // (a root leads to itself)
+            for (int r = 0; r < 6; r++) {
+                const uint32_t t = __shfl(at[k], (int)((at[k] - lo) & 63u));
+                if (at[k] < lo + 64) at[k] = t;
+            }
+            const uint32_t o = lo + lane;
+            if (at[k] != first) st(q + qs * (int64_t)(x - o), at[k] - o);
+            if (p < lo + 64) {                 // the chain comes by this window (uniform)
+                const uint32_t t = __shfl(at[k], (int)(p - lo));
+                root = t < lo + 64;
+                p = t;
+                if (root) break;
+            }
+        }
+        x -= p;
+        if (root) return x;
     }
 }
 
@@ -97,17 +141,70 @@ __device__ __forceinline__ uint32_t uf_compress(uint32_t* w, int64_t qs, uint32_
     }
 }
 
-// Offer edge (u,v) to F, then (if rejected) to F'.  su, sv are the endpoints'
-// parent words (F low, F' high), loaded earlier with one 8-byte load each.
-// F' only joins what F joins, so a shared parent in F' rejects the edge in both.
-__device__ __forceinline__ void offer_from(uint32_t* q, int64_t qs, uint32_t u, uint32_t v, uint64_t su, uint64_t sv,
-                                           bool& a1, bool& a2) {
+// For the lanes in m, which hold searches that stand open (in forest `forest` each,
+// q its first word; every lane of the wavefront calls it): the first of them gets
+// its two roots from a walk of the whole wavefront, and what that leaves shortened
+// serves the others.  One lane alone took 270 ns per vertex of a list in vertex
+// order: a ring of 200,000 vertices closed after 54 ms, with the walk after 2.4.
+__device__ __forceinline__ void uf_help(uint64_t m, uint32_t* q, int64_t qs, int forest, uint32_t& u, uint32_t& pu,
+                                        uint32_t& v, uint32_t& pv) {
+    const int lane = __ffsll((unsigned long long)m) - 1;
+    uint32_t* w = q + __shfl(forest, lane);
+#pragma unroll 1
+    for (int end = 0; end < 2; end++) {
+        const uint32_t r = uf_walk(w, qs, (uint32_t)__shfl((int)(end ? v : u), lane));
+        if ((int)__lane_id() == lane) {
+            if (end) v = pv = r;
+            else u = pu = r;
+        }
+    }
+}
+
+// The wavefront's lanes (all of them, active or not) unite their pairs in one
+// union-find.
+__device__ __forceinline__ bool uf_unite(uint32_t* q, int64_t qs, bool active, uint32_t u, uint32_t pu, uint32_t v, uint32_t pv) {
+    bool merged = false;
+    for (bool open = active;;) {
+        if (open) {
+            merged = uf_search(q, qs, u, pu, v, pv);
+            open = !merged && pu != pv;
+        }
+        const uint64_t m = __ballot(open);
+        if (!m) return merged;
+        uf_help(m, q, qs, 0, u, pu, v, pv);
+    }
+}
+
+// Offer edge (u,v) (the lanes that are active) to F, then (if rejected) to F'.
+// su, sv are the endpoints' parent words (F low, F' high), loaded earlier with
+// one 8-byte load each.  F' only joins what F joins, so a shared parent in F'
+// rejects the edge in both.  Every lane of the wavefront calls it.
+__device__ __forceinline__ void offer_from(uint32_t* q, int64_t qs, bool active, uint32_t u, uint32_t v, uint64_t su,
+                                           uint64_t sv, bool& a1, bool& a2) {
     const uint32_t p1u = u - (uint32_t)su, p1v = v - (uint32_t)sv;
     const uint32_t p2u = u - (uint32_t)(su >> 32), p2v = v - (uint32_t)(sv >> 32);
     a1 = a2 = false;
-    if (p2u == p2v) return;
-    a1 = uf_unite<0>(q, qs, u, p1u, v, p1v);
-    if (!a1) a2 = uf_unite<1>(q, qs, u, p2u, v, p2v);
+    uint32_t x = u, px = p1u, y = v, py = p1v;
+    int forest = 0;
+    for (bool open = active && p2u != p2v;;) {
+        if (open) {
+            if (forest == 0) {
+                a1 = uf_search(q, qs, x, px, y, py);
+                if (px == py && !a1) {
+                    forest = 1;
+                    x = u;
+                    px = p2u;
+                    y = v;
+                    py = p2v;
+                }
+            }
+            if (forest == 1) a2 = uf_search(q + 1, qs, x, px, y, py);
+            open = !a1 && !a2 && px != py;
+        }
+        const uint64_t m = __ballot(open);
+        if (!m) return;
+        uf_help(m, q, qs, forest, x, px, y, py);
+    }
 }
 
 // Accepted edges of one workgroup tile are staged in LDS (F from the front,

@@ -129,3 +129,46 @@ def test_long_chains_of_classes_and_blocks(ctx):
         a, b = best_ms(lambda: fn(d)), best_ms(lambda: fn(r))
         say(name, "in order %.3f ms, relabelled %.3f ms" % (a, b))
         assert a < 2 * b
+
+
+@pytest.mark.parametrize("V", [2000, 2049, 2050, 2305, 9000, 30_000])
+def test_rings(ctx, V):
+    """The edge that closes a ring climbs a chain of up to V vertices: around the
+    2,048 steps a search takes alone, and the 256 ids of a walk's round after that."""
+    e = np.concatenate([ring(V), np.array([[V // 2, V]], np.int32)])
+    wl, _ = oracle.bridge_tree(e, V + 1)
+    for x in (e, e[::-1]):
+        d = dev(x)
+        assert np.array_equal(ctx.find(d, V + 1, 8), [[V // 2, V]])
+        assert np.array_equal(ctx.two_edge_components(d, V + 1, 8)[0], wl)
+        assert np.array_equal(ctx.articulation_points(d, V + 1), [V // 2])
+        f1, f2 = ctx.cert_build(d, V + 1, 8)
+        assert f1.shape[0] == V and f2.shape[0] == 1
+
+
+def test_many_closing_edges(ctx):
+    """Rings of 3,000 vertices one after the other, 60 of them, each closed six times."""
+    n, k = 3000, 60
+    e = np.concatenate([path(n * k)] + [np.array([[(i + 1) * n - 1, i * n]] * 6, np.int32) for i in range(k)])
+    want = oracle.bridges(e, n * k)
+    d = dev(e)
+    assert len(want) == k - 1 and np.array_equal(ctx.find(d, n * k, 8), want)
+    assert np.array_equal(ctx.two_edge_components(d, n * k, 8)[0], oracle.bridge_tree(e, n * k)[0])
+    assert np.array_equal(ctx.articulation_points(d, n * k), oracle.articulation_points(e, n * k))
+
+
+@pytest.mark.parametrize("plan", ["one pass", "team"])
+def test_ring_time(ctx, plan, monkeypatch):
+    """2,048 steps at 0.3 us, then a round of 2 us per 256 ids for either end: 3.7 ms
+    for 200,000 vertices, allowed twice that over the relabelled ring's time."""
+    if plan == "team":
+        monkeypatch.setenv("BR_SOLO", "0")
+        monkeypatch.setenv("BR_LDS", "0")
+    V = 200_000
+    e = ring(V)
+    d, r = dev(e), dev(relabelled(e, V))
+    for name, fn in (("find", lambda x: ctx.find(x, V, 1)), ("cut", lambda x: ctx.articulation_points(x, V)),
+                     ("certificate", lambda x: ctx.cert_build(x, V, 1))):
+        a, b = best_ms(lambda: fn(d)), best_ms(lambda: fn(r))
+        say(plan, name, "in order %.3f ms, relabelled %.3f ms" % (a, b))
+        assert a < b + 7.4
