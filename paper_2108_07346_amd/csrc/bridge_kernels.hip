@@ -835,37 +835,25 @@ __global__ void k_tv_list(const uint32_t* q, int32_t qs, const int32_t* first, i
 
 // ---- 2-edge-connected classes of the certificate ----------------------------
 //
-// The classes are the components left once the bridges are removed.  Every
-// edge of F' is a non-tree edge, so never a bridge; a tree edge (parent(v), v)
-// is a bridge iff no edge of F' leaves v's subtree (the test of k_bridges).
-// The non-bridges are united with the larger root hooked under the smaller, so
-// after full compression each vertex's root is the smallest id of its class.
+// The classes are the components left once the bridges are removed.  A tree edge
+// (parent(v), v) is a bridge iff no edge of F' leaves v's subtree (the test of
+// k_bridges).  The path in F between two vertices of one class holds no bridge (a
+// bridge would part them), so the classes are the components of F without its
+// bridges.  The edges left are united with the larger root hooked under the
+// smaller, so after full compression each vertex's root is the smallest id of its
+// class.
 __global__ void k_class_tree(const int2* f1, const uint32_t* q, int32_t qs, const int32_t* first, const int32_t* in_arc,
                              const int32_t* pre, const int32_t* sub, Rmq R, int32_t V, int64_t A, uint32_t* g) {
-    WAVE_LOOP(v, V) {
-        int32_t w = 0;
-        const auto joins = [&] {
-            if (v >= V || first[v] == 0 || q[qs * (size_t)v] == 0) return false;      // no tree edge above v
-            const int32_t a = in_arc[v];
-            if (a < 0 || a >= A) return false;
-            const int32_t l = pre[v], r = pre[v] + sub[v] - 1;
-            if (l < 0 || r < l || r >= V) return false;
-            int32_t mn, mx;
-            range_minmax(R, l, r, mn, mx);
-            w = arc_src(f1, a);
-            return !(mn >= l && mx <= r);                                             // not a bridge
-        };
-        const bool on = joins();
-        tv_unite(g, on, (uint32_t)v, (uint32_t)w);
-    }
-}
-
-__global__ void k_class_cross(const int2* f2, int32_t dir, const uint32_t* cnt, uint32_t* g) {
-    const int64_t n2 = cnt[1];
-    WAVE_LOOP(k, n2) {
-        int2 e = make_int2(0, 0);
-        if (k < n2) e = f2[dir * k];
-        tv_unite(g, e.x != e.y, (uint32_t)e.x, (uint32_t)e.y);
+    GRID_LOOP(v, (int64_t)V) {
+        if (first[v] == 0 || q[qs * (size_t)v] == 0) continue;      // no tree edge above v
+        const int32_t a = in_arc[v];
+        if (a < 0 || a >= A) continue;
+        const int32_t l = pre[v], r = pre[v] + sub[v] - 1;
+        if (l < 0 || r < l || r >= V) continue;
+        int32_t mn, mx;
+        range_minmax(R, l, r, mn, mx);
+        if (mn >= l && mx <= r) continue;                                  // a bridge
+        root_unite(g, 1, (uint32_t)v, (uint32_t)arc_src(f1, a));
     }
 }
 
@@ -1161,7 +1149,6 @@ int device_classes_cert(const int2* f1, const int2* f2, int32_t dir, const uint3
     hipLaunchKernelGGL(k_tv_init, dim3(grid_for(V)), dim3(kT), 0, s, V, g, W.tour_len, W.tree_n, W.posof);
     hipLaunchKernelGGL(k_class_tree, dim3(grid_for(V)), dim3(kT), 0, s, f1, q, qs, W.first, W.in_arc, W.pre, W.sub, R, V, A,
                        g);
-    hipLaunchKernelGGL(k_class_cross, dim3(grid_for(V)), dim3(kT), 0, s, f2, dir, cnt, g);
     hipLaunchKernelGGL(k_tv_compress, dim3(grid_for(V)), dim3(kT), 0, s, g, V);
     hipLaunchKernelGGL(k_class_out, dim3(std::min(grid_for(V), kOutBlocks)), dim3(kT), 0, s, (const uint32_t*)g, V, label,
                        reinterpret_cast<uint32_t*>(W.misc + 1));

@@ -175,6 +175,45 @@ __device__ __forceinline__ bool uf_unite(uint32_t* q, int64_t qs, bool active, u
     }
 }
 
+// Root of x, halving the chain on the way
+__device__ __forceinline__ uint32_t uf_find(uint32_t* q, int64_t qs, uint32_t x) {
+    uint32_t d = ld(q + qs * (int64_t)x);
+    while (d != 0) {
+        const uint32_t p = x - d, dp = ld(q + qs * (int64_t)p);
+        if (dp == 0) return p;
+        st(q + qs * (int64_t)x, d + dp);
+        x = p - dp;
+        d = ld(q + qs * (int64_t)x);
+    }
+    return x;
+}
+
+// Unite u and v, lane by lane: kFreeSteps steps in Rem's order, then root under
+// root, which keeps the chains of a list in vertex order short.  (For tree edges,
+// each of which joins two components.  Classes, 3V edges of a mesh row by row,
+// V = 10^6: 1,725 us in k_class_tree in Rem's order, 137 so; a path 26 us so,
+// 630 and more root under root alone.)
+__device__ __forceinline__ void root_unite(uint32_t* q, int64_t qs, uint32_t u, uint32_t v) {
+    uint32_t pu = u - ld(q + qs * (int64_t)u), pv = v - ld(q + qs * (int64_t)v);
+    if (uf_search<kFreeSteps>(q, qs, u, pu, v, pv) || pu == pv) return;
+    for (;;) {
+        u = uf_find(q, qs, u);
+        v = uf_find(q, qs, v);
+        if (u == v) return;
+        if (u < v) {
+            const uint32_t t = u;
+            u = v;
+            v = t;
+        }
+        uint32_t* w = q + qs * (int64_t)u;
+        uint32_t d = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (d == 0 && __hip_atomic_compare_exchange_strong(w, &d, u - v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT))
+            return;
+        u -= d;
+    }
+}
+
 // Offer edge (u,v) (the lanes that are active) to F, then (if rejected) to F'.
 // su, sv are the endpoints' parent words (F low, F' high), loaded earlier with
 // one 8-byte load each.  F' only joins what F joins, so a shared parent in F'

@@ -172,3 +172,37 @@ def test_ring_time(ctx, plan, monkeypatch):
         a, b = best_ms(lambda: fn(d)), best_ms(lambda: fn(r))
         say(plan, name, "in order %.3f ms, relabelled %.3f ms" % (a, b))
         assert a < b + 7.4
+
+
+def mesh(W, H):
+    """Row by row: right, down and diagonal."""
+    x = np.arange(W * H, dtype=np.int32)
+    right, down = x % W < W - 1, x < W * (H - 1)
+    return np.concatenate([np.stack([x, x + o], 1)[m] for o, m in ((1, right), (W, down), (W + 1, right & down))])
+
+
+@pytest.mark.parametrize("W,H", [(2, 2), (40, 3), (1000, 1000)])
+def test_classes_of_meshes(ctx, W, H):
+    """Classes are what F without its bridges holds together, whatever F' holds: a
+    mesh, a path from it, a ring at the end of that."""
+    e, n = mesh(W, H), W * H
+    tail = np.concatenate([path(9) + n - 1, ring(5) + n + 8 - 1])
+    e, V = np.concatenate([e, tail]), n + 12
+    wl, wt = oracle.bridge_tree(e, V)
+    for x in (e, relabelled(e, V)):
+        d = dev(x)
+        lab, t = ctx.bridge_tree(d, V, 8)
+        wl, wt = oracle.bridge_tree(x, V)
+        assert np.array_equal(lab, wl) and np.array_equal(t, wt)
+        lab, k = ctx.two_edge_components(d, V, 8)
+        assert np.array_equal(lab, wl) and k == np.unique(wl).shape[0]
+
+
+def test_classes_of_a_ring_time(ctx):
+    """The ring's closing edge is in F' and needs no search of its own: within half
+    a millisecond of the bridges' time."""
+    V = 200_000
+    d = dev(ring(V))
+    a, b = best_ms(lambda: ctx.two_edge_components(d, V, 8)), best_ms(lambda: ctx.find(d, V, 8))
+    say("classes %.3f ms, find %.3f ms" % (a, b))
+    assert a < b + 0.5
