@@ -414,10 +414,25 @@ __global__ void k_preorder(const int2* f1, const uint32_t* q, int32_t qs, const 
 // (the other two atomics of the four, 2.2 M in all for 548,000 edges, took half
 // of the 90 us).  A stale word read past is only further from the end it moves
 // to: the atomic then settles it.
+//
+// Where the wavefront's active lanes all touch one end (the edges of a hub listed
+// together), one of them does so for all (800,000 edges of one hub: 3.7 ms, 0.11 so).
+template <class Better>
+__device__ __forceinline__ bool one_for_all(int32_t i, int32_t& v, int32_t now, Better better) {
+    if (__ballot(i != __builtin_amdgcn_readfirstlane(i))) return better(v, now);
+    int32_t best = now;
+    for (uint64_t m = __ballot(better(v, best)); m; m = __ballot(better(v, best))) {
+        const int32_t lo = __shfl(v, __ffsll((unsigned long long)m) - 1), hi = __shfl(v, 63 - __clzll((long long)m));
+        best = better(lo, hi) ? lo : hi;
+    }
+    v = best;
+    return best != now && lane_rank(__ballot(1)) == 0;
+}
 __device__ __forceinline__ void range_touch(int32_t* tmin, int32_t* tmax, int32_t px, int32_t py) {
     const int32_t a = min(px, py), b = max(px, py);
-    if (tmax[a] < b) atomicMax(&tmax[a], b);
-    if (tmin[b] > a) atomicMin(&tmin[b], a);
+    int32_t hi = b, lo = a;
+    if (one_for_all(a, hi, tmax[a], [](int32_t x, int32_t y) { return x > y; })) atomicMax(&tmax[a], hi);
+    if (one_for_all(b, lo, tmin[b], [](int32_t x, int32_t y) { return x < y; })) atomicMin(&tmin[b], lo);
 }
 
 // F' edges pull each endpoint's range toward the other endpoint's number

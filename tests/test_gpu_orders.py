@@ -230,3 +230,14 @@ def test_hub_of_the_largest_id_time(ctx):
     a = best_ms(lambda: ctx.cert_build(d, V, 8))
     say("certificate %.3f ms" % a)
     assert a < 1.2
+
+
+def test_ranges_of_a_hub_time(ctx):
+    """Articulation points of the same star: chaining the hub's arcs takes 2.3 ms
+    (one swap per leaf), its range an atomic per wavefront; 4 ms allowed."""
+    V = 200_000
+    d = dev(np.tile(star(V, V - 1)[::-1], (4, 1)))
+    assert np.array_equal(ctx.articulation_points(d, V), [V - 1])
+    a = best_ms(lambda: ctx.articulation_points(d, V))
+    say("cut %.3f ms" % a)
+    assert a < 4
