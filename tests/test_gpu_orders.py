@@ -241,3 +241,35 @@ def test_ranges_of_a_hub_time(ctx):
     a = best_ms(lambda: ctx.articulation_points(d, V))
     say("cut %.3f ms" % a)
     assert a < 4
+
+
+@pytest.mark.parametrize("leaves", [64, 65, 131_072, 131_073, 150_000])
+def test_bridges_of_hubs_in_order(ctx, leaves):
+    """Runs of one vertex's bridges at the limits of the sort on the device: 64 keys,
+    and ends 131,072 ids apart; beside them a path's worth of short runs."""
+    n = 9000
+    V = max(1 << 17, leaves + 1) + n
+    far = np.arange(V - n, V, dtype=np.int32)
+    hub = np.stack([np.arange(1, leaves + 1, dtype=np.int32), np.zeros(leaves, np.int32)], 1)
+    rng = np.random.default_rng(leaves)
+    e = np.concatenate([hub, np.stack([far[:-1], far[1:]], 1), np.stack([far[:70], far[:70] + 0], 1)])
+    e = e[rng.permutation(len(e))]
+    want = oracle.bridges(e, V)
+    d = dev(e)
+    assert np.array_equal(ctx.find(d, V, 3), want)
+    assert np.array_equal(ctx.bridge_tree(d, V, 3)[1], oracle.bridge_tree(e, V)[1])
+
+
+def test_union_of_stars_time(ctx):
+    """40 stars of 20,000 vertices in one batch, 800,000 bridges: the keys leave the
+    device in order (host sort alone: 5 ms and more); 6 ms allowed for the call."""
+    V, G = 20_000, 40
+    s = star(V, 0)
+    d = dev(np.tile(s, (G, 1)))
+    off = np.arange(G + 1, dtype=np.int64) * len(s)
+    Vs = np.full(G, V, np.int32)
+    pairs, boff = ctx.find_batched(d, off, Vs, 32768)
+    assert np.array_equal(boff, off) and all(np.array_equal(pairs[off[g]:off[g + 1]], s) for g in range(G))
+    a = best_ms(lambda: ctx.find_batched(d, off, Vs, 32768))
+    say("batch %.3f ms" % a)
+    assert a < 6
