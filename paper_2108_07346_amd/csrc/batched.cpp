@@ -111,8 +111,8 @@ struct BatchState {
         size_t arena_h_cap = 0;
     } arenas[2];
     std::unique_ptr<BatchPlan> transient[2];
-    // graphs past the small kernel's V as one disjoint union: its edges and the
-    // table that describes it (device, pinned host); grown, never shrunk
+    // graphs past the small kernel's V as disjoint unions: the edges of one and the
+    // table that describes it (device, pinned host); at most kUnionEdges edges
     void *union_d = nullptr, *union_h = nullptr;
     size_t union_d_cap = 0, union_h_cap = 0;
 };
@@ -540,12 +540,15 @@ static int gather_big(BatchState& st, BatchPlan& P, std::vector<std::vector<int3
     return BR_OK;
 }
 
-// Bridges of the graphs gs (indices into the batch) through one plain query over
-// their disjoint union; out[k] = pairs of graph gs[k].  Per graph the 160 KB
+// Bridges of the graphs gs (indices into the batch) through plain queries over
+// disjoint unions of them; out[k] = pairs of graph gs[k].  Per graph the 160 KB
 // kernel took a CU for its chunks and merges in turn (150 graphs of 100 to
 // 24,000 vertices: 1,040 of 1,860 us); the union gives every CU edges of all
-// of them.
+// of them.  A union is a copy of its graphs' edges, so it is kept to 1 GiB (the query
+// over one takes 0.3 ms and more whatever its size, the copy 0.4); a graph that
+// stands alone, as one past that does, is queried where it lies.
 constexpr int64_t kUnionRun = 64;        // rows per workgroup of the list's long part (32,768 edges per table)
+constexpr int64_t kUnionEdges = int64_t(1) << 27;
 static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const int64_t* eoff, const int32_t* V,
                       const std::vector<int32_t>& gs, std::vector<std::vector<int32_t>>& out) {
     const int32_t n = (int32_t)gs.size();
@@ -560,6 +563,7 @@ static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const i
         const int64_t row = union_row();
         while (k1 < n && vt + V[gs[k1]] <= kFinalStepMaxV) {
             const int64_t m = eoff[gs[k1] + 1] - eoff[gs[k1]], nr = (m + row - 1) / row;
+            if (k1 > k0 && et + nr * row > kUnionEdges) break;
             vbase.push_back(vt);
             at.push_back(et);
             for (int64_t r = 0; r < nr; r += kUnionRun)
@@ -572,6 +576,19 @@ static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const i
             k1++;
         }
         vbase.push_back(vt);
+        if (k1 - k0 == 1) {
+            const int32_t g = gs[k0];
+            const TuneEntry knobs{{"fuse", 1}};
+            out[k0].resize(2 * (size_t)(V[g] - 1));
+            int64_t nb = 0;
+            const int rc = bridges_find(c, d_edges + 2 * eoff[g], eoff[g + 1] - eoff[g], V[g], 1, out[k0].data(), V[g] - 1, &nb,
+                                        st.stream, &knobs);
+            if (rc == BR_ERANGE) return fail(BR_ERANGE, "batched: an edge has a vertex id outside its graph's [0, V)");
+            if (rc) return rc;
+            out[k0].resize(2 * (size_t)nb);
+            k0 = k1;
+            continue;
+        }
         const size_t ebytes = a256(8 * (size_t)et), rbytes = a256(sizeof(RowItem) * rows.size());
         const size_t tbytes = rbytes + sizeof(UnionItem) * (size_t)(k1 - k0);
         if (st.union_d_cap < ebytes + tbytes) {
@@ -603,7 +620,7 @@ static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const i
         c->fused.items = reinterpret_cast<const RowItem*>(dt);
         c->fused.n_items = (int32_t)rows.size();
         c->fused.item_words = (int32_t)(((max_v + 1) / 2 + 3) & ~3);
-        const TuneEntry knobs{{"fuse", 1}, {"table", k1 - k0 == 1 ? 1 : 0}};
+        const TuneEntry knobs{{"fuse", 1}, {"table", 0}};
         std::vector<int32_t> pairs(2 * (size_t)std::max<int64_t>(vt - (k1 - k0), 1));
         int64_t nb = 0;
         const int rc = bridges_find(c, du, et, (int32_t)vt, 1, pairs.data(), (int64_t)pairs.size() / 2, &nb, st.stream, &knobs);
