@@ -126,6 +126,15 @@ int64_t part_lo(int64_t E, int64_t M, int64_t i) { return i * (E / M) + (i * (E 
 
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
+int64_t chunks_of(int64_t E, int32_t C) { return std::max<int64_t>(1, (E + C - 1) / C); }
+
+// the same limit for every graph of up to batched_max_v_big() vertices, also those
+// that are not split into chunks after all
+int check_chunks(int32_t g, int64_t E, int32_t C) {
+    const int64_t M = chunks_of(E, C);
+    return M < (1 << 20) ? BR_OK : fail(BR_EINVAL, "batched: graph %d needs %lld chunks", g, (long long)M);
+}
+
 // Plan of one class of the batch: the small class takes the graphs with
 // V <= batched_max_v_dev() (and lists those above batched_max_v_big() as
 // `large`, for the plain path); the big class the graphs in between.
@@ -171,8 +180,8 @@ int build_plan(BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, i
         }
         // a run keeps at most what both forests take
         P.sbase[s + 1] = P.sbase[s] + std::min(E, 2 * runs * Vs);
-        const int64_t M = is_long ? 1 : std::max<int64_t>(1, (E + C - 1) / C);
-        if (M >= (1 << 20)) return fail(BR_EINVAL, "batched: graph %d needs %lld chunks", P.small[s], (long long)M);
+        if (int rc = check_chunks(P.small[s], E, C)) return rc;
+        const int64_t M = is_long ? 1 : chunks_of(E, C);
         P.Mg[s] = (int32_t)M;
         P.rbase[s] = rest;
         rest += M - 1;
@@ -761,7 +770,10 @@ int batched_query(br_ctx* c, const int32_t* d_edges, const int64_t* h_edge_off, 
     BatchPlan* PM = nullptr;
     std::vector<int32_t> mid;
     for (int32_t g = 0; g < G; g++)
-        if (h_V[g] > batched_max_v_dev() && h_V[g] <= batched_max_v_big()) mid.push_back(g);
+        if (h_V[g] > batched_max_v_dev() && h_V[g] <= batched_max_v_big()) {
+            if ((rc = check_chunks(g, h_edge_off[g + 1] - h_edge_off[g], C))) return rc;
+            mid.push_back(g);
+        }
     if (!mid.empty() && mode != 1) {
         rc = transient ? get_transient(c, st, h_edge_off, h_V, G, C, 1, &PM, true)
                        : get_plan(c, st, h_edge_off, h_V, G, C, 1, &PM, true);

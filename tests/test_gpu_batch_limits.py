@@ -94,3 +94,21 @@ def test_unions_next_to_each_other(br):
             ctx.find_batched(bad, off, np.array(V, np.int32), 1 << 20)
         assert x.value.code == br.BR_ERANGE
     ctx.close()
+
+
+@pytest.mark.parametrize("V", [100, 4096, 4097, 40_000])
+def test_chunks_per_graph(br, V):
+    """A graph of 2^20 chunks or more is refused, whether it would be split into them
+    or not; one fewer is taken."""
+    n = 1 << 20
+    e = np.random.default_rng(V).integers(0, V, size=(n, 2)).astype(np.int32)
+    d = torch.from_numpy(e).cuda()
+    ctx = br.Context(0)
+    Vs = np.array([V, 5], np.int32)
+    with pytest.raises(br.BridgeError) as x:
+        ctx.find_batched(d, np.array([0, n, n], np.int64), Vs, 1)
+    assert x.value.code == br.BR_EINVAL
+    for m, chunk in ((n, 2), (n - 1, 1)):
+        pairs, off = ctx.find_batched(d[:m], np.array([0, m, m], np.int64), Vs, chunk)
+        assert np.array_equal(pairs, oracle.bridges(e[:m], V)) and list(off) == [0, len(pairs), len(pairs)]
+    ctx.close()
