@@ -71,7 +71,10 @@ Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo, const TuneEntry
     const int lds_want = knob("BR_LDS", "lds", -1);
     const bool plan_env = env_int("BR_SOLO", -1) >= 0 || env_int("BR_LDS", -1) >= 0;   // wins over a tuned "fuse"
     const int fuse = plan_env ? env_int("BR_FUSE", -1) : knob("BR_FUSE", "fuse", -1);
-    const bool named = knob("BR_SOLO", "solo", -1) >= 0 || lds_want >= 0;
+    // "lds" 1 asks for the plan of small graphs: past those it is the one pass (a
+    // tuner entry serves a power of two of V; 50,000 vertices with the entry of
+    // 40,000 went to the tree)
+    const bool named = knob("BR_SOLO", "solo", -1) >= 0 || lds_want == 0;
     // graphs that fit a workgroup's LDS never take the tree unless told to
     const bool small_v = V <= batched_max_v_big() && lds_want != 0;
     if (allow_solo && E > 0 && (fuse == 1 || (fuse < 0 && (!named || small_v)))) {
@@ -986,7 +989,8 @@ int br_autotune(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t
         std::vector<TuneEntry> cands;
         if (E > 0) cands.push_back({{"fuse", 1}});
         for (int tile : {4096, 2048, 1024}) cands.push_back({{"lds", 0}, {"solo", 0}, {"tile", tile}});
-        if (E > 0 && V <= batched_max_v_big()) cands.push_back({{"lds", 1}});
+        const TuneEntry lds{{"lds", 1}};
+        if (make_plan(E, V, M, true, &lds).lds) cands.push_back(lds);      // (else the same launches as "fuse")
         if (E > 0 && V <= solo_max_v()) {
             for (int v = 0; v < solo_variants(); v++) {
                 TuneEntry on{{"lds", 0}, {"solo", 1}, {"variant", v}};
