@@ -41,7 +41,7 @@ static int env_int(const char* name, int dflt) {
 
 std::string plain_tune_key(int device, int64_t E, int32_t V, int32_t M) {
     return arch_name(device) + "|plain|v" + std::to_string(log2_bucket(V)) + "|e" + std::to_string(log2_bucket(E)) +
-           "|m" + std::to_string(M);
+           "|m" + std::to_string(M) + kTuneGen;
 }
 
 Plan plan_for(int device, int64_t E, int32_t V, int32_t M) {

@@ -471,7 +471,7 @@ std::string shape_key(int device, const int64_t* eoff, const int32_t* V, int32_t
     int32_t mv = 0;
     for (int32_t g = 0; g < G; g++) mv = std::max(mv, V[g]);
     return arch_name(device) + "|batched|g" + std::to_string(log2_bucket(G)) + "|e" + std::to_string(log2_bucket(E)) +
-           "|v" + std::to_string(log2_bucket(mv));
+           "|v" + std::to_string(log2_bucket(mv)) + kTuneGen;
 }
 
 bool same_shape(const BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, int32_t C, int32_t bpc, bool big) {

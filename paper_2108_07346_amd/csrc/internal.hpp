@@ -83,6 +83,11 @@ class Pool {
 using TuneEntry = std::map<std::string, double>;
 std::string arch_name(int device);      // e.g. "gfx950"
 int log2_bucket(int64_t x);             // smallest b with 2^b >= x
+// Ends every key.  To be raised when what an entry's names select changes, or what
+// the choice was measured on: "p2" is since lists are certified in one pass, when
+// an entry that names a tree began to switch that off (the large list: 120 ms
+// where the one pass takes 1.8).
+constexpr const char* kTuneGen = "|p2";
 bool tune_get(const std::string& key, TuneEntry& out);
 void tune_put(const std::string& key, const TuneEntry& e);   // also saved to BR_AUTOTUNE_CACHE if set
 

@@ -2,9 +2,10 @@
 // input-shape bucket, kept in memory and, when BR_AUTOTUNE_CACHE names a
 // file, in that file (JSON) so that later processes start tuned.
 //
-// File format: one JSON object whose keys are "<arch>|<path>|<bucket>" and
-// whose values are flat objects of numbers, e.g.
-//   {"gfx950|plain|v19|e30|m4096": {"solo": 1, "variant": 1, "wpc": 1, ...}}
+// File format: one JSON object whose keys are "<arch>|<path>|<bucket>|<generation
+// of the plans>" and whose values are flat objects of numbers, e.g.
+//   {"gfx950|plain|v19|e30|m4096|p2": {"solo": 1, "variant": 1, "wpc": 1, ...}}
+// Entries of another generation stay in the file and are not used.
 // Written whole to a temporary file and renamed over the old one.
 #include <cctype>
 #include <cstdio>

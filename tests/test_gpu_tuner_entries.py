@@ -54,3 +54,51 @@ def test_small_graph_entry_past_the_small_graphs(tmp_path):
     assert child(cache, 50_000, 120_000, 8)["kind"] == 3
     cache.write_text(json.dumps({key: {"lds": 0, "solo": 0, "tile": 4096}}))
     assert child(cache, 50_000, 120_000, 8)["kind"] == 0       # a tree asked for by name
+
+
+def test_entries_of_earlier_plans(tmp_path):
+    """A file written before lists were certified in one pass (keys of five parts)
+    names trees; it is neither used nor lost."""
+    cache = tmp_path / "tune.json"
+    key = child(cache, 50_000, 120_000, 8, tune=1)["tuned"]["key"]
+    old = "|".join(key.split("|")[:5])
+    cache.write_text(json.dumps({old: {"lds": 0, "solo": 1, "variant": 2}}))
+    assert child(cache, 50_000, 120_000, 8)["kind"] == 3
+    assert child(cache, 50_000, 120_000, 8, tune=1)["tuned"]["source"] == "measured"
+    saved = json.loads(cache.read_text())
+    assert saved[old] == {"lds": 0, "solo": 1, "variant": 2} and len(saved) == 2
+
+
+BATCH = r"""
+import sys
+sys.path.insert(0, %r)
+import numpy as np, torch, oracle
+import paper_2108_07346_amd as br
+V = 500
+es = [np.random.default_rng(g).integers(0, V, size=(3000, 2)).astype(np.int32) for g in range(20)]
+d = torch.from_numpy(np.concatenate(es)).cuda()
+ctx = br.Context(0)
+pairs, off = ctx.find_batched(d, np.arange(21, dtype=np.int64) * 3000, np.full(20, V, np.int32), 0)
+assert all(np.array_equal(pairs[off[g]:off[g + 1]], oracle.bridges(e, V)) for g, e in enumerate(es))
+print("CHUNK", int(ctx.profile()["rounds"]), flush=True)
+""" % ROOT
+
+
+def test_batch_entries_of_earlier_plans(tmp_path):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cache = tmp_path / "tune.json"
+
+    def run():
+        r = subprocess.run([sys.executable, "-u", "-c", BATCH], env=dict(os.environ, BR_AUTOTUNE_CACHE=str(cache)),
+                           capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return int(r.stdout.split("CHUNK")[1])
+
+    run()
+    [key] = json.loads(cache.read_text())
+    old = "|".join(key.split("|")[:5])
+    cache.write_text(json.dumps({old: {"chunk_edges": 1234, "blocks_per_cu": 1}}))
+    assert run() != 1234
+    saved = json.loads(cache.read_text())
+    assert saved[old]["chunk_edges"] == 1234 and len(saved) == 2
