@@ -223,9 +223,10 @@ int32_t br_lds_max_v(void);
  * default; then the winner again with its team merges requesting each
  * thread's edges at once, and (one-workgroup-per-node) with the siblings'
  * certificates of its own merges bucketed by endpoint ranges, then with its
- * chunks in input order instead of bucketed.  Each candidate computes
- * the certificate of d_edges (one settling run, best of two timed runs, HIP
- * events on `stream`).  The choice is kept in memory and, when the
+ * chunks in input order instead of bucketed.  Each candidate runs
+ * br_bridges_find on d_edges without handing out pairs (V above 2^29: its
+ * certificate alone): one settling run, then the best of two timed runs, of five
+ * where they are short.  The choice is kept in memory and, when the
  * environment variable BR_AUTOTUNE_CACHE names a file, in that file (JSON,
  * keyed by GPU architecture and shape bucket), where later processes find it
  * without measuring; a shape already in the cache is not measured again.

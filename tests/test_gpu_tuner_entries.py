@@ -102,3 +102,29 @@ def test_batch_entries_of_earlier_plans(tmp_path):
     assert run() != 1234
     saved = json.loads(cache.read_text())
     assert saved[old]["chunk_edges"] == 1234 and len(saved) == 2
+
+
+def test_plans_are_timed_over_the_whole_query():
+    """A sparse list, whose final step takes longer than its certificate: what the
+    tuner reports as the winner's time is the query's (the certificate is a quarter
+    of it), and ids out of range stay no error of the tuner."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import time
+
+    import paper_2108_07346_amd as br
+    V, E, M = 100_003, 200_000, 3
+    e = np.random.default_rng(V).integers(0, V, size=(E, 2)).astype(np.int32)
+    d = torch.from_numpy(e).cuda()
+    ctx = br.Context(0)
+    ms = ctx.autotune(d, V, M)["ms"]
+    best = 1e30
+    for _ in range(10):
+        a = time.perf_counter()
+        ctx.find(d, V, M)
+        best = min(best, 1000 * (time.perf_counter() - a))
+    print("tuner %.3f ms, query %.3f ms" % (ms, best), flush=True)
+    assert ms > 0.5 * best
+    e[7, 1] = V
+    assert ctx.autotune(torch.from_numpy(e).cuda(), V, M + 1)["source"] == "measured"
+    ctx.close()
