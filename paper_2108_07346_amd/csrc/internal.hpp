@@ -304,6 +304,7 @@ int launch_lds_cert(const Plan& P, const DevBufs& B, const FusedBufs& F, const C
 // The contracted certificate (contract.hpp, contract_kernels.hip): edges of F
 // that cross components of F', at most kMaxCross of them and of their ends.
 constexpr int kMaxCross = 16384;
+constexpr int kContractCounters = 4;       // words behind hid: hcnt, solved, deep
 struct Contract {
     uint32_t* hid = nullptr;       // [V] 1 + number in H of a root of F' (zero at launch)
     uint32_t* hcnt = nullptr;      // [2] H's vertices and edges (zero at launch)

@@ -38,7 +38,7 @@ __global__ void __launch_bounds__(kT) k_lds_cert(DevBufs B, int64_t E, int32_t V
     const uint32_t V = (uint32_t)Vi, tid = threadIdx.x;
     for (uint32_t x = tid; x < V; x += kT) q[x] = 0;
     if (C.hid)
-        for (uint32_t x = tid; x < V + 2; x += kT) C.hid[x] = 0;       // and H's counters behind it
+        for (uint32_t x = tid; x < V + kContractCounters; x += kT) C.hid[x] = 0;
     if (tid == 0) {
         H.n12 = H.ncross = H.nvert = 0;
         *B.err = 0;
