@@ -333,6 +333,8 @@ int run_certificate(br_ctx* c, const int32_t* d_a, int64_t Ea, const int32_t* d_
     c->bws = reinterpret_cast<int32_t*>(base + L.bws);
     c->prof.plan_kind = P.kind;
     c->prof.rounds = P.rounds;
+    c->route.final_step = device_final ? 1 : 0;
+    c->route.past = P.code_per > 0 ? 1 : P.fused && !P.table && c->fused.items && P.s2 > 1 && P.s2 < P.s1 ? 2 : 0;
     if (P.fused || P.lds) {
         rc = fused_prepare();
         if (rc == BR_OK && P.lds) rc = lds_cert_prepare();
@@ -580,6 +582,7 @@ static int contracted_step(br_ctx* c, const Plan& P, const DevBufs& B, const Fin
         if (rc) return rc;
         BR_HIP(hipStreamSynchronize(s));
         *solved = fin.h_status[6] != 0;
+        c->route.final_step = !*solved ? 1 : fin.done ? 4 : again ? 3 : 2;
         if (*solved || again || !fin.h_status[8]) return BR_OK;
     }
 }
@@ -966,6 +969,15 @@ int br_articulation_points(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t
         return fail(BR_ECAP, "br_articulation_points: %lld articulation points, capacity %lld", (long long)aps.size(),
                     (long long)cap);
     std::copy(aps.begin(), aps.end(), h_out);
+    return BR_OK;
+}
+
+// For the tests of the dispatch rules (br::Route, in its order); not part of the interface.
+int br_route(br_ctx* c, int64_t* out) {
+    if (!c || !out) return fail(BR_EINVAL, "br_route: null argument");
+    const Route& r = c->route;
+    const int64_t v[5] = {r.final_step, r.past, r.longs, r.in_unions, r.alone};
+    std::copy(v, v + 5, out);
     return BR_OK;
 }
 

@@ -569,7 +569,7 @@ static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const i
         std::vector<int64_t> vbase, at;
         std::vector<RowItem> rows;       // runs of rows of one graph: a workgroup's share of the list
         int32_t max_v = 0;
-        const int64_t row = union_row();
+        const int64_t row = kRow;
         while (k1 < n && vt + V[gs[k1]] <= kFinalStepMaxV) {
             const int64_t m = eoff[gs[k1] + 1] - eoff[gs[k1]], nr = (m + row - 1) / row;
             if (k1 > k0 && et + nr * row > kUnionEdges) break;
@@ -585,6 +585,7 @@ static int find_union(br_ctx* c, BatchState& st, const int32_t* d_edges, const i
             k1++;
         }
         vbase.push_back(vt);
+        (k1 - k0 == 1 ? c->route.alone : c->route.in_unions) += k1 - k0;
         if (k1 - k0 == 1) {
             const int32_t g = gs[k0];
             const TuneEntry knobs{{"fuse", 1}};
@@ -787,6 +788,8 @@ int batched_query(br_ctx* c, const int32_t* d_edges, const int64_t* h_edge_off, 
         if (rc) return rc;
     }
     std::vector<std::vector<int32_t>> mid_out;
+    c->route.longs = (int64_t)P->longs.size();
+    c->route.in_unions = c->route.alone = 0;
     if (!mid.empty() && mode == 1) {
         rc = find_union(c, st, d_edges, h_edge_off, h_V, mid, mid_out);
         if (rc) {

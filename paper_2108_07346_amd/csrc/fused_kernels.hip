@@ -37,7 +37,6 @@ namespace br {
 
 namespace {
 
-constexpr int kRow = 512;              // edges per row, the unit the stages deal in
 constexpr int kRowBlock = 512;
 constexpr int kMaxRows = 8;            // rows per workgroup of the offering stages
 constexpr int kFilterBlock = 1024;
@@ -458,8 +457,6 @@ void plan_fused(Plan& P) {
                 break;
             }
 }
-
-int32_t union_row() { return kRow; }
 
 int fused_prepare() {
     static const hipError_t e = [] {

@@ -280,7 +280,9 @@ struct FusedBufs {
     const RowItem* items = nullptr;
     int32_t n_items = 0, item_words = 0;
 };
-int32_t union_row();               // edges per row: a graph of a union starts at a whole row
+// Edges per row, the unit that the stages deal in: k_lds_cert takes some rows,
+// k_filter the others, and a graph of a union starts at a whole row.
+constexpr int kRow = 512;
 void plan_fused(Plan& P);
 bool plan_lds(Plan& P);            // false: V is past what that plan is for
 int fused_prepare();               // once per process: the kernels' LDS limit
@@ -413,6 +415,22 @@ struct Arena {
 
 }  // namespace br
 
+namespace br {
+// Which branch of a rule answered, for the tests of its limits: every branch gives
+// the same answer.
+struct Route {
+    // the plain path's final step: 0 host, 1 tours, 2 contracted, 3 the same on the
+    // state compressed first, 4 in the certificate's launch
+    int64_t final_step = 0;
+    // the long part of a one-pass list: 0 none or by rows, 1 past one table, 2 past a
+    // table per graph of a union
+    int64_t past = 0;
+    // the last batch: graphs certified from a sample and runs; graphs in unions;
+    // graphs of the same class queried alone
+    int64_t longs = 0, in_unions = 0, alone = 0;
+};
+}  // namespace br
+
 struct br_ctx {
     int device = 0;
     br::Arena ws;                  // device workspace
@@ -425,6 +443,7 @@ struct br_ctx {
     int profiling = 0;
     size_t keys_hint = 0;          // bridges found by the previous call (first copy size)
     int final_step = 1;            // 0: host search (Algorithm 1), 1: device bridge step
+    br::Route route;               // branches that the last call took (br_route)
     int32_t* bws = nullptr;        // device bridge-step scratch inside the workspace
     br::FusedBufs fused;           // the one-pass certificate's table buffers inside the workspace
     br::Contract contract;         // contracted final step's scratch inside the workspace

@@ -22,7 +22,6 @@ namespace br {
 namespace {
 
 constexpr int kT = kSolveT;
-constexpr int kRow = 512;
 constexpr int kU = 4;                       // edges per thread and step
 
 struct LdsHead {
