@@ -121,8 +121,11 @@ __global__ void __launch_bounds__(256) k_labels(const uint32_t* q, int64_t qs, i
 }  // namespace
 
 int contract_prepare() {
-    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_solve),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SolveLds));
+    static OncePerDevice once;
+    const hipError_t e = once([] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_solve), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)sizeof(SolveLds));
+    });
     return e == hipSuccess ? BR_OK : hip_fail(e, "hipFuncSetAttribute(k_solve)");
 }
 

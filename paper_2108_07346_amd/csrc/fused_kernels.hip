@@ -459,11 +459,12 @@ void plan_fused(Plan& P) {
 }
 
 int fused_prepare() {
-    static const hipError_t e = [] {
+    static OncePerDevice once;
+    const hipError_t e = once([] {
         for (hipError_t r : {raise_lds<2>(), raise_lds<4>(), raise_lds<8>(), raise_lds<16>(), raise_lds<32>()})
             if (r != hipSuccess) return r;
         return hipSuccess;
-    }();
+    });
     return e == hipSuccess ? BR_OK : hip_fail(e, "hipFuncSetAttribute(k_filter)");
 }
 

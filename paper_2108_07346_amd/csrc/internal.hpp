@@ -78,6 +78,26 @@ class Pool {
     bool stop_ = false;
 };
 
+// What f() gives on the current device, from one call per device of the process (a
+// kernel's attributes are set device by device).
+class OncePerDevice {
+public:
+    template <class Fn>
+    hipError_t operator()(Fn f) {
+        int d = 0;
+        const hipError_t e = hipGetDevice(&d);
+        if (e != hipSuccess) return e;
+        std::lock_guard<std::mutex> g(mu_);
+        auto it = done_.find(d);
+        if (it == done_.end()) it = done_.emplace(d, f()).first;
+        return it->second;
+    }
+
+private:
+    std::mutex mu_;
+    std::map<int, hipError_t> done_;
+};
+
 // ---- tuner (tuner.cpp) ----------------------------------------------------------
 // A tuned choice: named numbers ("solo", "variant", "chunk_edges", ...).
 using TuneEntry = std::map<std::string, double>;
@@ -285,7 +305,7 @@ struct FusedBufs {
 constexpr int kRow = 512;
 void plan_fused(Plan& P);
 bool plan_lds(Plan& P);            // false: V is past what that plan is for
-int fused_prepare();               // once per process: the kernels' LDS limit
+int fused_prepare();               // once per device: the kernels' LDS limit
 // zeroes `bytes` (a multiple of 16) at base and writes node 0's region table
 void launch_fused_init(void* base, size_t bytes, int64_t* off, int64_t* cap, int64_t cap0, hipStream_t s);
 int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_t s);   // kernels enqueued
@@ -298,7 +318,7 @@ void launch_filter_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, hip
 int launch_list_rest(const Plan& P, const DevBufs& B, const FusedBufs& F, uint32_t* g, int2* out, uint32_t* nout,
                      uint32_t room, hipStream_t s);
 struct Contract;
-int lds_cert_prepare();            // once per process: the kernel's LDS limit
+int lds_cert_prepare();            // once per device: the kernel's LDS limit
 // mode >= 0: the final step too where the list is offered whole (arguments as launch_contract)
 int launch_lds_cert(const Plan& P, const DevBufs& B, const FusedBufs& F, const Contract& C, int mode, uint32_t* h_status,
                     void* h_data, uint64_t* h_tree, hipStream_t s);
@@ -319,7 +339,7 @@ struct Contract {
     uint32_t* hcls = nullptr;      // ... its class's smallest vertex
     uint32_t *core = nullptr, *corej = nullptr, *tree = nullptr, *treej = nullptr, *non = nullptr, *root = nullptr;
 };
-int contract_prepare();            // once per process: the kernel's LDS limit
+int contract_prepare();            // once per device: the kernel's LDS limit
 size_t contract_clear_words(int32_t V);    // words that must be zero at launch
 size_t contract_words();                   // scratch words
 Contract contract_carve(uint32_t* cleared, uint32_t* scratch, int32_t V);

@@ -165,8 +165,11 @@ bool plan_lds(Plan& P) {
 }
 
 int lds_cert_prepare() {
-    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_cert),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
+    static OncePerDevice once;
+    const hipError_t e = once([] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_cert), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   160 * 1024 - 256);
+    });
     return e == hipSuccess ? BR_OK : hip_fail(e, "hipFuncSetAttribute(k_lds_cert)");
 }
 
