@@ -29,10 +29,11 @@ bound), divided by its duration from HIP events recorded on the call's stream
 during the timed steps, against the 8 TB/s HBM3E peak.  "traffic" is the
 counter-measured HBM bytes per launch from the committed rocprofv3 summary,
 when that summary was taken from the current kernel source (else null).
-"method_bytes_at_M" is the method's own traffic at the configured M -- the
-edge list read once, every certificate edge written to its node's region and
-read once more by its merge, from the library's per-node counts -- over the
-timed certificate phases (phase 0 and every merge).
+"method_bytes_at_M" is the method's own traffic -- the edge list read once,
+every certificate edge written to its node's region and read once more by its
+merge, from the library's per-node counts -- over the timed certificate phases.
+Its "chunks" says over how many chunks the plan works: the configured M for a
+tree plan, 1 for the one pass, which has no merges.
 """
 import argparse
 import hashlib
@@ -603,7 +604,7 @@ def main():
     method_at_m = None
     if alg_m > 0 and phases["ms_cert"] > 0:
         gbs = alg_m / (phases["ms_cert"] / 1000) / 1e9
-        method_at_m = {"bytes": alg_m, "ms_cert": round(phases["ms_cert"], 4), "GBs": gbs, "frac": gbs / PEAK_GBS}
+        method_at_m = {"bytes": alg_m, "chunks": M if plan_kind < 2 else 1, "ms_cert": round(phases["ms_cert"], 4), "GBs": gbs, "frac": gbs / PEAK_GBS}
     detail = {"phases_ms": {k: round(v, 5) for k, v in phases.items()}, "bridges": int(out.shape[0]),
               "certificate_edges": int(prof["cert_f1"] + prof["cert_f2"]), "merge_rounds": int(prof["rounds"]),
               "plan": PLAN_NAMES[plan_kind], "tuner": tuned,

@@ -202,25 +202,27 @@ int br_certificate_bridges(const int32_t* h_f1, int64_t n1, const int32_t* h_f2,
  *   h_bridge_off host int64 [G+1].
  * Synchronous.  BR_ECAP if cap < total bridges (h_bridge_off is still filled).
  * Graphs with V above the library's in-LDS limit (br_batched_max_v()) are
- * processed through br_bridges_find inside the call.
+ * processed through plain queries inside the call, those of up to br_lds_max_v()
+ * vertices several at a time (over a copy of their edges, 1 GiB at most).
  */
 int br_bridges_find_batched(br_ctx* ctx, const int32_t* d_edges, const int64_t* h_edge_off, const int32_t* h_V,
                             int32_t G, int32_t chunk_edges, int32_t* h_bridges, int64_t cap, int64_t* h_bridge_off,
                             void* stream);
 int32_t br_batched_max_v(void);
 /* Largest V of a graph whose union-find state (Algorithm 2, two 16-bit parent
- * offsets per vertex) fits one workgroup's 160 KB of LDS: the batched path
- * certifies such graphs there, the plain path plans for them (plan_kind 2). */
+ * offsets per vertex) fits one workgroup's 160 KB of LDS: with final step 0 the
+ * batched path certifies such graphs there, by default it queries unions of them,
+ * and the plain path reports plan_kind 2. */
 int32_t br_lds_max_v(void);
 
 /*
  * br_autotune -- measure the launch shapes of the certificate path for this
  * device and input shape and keep the fastest for later calls on inputs of
- * the same shape bucket (V and E in powers of two, the same M): the whole
- * list in one pass, the team path (many workgroups per chunk) with three first-stage tiles, the
- * plan for graphs that fit a workgroup's LDS, and the one-workgroup-per-node path in
- * each worker shape with the depths of the merges it does itself around its
- * default; then the winner again with its team merges requesting each
+ * the same shape bucket (V and E in powers of two, the same M): the whole list
+ * in one pass, the team path (many workgroups per chunk) with three first-stage
+ * tiles, the one-workgroup plan of graphs up to 8,192 vertices, and the
+ * one-workgroup-per-node path in each worker shape with the depths of the merges
+ * it does itself around its default; then the winner again with its team merges requesting each
  * thread's edges at once, and (one-workgroup-per-node) with the siblings'
  * certificates of its own merges bucketed by endpoint ranges, then with its
  * chunks in input order instead of bucketed.  Each candidate runs
@@ -273,7 +275,8 @@ typedef struct br_profile {
                               8 per edge of a right sibling's certificate read
                               by its merge (the merges carry state, so a
                               region's final size counts every edge written
-                              to it once); 0 otherwise                         */
+                              to it once; plan 3 has one region and no merge);
+                              0 otherwise                                      */
 } br_profile;
 int br_set_profiling(br_ctx* ctx, int on);
 

@@ -193,7 +193,8 @@ class Context:
         return lab[:int(V)].copy(), tree[:nt.value].copy()
 
     def articulation_points(self, edges, V: int, stream=None) -> np.ndarray:
-        """Articulation points (int32 vertex ids ascending) through the scan-first certificate."""
+        """Articulation points (int32 vertex ids ascending): from a spanning forest and the blocks
+        that all edges group it into; with final step 0 through the scan-first certificate."""
         ptr, E = _edges_arg(edges)
         out = np.empty(max(int(V), 1), dtype=np.int32)
         n = ctypes.c_int64(0)
@@ -387,7 +388,7 @@ def probe_read(buf, stream=None) -> None:
 
 
 def lds_max_v() -> int:
-    """Largest V whose whole phase tree the library can run in one workgroup's LDS."""
+    """Largest V of a graph whose union-find state fits one workgroup's LDS."""
     return int(load().br_lds_max_v())
 
 

@@ -1,12 +1,15 @@
 // Batched bridge queries: G independent graphs, one persistent launch.
 //
 // Host side of the batched path: plans the per-graph phase trees (chunks of
-// chunk_edges edges, node regions, merge counters), orders the work items
-// largest-first, captures "clear counters -> persistent kernel -> copy
-// certificates to the host" in a HIP graph that is replayed while the batch
-// shape and input buffer stay the same, then runs the final depth-first
-// search of every graph on a pool of host threads.  chunk_edges = 0 asks the
-// library's tuner, which times candidate chunk sizes and workgroups per CU on
+// chunk_edges edges, node regions, merge counters; for long lists a sample and
+// runs), orders the work items largest-first, and captures "clear counters ->
+// persistent kernel -> runs and finishes of the long lists" and "bridges of the
+// graphs left over" in HIP graphs that are replayed while the batch shape and
+// input buffer stay the same.  With the final step on the device the bridges come
+// back; with final step 0 the certificates do, and a pool of host threads searches
+// them.  Graphs past the small kernel's V go through plain queries over unions of
+// them, those past a CU's LDS through one plain query each.  chunk_edges = 0 asks
+// the library's tuner, which times candidate chunk sizes and workgroups per CU on
 // the batch itself and remembers the winner per device and batch shape
 // (tuner.cpp).
 #include <algorithm>
@@ -24,12 +27,7 @@
 
 namespace br {
 
-
-
 namespace {
-
-// simple fixed pool of host threads for the final search
-
 
 struct BatchPlan {
     // key
@@ -53,8 +51,8 @@ struct BatchPlan {
     int2* h_area0 = nullptr;
     uint32_t* h_cnt0 = nullptr;
     uint32_t* h_err = nullptr;
-    // final step on the device: the certificates of all small graphs as one
-    // certificate of their disjoint union (vertex ids shifted by vbase)
+    // first vertex of each small graph where their vertices are counted through
+    // (roots' flags, the long graphs' states)
     std::vector<int64_t> vbase;      // [S+1]
     int64_t vtot = 0;
     // final step on the device: per graph bridge keys (u << 16 | v, sorted) in
@@ -75,7 +73,6 @@ struct BatchPlan {
     const void* graph_edges = nullptr;
     int graph_mode = -1;
     int blocks = 0;
-    int32_t max_v = 0;
     bool owns = true;                // dmem / hmem allocated for this plan (else borrowed arenas)
     size_t dbytes = 0;
     ~BatchPlan() {
@@ -151,7 +148,6 @@ int build_plan(BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, i
         if (V[g] > lo && V[g] <= hi) P.small.push_back(g);
         else if (!big && V[g] > batched_max_v_big()) P.large.push_back(g);
     }
-    for (int32_t g : P.small) P.max_v = std::max(P.max_v, V[g]);
     const int32_t S = (int32_t)P.small.size();
     // per small graph (indexed by position s in P.small): chunks, nodes, counters
     P.Mg.resize(S);
@@ -358,9 +354,9 @@ int build_plan(BatchPlan& P, const int64_t* eoff, const int32_t* V, int32_t G, i
     return BR_OK;
 }
 
-// enqueue clear -> kernel -> copies on s (captured into P.graph on first use)
-// the captured part: clear the counters, the persistent kernel, and with the
-// final step on the device the combined certificate and its bridge step
+// The captured parts.  0: clear the counters, the persistent kernel, the long
+// lists' runs and finishes.  1 (final step on the device): the bridges of the graphs
+// that the kernel left, by size class.
 int enqueue(BatchPlan& P, const int32_t* d_edges, hipStream_t s, int mode, int part, BatchState* st) {
     P.dev.edges = reinterpret_cast<const int2*>(d_edges);
     if (part == 0) {

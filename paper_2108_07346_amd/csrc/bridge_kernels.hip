@@ -206,7 +206,9 @@ __global__ void __launch_bounds__(kT) k_rank(const int2* f1, const uint32_t* cnt
 // so that no input order lines the gaps up) is a splitter.  k_succ writes every
 // arc's successor; k_walk follows each splitter's arcs to the next splitter, one
 // load per arc, and leaves in each arc's word the splitter and its distance from
-// it; k_rank_split jumps over the splitters alone; k_spread adds the two up.
+// it; k_rank_split jumps over the splitters alone; k_spread adds the two up.  (The
+// sparse ruling set of Reid-Miller and of Helman and JaJa, with Wyllie's jumps over
+// the ruling arcs.)
 // The arcs before a tour's first splitter are walked from the tour's head, twice:
 // the first walk finds the splitter (or the tour's end), the second writes.
 // What bounds it: random lines, about three per arc in k_walk and k_spread and
@@ -1075,11 +1077,6 @@ void device_scan1(int32_t* a, int64_t n, uint64_t* status, uint32_t* ticket, hip
     hipLaunchKernelGGL(k_scan1, dim3((unsigned)cdiv(n, kSB)), dim3(kT), 0, s, a, n, status, ticket);
 }
 
-// Bridges of a certificate held on the device: F = f1[0..cnt[0]), F' =
-// f2[dir*k] for k < cnt[1] (counts read on the device), vertex v is the root of
-// its tree of F iff q[qs*v] == 0.  Writes up to V keys at *d_keys and their
-// number at *d_n; *d_n sits 4 bytes into a 256-byte status block that the keys
-// follow directly.
 // The keys at `keys` (*n of them) in canonical order at `out`, status word 7 set
 // if that is done (else the host sorts them); pos: V words.
 static void order_keys(const BridgeWs& W, int32_t V, const uint64_t* keys, const uint32_t* n, uint64_t* out, uint32_t* pos,
@@ -1164,6 +1161,11 @@ static BridgeWs number_tree(const int2* f1, const int2* f2, int32_t dir, const u
     return W;
 }
 
+// Bridges of a certificate held on the device: F = f1[0..cnt[0]), F' =
+// f2[dir*k] for k < cnt[1] (counts read on the device), vertex v is the root of
+// its tree of F iff q[qs*v] == 0.  Writes up to V keys at *d_keys and their
+// number at *d_n; *d_n sits 4 bytes into a 256-byte status block that the keys
+// follow directly.
 int device_bridges_cert(const int2* f1, const int2* f2, int32_t dir, const uint32_t* cnt, const uint32_t* q, int32_t qs,
                         int32_t V, const uint32_t* err, int32_t* ws, uint64_t** d_keys, uint32_t** d_n, hipStream_t s) {
     const int64_t A = 2 * (int64_t)std::max(V - 1, 1);

@@ -362,8 +362,8 @@ void launch_copy_out(const Plan& P, const DevBufs& B, int32_t* d_out, int64_t ou
                      hipStream_t s);
 
 // The plan of one query.  tuned: a tuner entry for this shape (knobs it
-// names replace the size rules); environment variables BR_SOLO, BR_SOLO_TOP,
-// BR_SOLO_WPC and BR_SOLO_VARIANT replace both (measurements).
+// names replace the size rules); environment variables BR_FUSE, BR_SOLO, BR_LDS
+// and those of the tree plans' shapes replace both (measurements).
 Plan make_plan(int64_t E, int32_t V, int32_t M, bool allow_solo = true, const TuneEntry* tuned = nullptr);
 // make_plan with the tuner's entry for this device and shape, if any
 Plan plan_for(int device, int64_t E, int32_t V, int32_t M);
@@ -485,9 +485,9 @@ struct br_ctx {
 namespace br {
 int ensure_workspace(br_ctx* c, size_t bytes, hipStream_t s);
 // br_bridges_find; plan_knobs: plan with these knobs instead of the tuner's entry
+// (with "table" 0 the list is a union of graphs, whose row items c->fused holds)
 int bridges_find(br_ctx* c, const int32_t* d_edges, int64_t E, int32_t V, int32_t M, int32_t* h_bridges, int64_t cap,
                  int64_t* n_bridges, void* stream, const TuneEntry* plan_knobs);
-// (knobs with "table" 0: c->fused holds the union's row items)
 // br_bridges_find_batched after argument checks; transient: the batch shape
 // is used once (serving ticks): plans built in reused arenas, launched
 // without graph capture, chunk size from the tuner's cache or a default
