@@ -501,11 +501,9 @@ int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_
     const int64_t nrows = (P.E + kRow - 1) / kRow;
     const int64_t m1 = (nrows + P.s1 - 1) / P.s1, m2 = (nrows + P.s2 - 1) / P.s2;
     const int cus = g_cus > 0 ? g_cus : 256;
-    auto rows = [&](int64_t nsel, int32_t mul, uint32_t div, int want) {
+    auto rows = [&](int64_t nsel, int32_t mul, uint32_t div, int64_t rpw_want) {
         if (nsel <= 0) return;
-        // as many workgroups as the chip holds at once before a workgroup takes
-        // a second row: the chains of dependent reads decide, not the launch
-        const int32_t rpw = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kMaxRows, nsel / want));
+        const int32_t rpw = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kMaxRows, rpw_want));
         hipLaunchKernelGGL(k_rows, dim3((unsigned)((nsel + rpw - 1) / rpw)), dim3(kRowBlock), 0, s, B, P.E, P.V, P.cap[0],
                            (uint32_t)nsel, mul, div, rpw);
         launches++;
@@ -514,10 +512,17 @@ int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_
         launch_flatten(P, B, codes ? F.rcode : nullptr, F.ncode, s);
         launches++;
     };
-    rows(m1, P.s1, 0, 4 * cus);
+    // Most of stage 1 is accepted: as many workgroups as the chip holds at once before
+    // a workgroup takes a second row (the chains of dependent reads decide, not the
+    // launch).  Few of stage 2's edges are, and its workgroups wait for each other's
+    // reservations, 12 ns each: half as many (dense 874 rows: 23.3 us with a workgroup
+    // each, 19.2 so; large 3,130 rows: 64.4 us in threes, 48.3 in sevens).
+    const auto spread = [&](int64_t nsel) { return nsel / (4 * cus); };
+    const auto gathered = [&](int64_t nsel) { return (nsel + 2 * cus - 1) / (2 * cus); };
+    rows(m1, P.s1, 0, spread(m1));
     if (P.s2 < P.s1) {
         flatten(false);
-        rows(m2 - m1, P.s2, 3, 4 * cus);
+        rows(m2 - m1, P.s2, 3, gathered(m2 - m1));
     }
     if (P.s2 > 1) {
         const uint32_t nsel = (uint32_t)(nrows - m2), div = (uint32_t)(P.s2 - 1);
@@ -531,7 +536,7 @@ int launch_fused(const Plan& P, const DevBufs& B, const FusedBufs& F, hipStream_
             return launches + 1;
         }
         if (P.code_per == 0) {
-            rows(nsel, 1, div, 4 * cus);
+            rows(nsel, 1, div, spread(nsel));
             return launches;
         }
         launch_codes(P, B.state, B.qs, F, s, &launches);
