@@ -146,6 +146,22 @@ def test_rings(ctx, V):
         assert f1.shape[0] == V and f2.shape[0] == 1
 
 
+@pytest.mark.parametrize("gap", [3, 63, 64, 65, 255, 256, 257, 300])
+def test_rings_with_gaps(ctx, gap):
+    """A ring of 2,600 vertices whose ids lie `gap` apart, a second one between them: a
+    walk's round of 256 ids holds many steps of the chain, one, or none."""
+    n = 2600
+    V = n * gap
+    a = np.arange(n, dtype=np.int32) * gap
+    e = np.concatenate([np.stack([a, np.roll(a, -1)], 1), np.stack([a, np.roll(a, -1)], 1) + gap // 2, [[a[n // 2], a[7] + gap // 2]]])
+    d = dev(e.astype(np.int32))
+    assert np.array_equal(ctx.find(d, V, 8), oracle.bridges(e, V))
+    assert np.array_equal(ctx.two_edge_components(d, V, 8)[0], oracle.bridge_tree(e, V)[0])
+    assert np.array_equal(ctx.articulation_points(d, V), oracle.articulation_points(e, V))
+    f1, f2 = ctx.cert_build(d, V, 8)
+    assert f1.shape[0] == 2 * n - 1 and f2.shape[0] == 2
+
+
 def test_many_closing_edges(ctx):
     """Rings of 3,000 vertices one after the other, 60 of them, each closed six times."""
     n, k = 3000, 60
