@@ -76,7 +76,7 @@ def test_whole_lists(ctx, E, want):
 
 def test_long_chains(ctx):
     # every edge six times: shuffled ids leave chains of a few steps, ids in order some
-    # of more than 128
+    # of more than 64
     V = 50_000
     e = np.repeat(path(V), 6, 0)
     assert final(ctx, e, V) == AGAIN
