@@ -278,7 +278,8 @@ def test_bridges_of_hubs_in_order(ctx, leaves):
 
 def test_union_of_stars_time(ctx):
     """40 stars of 20,000 vertices in one batch, 800,000 bridges: the keys leave the
-    device in order (host sort alone: 5 ms and more); 6 ms allowed for the call."""
+    device in order (host sort alone: 5 ms and more, 10 to 11 for the call); 8 ms
+    allowed for the call."""
     V, G = 20_000, 40
     s = star(V, 0)
     d = dev(np.tile(s, (G, 1)))
@@ -288,4 +289,4 @@ def test_union_of_stars_time(ctx):
     assert np.array_equal(boff, off) and all(np.array_equal(pairs[off[g]:off[g + 1]], s) for g in range(G))
     a = best_ms(lambda: ctx.find_batched(d, off, Vs, 32768))
     say("batch %.3f ms" % a)
-    assert a < 6
+    assert a < 8
