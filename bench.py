@@ -335,7 +335,7 @@ def bench_articulation(args):
         assert np.array_equal(want, out)
         cpu = {"value": g.E * reps / dtc, "unit": "edges/s", "cores": 1, "kind": "oracle",
                "sample": "whole dense workload, %d repetition(s) in %.1f s, one host core" % (reps, dtc)}
-    line = {"metric": "articulation points: edges/s (scan-first certificate and cut-vertex test on the GPU)",
+    line = {"metric": "articulation points: edges/s (spanning forest and cut-vertex test on the GPU)",
             "value": g.E * args.steps / dt, "unit": "edges/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "ms_per_step": 1000 * dt / args.steps, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
             "dtype": "int32", "data": "synthetic (seeded planted-cluster generator)",
