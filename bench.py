@@ -288,10 +288,9 @@ def bench_figures(args):
 
 
 def bench_articulation(args):
-    """Articulation points of the dense workload: the scan-first certificate and
-    the cut-vertex test on it, both on the GPU (the default final step); the
-    host low-link search over the copied certificate (final step 0) timed as a
-    detail; the oracle (the low-link search on the whole graph) beside it."""
+    """Articulation points of the dense workload: a spanning forest of the list and
+    the cut-vertex test over its blocks on the GPU; the scan-first certificate with
+    Algorithm 1's search on the host is reported under "detail"."""
     import numpy as np
     import torch
     import graphgen
